@@ -36,7 +36,16 @@ __device__ __forceinline__ T tab(const T *p, long i)
 // One thread per line (FP64 contexts, and FP32 contexts whose source product takes the plain scan W):
 // block = one lateral tile pb and one octet of angular lines a = 8*oct + e (e = tid/32), 32 cells
 // pt = tid%32.  FP32 contexts with the split-BF16 product use epass8_body below.
-template <typename T, int MODE, bool BANDS = false>
+//
+// What bounds it at the sizes that take it (short angular grids, FP64): the serial chain over the groups.  A
+// wave's next loads used to wait for its own stores (one memory counter, in order), so a group cost a store
+// plus a load round trip.  EP_RING groups are now in flight in a register ring, every load issued before the
+// stores of the groups ahead of it and without a branch (past the last group it re-reads group 0): 44 -> 28 us
+// at 4 x 4 cells, 11 x 11 angles, 60 groups; 47 -> 29 us at 16 x 16, 7 x 7, 48 groups in FP64; 81 -> 58 us at
+// 20 x 24, 15 x 15, 60 groups in FP64; unchanged where the grid fills the chip (64 x 64 cells).  A ring of 1
+// gives 31 / 36 / 67 us there, one of 4 the same as 2 but 6 % less at 64 x 64 cells for its registers.
+constexpr int EP_RING = 2;
+template <typename T, int MODE, bool BANDS, bool HASQ>
 __device__ __forceinline__ void epass_body(const EParams<T> &P, int bx)
 {
     constexpr bool CL = (MODE & MODE_CLOSE) != 0;
@@ -59,23 +68,33 @@ __device__ __forceinline__ void epass_body(const EParams<T> &P, int bx)
     T U0b[4] = {}, U1b[4] = {}, U2b[4] = {};   // per-band scans (BANDS)
     double ph0 = 0, ph1 = 0, ph2 = 0, injc = 0, injo = 0;
     T fic = 0, fio = 0, fme = 0, fmn = 0;   // surrogate records (energy sent to the next generation, moments)
-    const bool hasQ = P.Q != nullptr, hasW = P.W != nullptr;
+    const bool hasW = P.W != nullptr;
     const bool feat = P.inj_c != nullptr;
-    for (int g = P.G - 1; g >= 0; --g) {
+    T rx1[EP_RING], rx2[EP_RING], rqc[EP_RING], rqo[EP_RING];
+    auto fetch = [&](int g, T &f1, T &f2, T &fqc, T &fqo) {
+        const long gc = max(g, 0);
+        const T *p = P.psi + (2L * gc) * S + line;
+        f1 = p[0];
+        f2 = p[S];
+        // trapezoidal sources of the two half-steps: Q^n + Q* (close), Q^n + Q* (open)
+        fqc = fqo = T(0);
+        if constexpr (HASQ) {
+            const long o = gc * S + line;
+            if (CL) fqc = P.Q[o];
+            if (OP) fqo = P.Q[QS + o];
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < EP_RING; ++u) fetch(P.G - 1 - u, rx1[u], rx2[u], rqc[u], rqo[u]);
+    auto group = [&](const int g, const int u) {
         T *p1 = P.psi + (2L * g) * S + line;
         T *p2 = p1 + S;
-        const T x1 = *p1, x2 = *p2;
+        const T x1 = rx1[u], x2 = rx2[u], qc = rqc[u], qo = rqo[u];
+        fetch(g - EP_RING, rx1[u], rx2[u], rqc[u], rqo[u]);
         const T sm = tab(P.Sm, g), sp = tab(P.Sp, g), kp = tab(P.kap, g);
         // rho-free operator: psi1 row [-(S-+k), S-], psi2 row [-3S+, -(S+ + 2S- + k)], coupling S+[1,3]
         const T d11 = -(sm + kp), d12 = sm, d21 = T(-3) * sp, d22 = -(sp + T(2) * sm + kp);
         const T c1 = sp, c2 = T(3) * sp;
-        // trapezoidal sources of the two half-steps: Q^n + Q* (close), Q^n + Q* (open)
-        T qc = 0, qo = 0;
-        if (hasQ) {
-            const long o = (long)g * S + line;
-            if (CL) qc = P.Q[o];
-            if (OP) qo = P.Q[QS + o];
-        }
         T y1 = x1, y2 = x2;
         if (CL) {
             const T f = fin + fcl;
@@ -108,7 +127,7 @@ __device__ __forceinline__ void epass_body(const EParams<T> &P, int bx)
             ph1 += P.dBot * ((double)y1 - (double)y2);
             if (OP) ph2 += P.dBot * ((double)z1 - (double)z2);
         }
-        if (hasQ) {
+        if constexpr (HASQ) {
             const double wi = tab(P.dInj, g);
             if (CL) injc += wi * (double)qc;
             if (OP) injo += wi * (double)qo;
@@ -153,7 +172,15 @@ __device__ __forceinline__ void epass_body(const EParams<T> &P, int bx)
         fin = x1 - x2;
         fcl = y1 - y2;
         fop = z1 - z2;
+    };
+    int g0 = P.G - 1;
+    for (; g0 >= EP_RING - 1; g0 -= EP_RING) {
+#pragma unroll
+        for (int u = 0; u < EP_RING; ++u) group(g0 - u, u);
     }
+#pragma unroll
+    for (int u = 0; u < EP_RING - 1; ++u)
+        if (g0 - u >= 0) group(g0 - u, u);
     if (CL) P.dep_c[line] = dac * (ph0 + ph1 - injc) * P.scale;
     if (OP) P.dep_o[line] = dao * (ph1 + ph2 - injo) * P.scale;
     if (feat) {
@@ -166,21 +193,21 @@ __device__ __forceinline__ void epass_body(const EParams<T> &P, int bx)
     }
 }
 
-template <typename T, int MODE, bool BANDS>
+template <typename T, int MODE, bool BANDS, bool HASQ>
 __global__ __launch_bounds__(256) void epass_kernel(EParams<T> P)
 {
-    epass_body<T, MODE, BANDS>(P, blockIdx.x);
+    epass_body<T, MODE, BANDS, HASQ>(P, blockIdx.x);
 }
 
-template <typename T, bool BANDS>
+template <typename T, bool BANDS, bool HASQ>
 static void launch_epass_t(const EParams<T> &P, int mode, unsigned nb, hipStream_t st)
 {
     if (mode == MODE_PAIR)
-        hipLaunchKernelGGL((epass_kernel<T, MODE_PAIR, BANDS>), dim3(nb), dim3(256), 0, st, P);
+        hipLaunchKernelGGL((epass_kernel<T, MODE_PAIR, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
     else if (mode == MODE_OPEN)
-        hipLaunchKernelGGL((epass_kernel<T, MODE_OPEN, BANDS>), dim3(nb), dim3(256), 0, st, P);
+        hipLaunchKernelGGL((epass_kernel<T, MODE_OPEN, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
     else
-        hipLaunchKernelGGL((epass_kernel<T, MODE_CLOSE, BANDS>), dim3(nb), dim3(256), 0, st, P);
+        hipLaunchKernelGGL((epass_kernel<T, MODE_CLOSE, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
 }
 
 template <typename T>
@@ -189,10 +216,13 @@ hipError_t launch_epass(const EParams<T> &P, int mode, hipStream_t st)
     if (P.Wh != nullptr) return hipErrorInvalidValue;   // split scans: launch_epass8
     if (P.NB > 4) return hipErrorInvalidValue;
     const unsigned nb = (unsigned)((P.NLINE / P.NAPT) * P.NOCT);
-    if (P.NB > 1)
-        launch_epass_t<T, true>(P, mode, nb, st);
-    else
-        launch_epass_t<T, false>(P, mode, nb, st);
+    if (P.NB > 1) {
+        if (P.Q) launch_epass_t<T, true, true>(P, mode, nb, st);
+        else launch_epass_t<T, true, false>(P, mode, nb, st);
+    } else {
+        if (P.Q) launch_epass_t<T, false, true>(P, mode, nb, st);
+        else launch_epass_t<T, false, false>(P, mode, nb, st);
+    }
     return hipGetLastError();
 }
 
@@ -386,7 +416,10 @@ template hipError_t launch_epass_strag<double>(const EParams<double> &, int, hip
 #define EP_ST(v, p) __builtin_nontemporal_store(v, p)
 __device__ __forceinline__ float bf16_to_f32(unsigned short h) { return __builtin_bit_cast(float, (unsigned)h << 16); }
 // FEAT / LO = false compile out the surrogate records and the lo half of the split scans.
-template <int MODE, bool FEAT = true, bool LO = true, bool BANDS = false>
+// RING > 0 keeps that many groups in flight in a register ring (HASQ: with the BF16 source), as the
+// one-line-per-thread pass does: for grids with too few waves to hide a group's store and load round trip.
+// The arithmetic is the same either way, bit for bit.
+template <int MODE, bool FEAT = true, bool LO = true, bool BANDS = false, int RING = 0, bool HASQ = false>
 __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
 {
     constexpr int L = PBS_EPASS_LPT;
@@ -418,7 +451,7 @@ __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
     float rcc[L] = {}, rco[L] = {};
     double ph0 = 0, ph1 = 0, ph2 = 0, injc = 0, injo = 0;
     float fic = 0, fio = 0, fme = 0, fmn = 0;
-    const bool hasQ = P.Q != nullptr, hasW = P.Wh != nullptr, hasL = LO && P.Wl != nullptr,
+    const bool hasQ = RING ? HASQ : P.Q != nullptr, hasW = P.Wh != nullptr, hasL = LO && P.Wl != nullptr,
                feat = FEAT && P.inj_c != nullptr;
     const bool qbf = hasQ && P.Qb != nullptr;
     const int NAq = (NA + 3) & ~3;
@@ -426,41 +459,81 @@ __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
     typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
     static_assert(L == 4, "the BF16 source is read as 4-line chunks");
     const long SB = (long)P.G * NPB * P.NOCT * (PBS_PT * 8);
-    for (int g = P.G - 1; g >= 0; --g) {
+    // ring loads: no branch (a line past the last node reads the last one's value, dropped at its use; a
+    // group past the last one re-reads group 0)
+    constexpr int R = RING ? RING : 1;
+    float rx1[R][L], rx2[R][L];
+    u16x4 rqc[R], rqo[R];
+    const float *lp[L];
+    const unsigned short *qp = nullptr;
+    if constexpr (RING > 0) {
+#pragma unroll
+        for (int e = 0; e < L; ++e) lp[e] = P.psi + ((long)pbk * NA + min(8 * oct + L * sub + e, NA - 1)) * PBS_PT + pt;
+        if constexpr (HASQ) qp = P.Qb + ((long)pbk * NAq + min(8 * oct + L * sub, NAq - L)) * PBS_PT + pt * L;
+    }
+    auto fetch = [&](int g, int u) {
+        const long gc = max(g, 0);
+#pragma unroll
+        for (int e = 0; e < L; ++e) {
+            rx1[u][e] = EP_LD(lp[e] + 2 * gc * S);
+            rx2[u][e] = EP_LD(lp[e] + (2 * gc + 1) * S);
+        }
+        if constexpr (HASQ) {
+            const unsigned short *q = qp + gc * NPB * NAq * PBS_PT;
+            if (CL) rqc[u] = EP_LD(reinterpret_cast<const u16x4 *>(q));
+            if (OP) rqo[u] = EP_LD(reinterpret_cast<const u16x4 *>(q + QSb));
+        }
+    };
+    auto group = [&](const int g, const int u) {
+#pragma clang fp contract(off)
+        // every fused operation is written out: the variants of this pass (and the batched one) then give the
+        // same bits whatever the compiler would contract in each
         const float sm = tab(P.Sm, g), sp = tab(P.Sp, g), kp = tab(P.kap, g);
-        const float d11 = -(sm + kp), d12 = sm, d21 = -3.f * sp, d22 = -(sp + 2.f * sm + kp);
+        const float d11 = -(sm + kp), d12 = sm, d21 = -3.f * sp, d22 = -(fmaf(2.f, sm, sp) + kp);
         const float c1 = sp, c2 = 3.f * sp;
-        const float mc11 = 1.f - ac * d11, mc12 = -ac * d12, mc21 = -ac * d21, mc22 = 1.f - ac * d22;
-        const float mo11 = 1.f - ao * d11, mo12 = -ao * d12, mo21 = -ao * d21, mo22 = 1.f - ao * d22;
-        const float ic = CL ? fast_rcp(mc11 * mc22 - mc12 * mc21) : 0.f;
-        const float io = OP ? fast_rcp(mo11 * mo22 - mo12 * mo21) : 0.f;
+        const float mc11 = fmaf(-ac, d11, 1.f), mc12 = -ac * d12, mc21 = -ac * d21, mc22 = fmaf(-ac, d22, 1.f);
+        const float mo11 = fmaf(-ao, d11, 1.f), mo12 = -ao * d12, mo21 = -ao * d21, mo22 = fmaf(-ao, d22, 1.f);
+        const float ic = CL ? fast_rcp(fmaf(mc11, mc22, -(mc12 * mc21))) : 0.f;
+        const float io = OP ? fast_rcp(fmaf(mo11, mo22, -(mo12 * mo21))) : 0.f;
         float *p1 = P.psi + (2L * g) * S + line0;
         float *p2 = p1 + S;
         float x1[L], x2[L], qc[L], qo[L];
+        if constexpr (RING > 0) {
 #pragma unroll
-        for (int e = 0; e < L; ++e) {
-            const bool v = e < nval;
-            x1[e] = v ? EP_LD(&p1[e * PBS_PT]) : 0.f;
-            x2[e] = v ? EP_LD(&p2[e * PBS_PT]) : 0.f;
-            qc[e] = qo[e] = 0.f;
-            if (hasQ && !qbf && v) {
-                const long o = (long)g * S + line0 + e * PBS_PT;
-                if (CL) qc[e] = EP_LD(&P.Q[o]);
-                if (OP) qo[e] = EP_LD(&P.Q[QS + o]);
+            for (int e = 0; e < L; ++e) {
+                const bool v = e < nval;
+                x1[e] = v ? rx1[u][e] : 0.f;
+                x2[e] = v ? rx2[u][e] : 0.f;
+                qc[e] = HASQ && CL && v ? bf16_to_f32(rqc[u][e]) : 0.f;
+                qo[e] = HASQ && OP && v ? bf16_to_f32(rqo[u][e]) : 0.f;
             }
-        }
-        if (qbf && nval > 0) {
-            // the BF16 source holds the thread's 4 lines of one cell as one 8-byte chunk
-            const long o = (((long)g * NPB + pbk) * NAq + 8 * oct + L * sub) * PBS_PT + pt * L;
-            if (CL) {
-                const u16x4 c = EP_LD(reinterpret_cast<const u16x4 *>(P.Qb + o));
+            fetch(g - RING, u);
+        } else {
 #pragma unroll
-                for (int e = 0; e < L; ++e) qc[e] = e < nval ? bf16_to_f32(c[e]) : 0.f;
+            for (int e = 0; e < L; ++e) {
+                const bool v = e < nval;
+                x1[e] = v ? EP_LD(&p1[e * PBS_PT]) : 0.f;
+                x2[e] = v ? EP_LD(&p2[e * PBS_PT]) : 0.f;
+                qc[e] = qo[e] = 0.f;
+                if (hasQ && !qbf && v) {
+                    const long o = (long)g * S + line0 + e * PBS_PT;
+                    if (CL) qc[e] = EP_LD(&P.Q[o]);
+                    if (OP) qo[e] = EP_LD(&P.Q[QS + o]);
+                }
             }
-            if (OP) {
-                const u16x4 c = EP_LD(reinterpret_cast<const u16x4 *>(P.Qb + QSb + o));
+            if (qbf && nval > 0) {
+                // the BF16 source holds the thread's 4 lines of one cell as one 8-byte chunk
+                const long o = (((long)g * NPB + pbk) * NAq + 8 * oct + L * sub) * PBS_PT + pt * L;
+                if (CL) {
+                    const u16x4 c = EP_LD(reinterpret_cast<const u16x4 *>(P.Qb + o));
 #pragma unroll
-                for (int e = 0; e < L; ++e) qo[e] = e < nval ? bf16_to_f32(c[e]) : 0.f;
+                    for (int e = 0; e < L; ++e) qc[e] = e < nval ? bf16_to_f32(c[e]) : 0.f;
+                }
+                if (OP) {
+                    const u16x4 c = EP_LD(reinterpret_cast<const u16x4 *>(P.Qb + QSb + o));
+#pragma unroll
+                    for (int e = 0; e < L; ++e) qo[e] = e < nval ? bf16_to_f32(c[e]) : 0.f;
+                }
             }
         }
         const float w = tab(P.wc, g), dec = tab(P.wdec, g), idE = tab(P.invdE, g);
@@ -472,18 +545,18 @@ __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
             float y1 = x1[e], y2 = x2[e];
             if (CL) {
                 const float f = fin[e] + fcl[e];
-                const float r1 = x1[e] + ac * (d11 * x1[e] + d12 * x2[e] + c1 * f + qc[e]);
-                const float r2 = x2[e] + ac * (d21 * x1[e] + d22 * x2[e] + c2 * f);
-                y1 = (r1 * mc22 - mc12 * r2) * ic;
-                y2 = (mc11 * r2 - mc21 * r1) * ic;
+                const float r1 = fmaf(ac, fmaf(c1, f, fmaf(d12, x2[e], d11 * x1[e])) + qc[e], x1[e]);
+                const float r2 = fmaf(ac, fmaf(c2, f, fmaf(d21, x1[e], d22 * x2[e])), x2[e]);
+                y1 = fmaf(r1, mc22, -(mc12 * r2)) * ic;
+                y2 = fmaf(mc11, r2, -(mc21 * r1)) * ic;
             }
             float z1 = y1, z2 = y2;
             if (OP) {
                 const float f = (CL ? fcl[e] : fin[e]) + fop[e];
-                const float r1 = y1 + ao * (d11 * y1 + d12 * y2 + c1 * f + qo[e]);
-                const float r2 = y2 + ao * (d21 * y1 + d22 * y2 + c2 * f);
-                z1 = (r1 * mo22 - mo12 * r2) * io;
-                z2 = (mo11 * r2 - mo21 * r1) * io;
+                const float r1 = fmaf(ao, fmaf(c1, f, fmaf(d12, y2, d11 * y1)) + qo[e], y1);
+                const float r2 = fmaf(ao, fmaf(c2, f, fmaf(d21, y1, d22 * y2)), y2);
+                z1 = fmaf(r1, mo22, -(mo12 * r2)) * io;
+                z2 = fmaf(mo11, r2, -(mo21 * r1)) * io;
             }
             if (e < nval) {
                 EP_ST(z1, &p1[e * PBS_PT]);
@@ -510,17 +583,17 @@ __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
                     for (int b = 0; b < 4; ++b)
                         if (b < P.NB) {
                             const float d = tab(P.wdecb, (long)b * P.G + g), wb = b == bg ? w : 0.f;
-                            if (CL) U0[e] += (U0b[b][e] = wb * x1[e] + d * U0b[b][e]);
-                            U1[e] += (U1b[b][e] = wb * y1 + d * U1b[b][e]);
-                            if (OP) U2[e] += (U2b[b][e] = wb * z1 + d * U2b[b][e]);
+                            if (CL) U0[e] += (U0b[b][e] = fmaf(wb, x1[e], d * U0b[b][e]));
+                            U1[e] += (U1b[b][e] = fmaf(wb, y1, d * U1b[b][e]));
+                            if (OP) U2[e] += (U2b[b][e] = fmaf(wb, z1, d * U2b[b][e]));
                         }
                 } else {
-                    if (CL) U0[e] = w * x1[e] + dec * U0[e];
-                    U1[e] = w * y1 + dec * U1[e];
-                    if (OP) U2[e] = w * z1 + dec * U2[e];
+                    if (CL) U0[e] = fmaf(w, x1[e], dec * U0[e]);
+                    U1[e] = fmaf(w, y1, dec * U1[e]);
+                    if (OP) U2[e] = fmaf(dec, U2[e], w * z1);
                 }
-                const float vc = CL ? (U0[e] + U1[e]) * idE : 0.f;
-                const float vo = OP ? (U1[e] + U2[e]) * idE : 0.f;
+                const float uc = CL ? U0[e] + U1[e] : 0.f, uo = OP ? U1[e] + U2[e] : 0.f, vc = uc * idE;
+                const float vo = uo * idE;
                 if (hasL) {
                     const __bf16 bc = (__bf16)vc, bo = (__bf16)vo;
                     hc[e] = __builtin_bit_cast(unsigned short, bc);
@@ -533,7 +606,7 @@ __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
                     // only the rounded value enters the product: round with error feedback along the
                     // groups, so that the line's rounding errors telescope in the number and energy of
                     // the re-emitted protons instead of adding up
-                    const float tc = vc + rcc[e], to = vo + rco[e];
+                    const float tc = fmaf(uc, idE, rcc[e]), to = fmaf(uo, idE, rco[e]);
                     const __bf16 bc = (__bf16)tc, bo = (__bf16)to;
                     hc[e] = __builtin_bit_cast(unsigned short, bc);
                     ho[e] = __builtin_bit_cast(unsigned short, bo);
@@ -542,11 +615,11 @@ __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
                 }
                 if (feat) {
                     const float wi = (float)tab(P.dInj, g);
-                    if (CL) fic += wi * vc;
+                    if (CL) fic = fmaf(wi, vc, fic);
                     if (OP) {
-                        fio += wi * vo;
-                        fme += (float)tab(P.wmom, g) * z1 + (float)tab(P.wmom, 2L * P.G + g) * z2;
-                        fmn += (float)tab(P.wmom, (long)P.G + g) * z1;
+                        fio = fmaf(wi, vo, fio);
+                        fme += fmaf((float)tab(P.wmom, g), z1, (float)tab(P.wmom, 2L * P.G + g) * z2);
+                        fmn = fmaf((float)tab(P.wmom, (long)P.G + g), z1, fmn);
                     }
                 }
             }
@@ -556,18 +629,18 @@ __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
         }
         // deposit functional (FP64), summed over the lines: A, B depend on the energy group only
         const double A = tab(P.dA, g), B = tab(P.dB, g);
-        if (CL) ph0 += A * s0a + B * s0b;
-        ph1 += A * s1a + B * s1b;
-        if (OP) ph2 += A * s2a + B * s2b;
+        if (CL) ph0 += fma(A, s0a, B * s0b);
+        ph1 += fma(A, s1a, B * s1b);
+        if (OP) ph2 += fma(A, s2a, B * s2b);
         if (g == 0) {
-            if (CL) ph0 += P.dBot * (s0a - s0b);
-            ph1 += P.dBot * (s1a - s1b);
-            if (OP) ph2 += P.dBot * (s2a - s2b);
+            if (CL) ph0 = fma(P.dBot, s0a - s0b, ph0);
+            ph1 = fma(P.dBot, s1a - s1b, ph1);
+            if (OP) ph2 = fma(P.dBot, s2a - s2b, ph2);
         }
         if (hasQ) {
             const double wi = tab(P.dInj, g);
-            if (CL) injc += wi * sqc;
-            if (OP) injo += wi * sqo;
+            if (CL) injc = fma(wi, sqc, injc);
+            if (OP) injo = fma(wi, sqo, injo);
         }
         if (hasW) {
             const long ob = (((long)g * NPB + pbk) * P.NOCT + oct) * (PBS_PT * 8) + pt * 8 + L * sub;
@@ -580,6 +653,20 @@ __device__ __forceinline__ void epass8_body(const EParams<float> &P, long gid)
                 }
             }
         }
+    };
+    if constexpr (RING > 0) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) fetch(P.G - 1 - u, u);
+        int g0 = P.G - 1;
+        for (; g0 >= R - 1; g0 -= R) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) group(g0 - u, u);
+        }
+#pragma unroll
+        for (int u = 0; u < R - 1; ++u)
+            if (g0 - u >= 0) group(g0 - u, u);
+    } else {
+        for (int g = P.G - 1; g >= 0; --g) group(g, 0);
     }
     const long slot = ((long)pbk * NA + grp) * PBS_PT + pt;
     if (CL) P.dep_c[slot] = dac * (ph0 + ph1 - injc) * P.scale;
@@ -620,14 +707,51 @@ static void launch_epass8_t(const EParams<float> &P, int mode, unsigned nb, hipS
         hipLaunchKernelGGL((epass8_kernel<MODE_CLOSE, FEAT, LO, BANDS>), dim3(nb), dim3(256), 0, st, P);
 }
 
+// Ring of the 4-line pass and the grids that take it.  Up to EP8_RING_WAVES waves (two rounds of the plain
+// kernel's 4 waves per SIMD) the chip is short of loads in flight and the ring wins: 279 -> 146 us per launch at
+// 32 x 32 cells, 15 x 15 angles, 131 groups (928 waves); 446 -> 353 us at 45 x 70, 19 x 19, 75 groups (4554);
+// 403 -> 354 us at 40 x 40, 31 x 31, 64 groups (6050).  At 64 x 64 cells and 31 x 31 angles (15488 waves) the two
+// take the same time.  A ring of 3 is slower than 2 everywhere (fewer waves).
+constexpr int EP8_RING = 2;
+constexpr long EP8_RING_WAVES = 8192;
+template <int MODE, bool FEAT, bool BANDS, bool HASQ>
+__global__ __launch_bounds__(256) void epass8_ring_kernel(EParams<float> P)
+{
+    epass8_body<MODE, FEAT, false, BANDS, EP8_RING, HASQ>(P, (long)blockIdx.x * 256 + threadIdx.x);
+}
+
+template <bool FEAT, bool BANDS, bool HASQ>
+static void launch_epass8_ring_t(const EParams<float> &P, int mode, unsigned nb, hipStream_t st)
+{
+    if (mode == MODE_PAIR)
+        hipLaunchKernelGGL((epass8_ring_kernel<MODE_PAIR, FEAT, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
+    else if (mode == MODE_OPEN)
+        hipLaunchKernelGGL((epass8_ring_kernel<MODE_OPEN, FEAT, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
+    else
+        hipLaunchKernelGGL((epass8_ring_kernel<MODE_CLOSE, FEAT, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
+}
+
 hipError_t launch_epass8(const EParams<float> &P, int mode, hipStream_t st)
 {
     const long nthreads = (P.NLINE / P.NAPT) * P.NOCT * (8 / PBS_EPASS_LPT) * PBS_PT;
     const unsigned nb = (unsigned)((nthreads + 255) / 256);
     if (P.NB > 4) return hipErrorInvalidValue;
+    if (P.NB > 1 && P.inj_c != nullptr) return hipErrorInvalidValue;   // banded nuclear data: no surrogate records
+    if (nthreads / 64 <= EP8_RING_WAVES && P.Wl == nullptr && (P.Q == nullptr || P.Qb != nullptr)) {
+        const bool q = P.Q != nullptr;
+        if (P.NB > 1) {
+            if (q) launch_epass8_ring_t<false, true, true>(P, mode, nb, st);
+            else launch_epass8_ring_t<false, true, false>(P, mode, nb, st);
+        } else if (P.inj_c != nullptr) {
+            if (q) return hipErrorInvalidValue;   // the records are the primaries', which have no source
+            launch_epass8_ring_t<true, false, false>(P, mode, nb, st);
+        } else {
+            if (q) launch_epass8_ring_t<false, false, true>(P, mode, nb, st);
+            else launch_epass8_ring_t<false, false, false>(P, mode, nb, st);
+        }
+        return hipGetLastError();
+    }
     if (P.NB > 1) {
-        // banded nuclear data: no surrogate records
-        if (P.inj_c != nullptr) return hipErrorInvalidValue;
         if (P.Wl != nullptr)
             launch_epass8_t<false, true, true>(P, mode, nb, st);
         else
@@ -2712,7 +2836,7 @@ __device__ __forceinline__ int beam_mode(int s, int nz)
     return MODE_PAIR;
 }
 
-template <bool LO>
+template <bool LO, int RING, bool HASQ>
 __global__ __launch_bounds__(256) void epass_batched_kernel(
     const BeamDev *__restrict__ beams, BatchShape Sh, int k, int s)
 {
@@ -2750,11 +2874,11 @@ __global__ __launch_bounds__(256) void epass_batched_kernel(
     P.NAPT = (long)Sh.NA * PBS_PT;
     const long gid = (long)blockIdx.x * 256 + threadIdx.x;
     if (mode == MODE_PAIR)
-        epass8_body<MODE_PAIR, false, LO>(P, gid);
+        epass8_body<MODE_PAIR, false, LO, false, RING, HASQ>(P, gid);
     else if (mode == MODE_OPEN)
-        epass8_body<MODE_OPEN, false, LO>(P, gid);
+        epass8_body<MODE_OPEN, false, LO, false, RING, HASQ>(P, gid);
     else
-        epass8_body<MODE_CLOSE, false, LO>(P, gid);
+        epass8_body<MODE_CLOSE, false, LO, false, RING, HASQ>(P, gid);
 }
 
 // BN = 128 / 256: LDS-staged kernel with BN-column blocks; BN = 0: global-B kernel (256 columns)
@@ -3023,10 +3147,15 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
             sd->pend[k] = 0;
         }
         const unsigned nbe = (unsigned)(((long)Sh.NPB * Sh.NOCT * (8 / PBS_EPASS_LPT) * PBS_PT + 255) / 256);
+        const bool ring = 4L * nbe * nbeam <= EP8_RING_WAVES && Sh.nprod == 1;
         if (Sh.nprod == 3)
-            hipLaunchKernelGGL(epass_batched_kernel<true>, dim3(nbe, nbeam), dim3(256), 0, st, beams, Sh, k, s);
+            hipLaunchKernelGGL((epass_batched_kernel<true, 0, false>), dim3(nbe, nbeam), dim3(256), 0, st, beams, Sh, k, s);
+        else if (!ring)
+            hipLaunchKernelGGL((epass_batched_kernel<false, 0, false>), dim3(nbe, nbeam), dim3(256), 0, st, beams, Sh, k, s);
+        else if (k > 0)
+            hipLaunchKernelGGL((epass_batched_kernel<false, EP8_RING, true>), dim3(nbe, nbeam), dim3(256), 0, st, beams, Sh, k, s);
         else
-            hipLaunchKernelGGL(epass_batched_kernel<false>, dim3(nbe, nbeam), dim3(256), 0, st, beams, Sh, k, s);
+            hipLaunchKernelGGL((epass_batched_kernel<false, EP8_RING, false>), dim3(nbe, nbeam), dim3(256), 0, st, beams, Sh, k, s);
         if (sd && march) {
             // generation k's T A T beside the source product and the later generations' energy passes
             hipError_t e = hipEventRecord(sd->ev_e[k], st);

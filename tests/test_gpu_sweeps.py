@@ -1,0 +1,95 @@
+"""Sweep kernels at the sizes where a variant's edges lie, through the C ABI against the FP64 oracle.
+
+Bounds: FP64 sub-steps 1e-12, FP32 ones 1e-5 of the largest value of the generation (the bounds of the other
+sub-step tests: a few hundred rounding errors of 2^-53 / 2^-24 along a line)."""
+import numpy as np
+import pytest
+
+from paper_2504_00340_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-12, "fp32": 1e-5}
+
+
+@pytest.fixture(scope="module")
+def O():
+    from oracle import oracle
+
+    return oracle
+
+
+def _setup(O, prec, shape, phys=None, src=None, seed=7):
+    from paper_2504_00340_amd import pbsplit as P
+
+    c = I.small(nz=2, seed=seed, **shape)
+    if phys:
+        c["phys"] = phys
+    s = P.Solver(c["grid"], c["phys"], precision=prec)
+    if src is not None and (shape["nth"] - 1) ** 2 >= 128 and prec == "fp32":
+        s.set_source_precision(src)
+    s.set_phantom(c["rho"])
+    s.set_beam(c["beam"])
+    st = I.random_state(s.state_shape, seed)
+    st[:, :, 1] *= 0.3
+    s.set_state(st)
+    return s, O.Oracle(c["grid"], c["phys"]), c, st
+
+
+def _check(got, ref, prec, what):
+    for k in range(ref.shape[0]):
+        e = np.abs(got[k] - ref[k])
+        print(what, prec, "generation", k, "max error", e.max() / np.abs(ref[k]).max(), "at",
+              np.unravel_index(e.argmax(), e.shape), flush=True)
+        assert e.max() <= TOL[prec] * np.abs(ref[k]).max()
+
+
+# group counts around the ring of groups in flight (shorter, equal, one more, a remainder), angular counts whose
+# last line group is full (nth 10: 81 = 8 * 10 + 1; nth 16: 225 = 8 * 28 + 1; nth 18 is not supported)
+@pytest.mark.parametrize("ng", [2, 3, 4, 5, 7])
+@pytest.mark.parametrize("nth,prec", [(6, "fp32"), (10, "fp64"), (16, "fp64"), (16, "fp32"), (20, "fp32")])
+def test_energy_step_around_the_group_ring(O, nth, prec, ng):
+    print("case energy ring", nth, prec, ng, flush=True)
+    # generation 1's one-product BF16 source has its own bound (checked elsewhere): three products here take the
+    # pass without the ring for it, so check generation 0 in the default mode and all in the exact one
+    s, o, c, st = _setup(O, prec, dict(nx=5, ny=7, nth=nth, ng=ng, ngen=2))
+    ref = st.copy()
+    o.energy_all(ref, np.ascontiguousarray(c["rho"][1].reshape(-1)), 0.02)
+    s.apply(1, 1, 0.02)
+    got = s.state()
+    s.close()
+    if prec == "fp32" and nth >= 16:
+        _check(got[:1], ref[:1], prec, "ring")
+        e = np.abs(got[1] - ref[1]).max() / np.abs(ref[1]).max()
+        print("generation 1, BF16 source:", e, flush=True)
+        assert e <= 1e-2
+    else:
+        _check(got, ref, prec, "ring")
+
+
+def test_batched_ring_is_the_single_beam_pass():
+    """Few beams take the ring in both paths; the plain pass of a wide batch must give the same bits."""
+    from paper_2504_00340_amd.pbsplit import Batch, Solver
+
+    def beams(n):
+        out = []
+        for i in range(n):
+            c = I.small(nx=16, ny=16, nth=16, ng=9 + i % 3, nz=3, ngen=2, e0=32.0, e_hi=40.0, depth=0.6, seed=40 + i)
+            out.append(dict(grid=c["grid"], beam=c["beam"], rho=c["rho"]))
+        return out
+
+    few, many = beams(2), beams(40)   # 232 waves per beam: 464 and 9280, either side of the rule
+    doses = []
+    for bs in (few, many):
+        b = Batch(bs, dict(I.PHYS))
+        b.run()
+        doses.append([b.dose(i) for i in range(2)])
+        b.close()
+    for i in range(2):
+        s = Solver(few[i]["grid"], dict(I.PHYS), "fp32")
+        s.set_phantom(few[i]["rho"])
+        s.set_beam(few[i]["beam"])
+        s.run()
+        d = s.dose()
+        s.close()
+        assert np.array_equal(d, doses[0][i]) and np.array_equal(d, doses[1][i])
