@@ -14,6 +14,8 @@
 //   qgemm   angular part of the catastrophic source: Q = P2^T W for every (state, group,
 //           lateral tile).
 //   dose    deterministic per-voxel reduction of the per-line deposits.
+#include <type_traits>
+
 #include "pbs_common.h"
 
 namespace pbs {
@@ -943,78 +945,6 @@ __device__ __forceinline__ void scan_join64(float &y, float m32) { PBS_FMAC_DPP(
 // two wait states after the last scan step, for any DPP read of y that the compiler places next
 __device__ __forceinline__ void scan_done() { asm volatile("s_nop 1"); }
 
-__device__ __forceinline__ void tpass_dpp_body(const TParams<float> &P, long plane)
-{
-    if (plane >= P.nplanes) return;   // uniform per wave
-    const int lane = threadIdx.x & 63;
-    const int a = (int)(plane % P.NA);
-    const long slab = plane / P.NA;
-    const float cx = P.theta[a / P.m], cy = P.theta[a % P.m];
-    const bool mx = cx < 0.f, my = cy < 0.f;
-    const float ax = fabsf(cx) * P.h_half_over_dx, ay = fabsf(cy) * P.h_half_over_dy;
-    const float idiag = 1.f / (1.f + ax + ay);
-    const float cq = ay * idiag;
-    float *base = P.psi + slab * P.NLINE + (long)a * PBS_PT;
-    const long NAPT = (long)P.NA * PBS_PT;
-    const int nx = P.nx, ny = P.ny;
-    const bool valid = lane < ny;
-    const int qc = my ? ny - 1 - lane : lane;
-    // scan multipliers: c^1, c^2, c^4, c^8 within rows of 16 lanes; c^((lane&15)+1), c^((lane&31)+1)
-    const float c1 = cq, c2 = c1 * c1, c4 = c2 * c2, c8 = c4 * c4;
-    float m16 = 1.f, m32 = 1.f;
-    {
-        const int e16 = (lane & 15) + 1, e32 = (lane & 31) + 1;
-        float pw = cq;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            if ((e16 >> i) & 1) m16 *= pw;
-            if ((e32 >> i) & 1) m32 *= pw;
-            pw *= pw;
-        }
-    }
-    auto addr = [&](int r) -> float * {
-        const int p = mx ? nx - 1 - r : r;
-        const long pq = (long)p * ny + qc;
-        return base + (pq / PBS_PT) * NAPT + (pq % PBS_PT);
-    };
-    float rb[16];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) rb[i] = (valid && i < nx) ? *addr(i) : 0.f;
-    float pm1 = 0.f, dxm = 0.f, ym1 = 0.f;
-    for (int r0 = 0; r0 < nx; r0 += 8) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) rb[8 + i] = (valid && r0 + 8 + i < nx) ? *addr(r0 + 8 + i) : 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (r0 + i >= nx) break;
-            const float p0 = rb[i], p1 = rb[i + 1];
-            const float left = dpp_f<0x138, 0xF>(p0);
-            const float right = dpp_f<0x130, 0xF>(p0);
-            const float dyp = superbee_slope(p0 - left, right - p0);
-            const float dym = dpp_f<0x138, 0xF>(dyp);
-            const float dxp = superbee_slope(p0 - pm1, p1 - p0);
-            const float R = p0 - ax * ((p0 - pm1) + (dxp - dxm)) - ay * ((p0 - left) + (dyp - dym));
-            float y = (R + ax * ym1) * idiag;
-            // y_q = b_q + c y_{q-1} along the row: Kogge-Stone within rows of 16, then row broadcasts
-            scan_rows16(y, c1, c2, c4, c8);
-            scan_join32(y, m16);
-            scan_join64(y, m32);
-            scan_done();
-            if (valid) *addr(r0 + i) = y;
-            pm1 = p0;
-            dxm = dxp;
-            ym1 = y;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) rb[i] = rb[8 + i];
-    }
-}
-
-__global__ __launch_bounds__(256) void tpass_dpp_kernel(TParams<float> P)
-{
-    tpass_dpp_body(P, (long)blockIdx.x * 4 + (threadIdx.x >> 6));
-}
-
 constexpr int TPASS_PF = 8;   // rows of the row-affine sweep loaded ahead (nx must be a multiple)
 
 // Same sweep when ny is 32 or 64 and nx a multiple of TPASS_PF: a lane's address is affine in the row
@@ -1515,6 +1445,409 @@ __global__ __launch_bounds__(256) void tpass_wide2_kernel(TParams<float> P)
     tpass_wide2_body(P, __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6))));
 }
 
+// --- The same sweep for any ny <= 128 and any nx, FP32 and FP64 (every grid that no aligned variant above
+// takes).  What bounds the general case is instructions and idle lanes, not memory: the sweep it replaces spent
+// one wave per plane whatever its width, moved neighbours and the row scan through LDS shuffles and waited for
+// each row's loads.  Here the width picks how planes share a wave --
+//   ny <= 16: four planes, one per 16-lane row;  <= 32: two;  <= 64: one;
+//   ny <= 96: two planes in three operations (tpass_wide2_body's arrangement);  <= 128: one in two
+// -- neighbours and scan move by DPP, and TPASS_PK_PF rows are loaded ahead.  A row need not start a lateral
+// tile, so a lane's address is not affine in the row: its cell pq = p ny + q sits at 4|8 x (pq + (pq / 32) 32
+// (NA - 1)) bytes from the plane's first cell, three operations in a buffer resource based at the wave's first
+// slab.  Lanes without a cell carry offset 2^31, past the resource: their loads read the ghost value 0 and their
+// stores are dropped.
+// Measured, us per step half of two generations, before -> after: 4 x 4 cells, 11 x 11 angles, 60 groups 21 -> 7;
+// 24 x 24, 15 x 15, 110 groups 237 -> 88; 50 x 50, 15 x 15, 64 groups 309 -> 218; 45 x 70, 19 x 19, 75 groups (three
+// generations) 1867 -> 860; FP64 20 x 24, 15 x 15, 60 groups 224 -> 73 (5.7 TB/s) and 64 x 64, 15 x 15, 64 groups
+// 860 -> 685.  Eight rows ahead instead of four: 5 % slower at 4 x 4 and 50 x 50, the same elsewhere.
+constexpr int TPASS_PK_PF = 4;
+
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_zt(T x)
+{
+    if constexpr (sizeof(T) == 4) {
+        return dpp_z<CTRL>(x);
+    } else {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+        const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xF, 0xF, true);
+        const unsigned hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, true);
+        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+    }
+}
+template <typename T>
+__device__ __forceinline__ T lane_of(T v, int l)
+{
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+    } else {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, l);
+        const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
+        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+    }
+}
+// y_q = b_q + c y_{q-1} over W lanes (16, 32 or 64): the multipliers of the 16-lane rows, then of the joins, which
+// must be 0 in the lanes a join does not change (m16: rows 0 and 2, m32: lanes 0-31)
+template <int W, typename T>
+__device__ __forceinline__ void scan_lanes(T &y, T c1, T c2, T c4, T c8, T m16, T m32)
+{
+    if constexpr (sizeof(T) == 4) {
+        scan_rows16(y, c1, c2, c4, c8);
+        if constexpr (W >= 32) scan_join32(y, m16);
+        if constexpr (W >= 64) scan_join64(y, m32);
+        scan_done();
+    } else {
+        y = fma(c1, dpp_zt<0x111>(y), y);
+        y = fma(c2, dpp_zt<0x112>(y), y);
+        y = fma(c4, dpp_zt<0x114>(y), y);
+        y = fma(c8, dpp_zt<0x118>(y), y);
+        if constexpr (W >= 32) y = fma(m16, dpp_zt<0x142>(y), y);
+        if constexpr (W >= 64) y = fma(m32, dpp_zt<0x143>(y), y);
+    }
+}
+// c^e for 1 <= e <= 64
+template <typename T>
+__device__ __forceinline__ T pow_lane(T c, int e)
+{
+    T m = T(1), pw = c;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) {
+        if ((e >> i) & 1) m *= pw;
+        pw *= pw;
+    }
+    return m;
+}
+template <typename T, int AUX>
+__device__ __forceinline__ T buf_ld(__amdgpu_buffer_rsrc_t rs, unsigned o)
+{
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, AUX));
+    } else {
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(double, (u32x2)__builtin_amdgcn_raw_buffer_load_b64(rs, o, 0, AUX));
+    }
+}
+template <int AUX, typename T>
+__device__ __forceinline__ void buf_st(T v, __amdgpu_buffer_rsrc_t rs, unsigned o)
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    if constexpr (sizeof(T) == 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, o, 0, AUX);
+    else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, o, 0, AUX);
+}
+
+// What the packed sweeps need: 32-bit plane numbers, two slabs inside a 31-bit buffer resource.
+template <typename T>
+static inline bool tpass_packed_fits(const TParams<T> &P)
+{
+    return P.ny <= 128 && P.nplanes < (1L << 31) - 256 && 2 * P.NLINE * (long)sizeof(T) < 0x7fffffffL;
+}
+
+// One plane per W lanes (W = 16, 32, 64; ny <= W); wave number from the caller, the same in all lanes.
+template <typename T, int W, int AUX>
+__device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wave)
+{
+    constexpr unsigned NPW = 64 / W, TS = sizeof(T), SH = TS == 4 ? 2 : 3;
+    const unsigned pl0 = wave * NPW, nplanes = (unsigned)P.nplanes, NA = P.NA, m = P.m;
+    if (pl0 >= nplanes) return;   // uniform per wave
+    const int lane = threadIdx.x & 63, q = lane % W, sub = lane / W;
+    const int nx = P.nx, ny = P.ny;
+    const unsigned slab0 = pl0 / NA;
+    unsigned a = pl0 - slab0 * NA + sub;
+    const bool next = a >= NA;
+    if (next) a -= NA;
+    const unsigned ai = a / m, aj = a - ai * m;
+    const bool live = pl0 + sub < nplanes && q < ny;
+    const T cx = P.theta[ai], cy = P.theta[aj];
+    const bool mx = cx < T(0), my = cy < T(0);   // sweep frames mirrored so the velocity is >= 0
+    const T ax = fabs(cx) * P.h_half_over_dx, ay = fabs(cy) * P.h_half_over_dy;
+    const T idiag = T(1) / (T(1) + ax + ay);
+    const T c1 = ay * idiag, c2 = c1 * c1, c4 = c2 * c2, c8 = c4 * c4;
+    T m16 = T(0), m32 = T(0);
+    if constexpr (W >= 32)
+        if ((lane >> 4) & 1) m16 = pow_lane(c1, (lane & 15) + 1);
+    if constexpr (W >= 64)
+        if (lane >= 32) m32 = pow_lane(c1, (lane & 31) + 1);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(P.psi + slab0 * P.NLINE), (short)0, (int)(2 * P.NLINE * TS), 0x00020000);
+    const unsigned K = PBS_PT * TS * (NA - 1);
+    const unsigned base = live ? a * (PBS_PT * TS) + (next ? (unsigned)(P.NLINE * TS) : 0u) : 0x80000000u;
+    const int step = live ? (mx ? -ny : ny) : 0;
+    int pld = live ? (mx ? nx - 1 : 0) * ny + (my ? ny - 1 - q : q) : 0, pst = pld;   // cell loaded / stored next
+    auto addr = [&](int pq) { return base + ((unsigned)pq << SH) + ((unsigned)pq >> 5) * K; };
+    // neighbour moves inside the plane's W lanes: 16-lane rows shift by themselves; two planes need the lanes at
+    // the seam masked (opaque factors: a select would run the move under a partial exec mask)
+    T keep_l = T(1), keep_r = T(1);
+    if constexpr (W == 32) {
+        keep_l = q == 0 ? T(0) : T(1);
+        keep_r = q == 31 ? T(0) : T(1);
+        asm volatile("" : "+v"(keep_l), "+v"(keep_r));
+    }
+    auto from_left = [&](T v) {
+        if constexpr (W == 16) return dpp_zt<0x111>(v);
+        else if constexpr (W == 32) return keep_l * dpp_zt<0x138>(v);
+        else return dpp_zt<0x138>(v);
+    };
+    auto from_right = [&](T v) {
+        if constexpr (W == 16) return dpp_zt<0x101>(v);
+        else if constexpr (W == 32) return keep_r * dpp_zt<0x130>(v);
+        else return dpp_zt<0x130>(v);
+    };
+    constexpr int PF = TPASS_PK_PF;
+    T rb[2 * PF];
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+        rb[i] = T(0);
+        if (i < nx) {
+            rb[i] = buf_ld<T, AUX>(rs, addr(pld));
+            pld += step;
+        }
+    }
+    T dxb = rb[0], dxm = T(0), ym1 = T(0);   // p0 - p_{-1} with the ghost row upstream
+    auto row = [&](T p0, T p1) {
+        const T dyb = p0 - from_left(p0), dyf = from_right(p0) - p0;
+        const T dyp = superbee_slope(dyb, dyf);
+        const T dym = from_left(dyp);
+        const T dxf = p1 - p0;
+        const T dxp = superbee_slope(dxb, dxf);
+        const T R = p0 - ax * (dxb + (dxp - dxm)) - ay * (dyb + (dyp - dym));
+        T y = (R + ax * ym1) * idiag;
+        scan_lanes<W>(y, c1, c2, c4, c8, m16, m32);
+        buf_st<AUX>(y, rs, addr(pst));
+        pst += step;
+        dxb = dxf;
+        dxm = dxp;
+        ym1 = y;
+    };
+    int r0 = 0;
+    for (; r0 + 2 * PF <= nx; r0 += PF) {
+#pragma unroll
+        for (int i = 0; i < PF; ++i) {
+            rb[PF + i] = buf_ld<T, AUX>(rs, addr(pld));
+            pld += step;
+        }
+#pragma unroll
+        for (int i = 0; i < PF; ++i) row(rb[i], rb[i + 1]);
+#pragma unroll
+        for (int i = 0; i < PF; ++i) rb[i] = rb[PF + i];
+    }
+    // the last rows: fewer than PF left to load, then the ghost row
+    {
+#pragma unroll
+        for (int i = 0; i < PF; ++i) {
+            rb[PF + i] = T(0);
+            if (r0 + PF + i < nx) {
+                rb[PF + i] = buf_ld<T, AUX>(rs, addr(pld));
+                pld += step;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * PF; ++i)
+            if (r0 + i < nx) row(rb[i], i + 1 < 2 * PF ? rb[i + 1 < 2 * PF ? i + 1 : 0] : T(0));
+    }
+}
+
+// 64 < ny <= 96 (TWO: two planes in three operations, as tpass_wide2_body) or ny <= 128 (one plane in two).
+template <typename T, bool TWO, int AUX>
+__device__ __forceinline__ void tpass_packw_body(const TParams<T> &P, unsigned wave)
+{
+    constexpr unsigned TS = sizeof(T), SH = TS == 4 ? 2 : 3;
+    constexpr int NO = TWO ? 3 : 2, NPL = TWO ? 2 : 1;
+    const unsigned pl0 = wave * NPL, nplanes = (unsigned)P.nplanes, NA = P.NA, m = P.m;
+    if (pl0 >= nplanes) return;   // uniform per wave
+    const int lane = threadIdx.x & 63, ql = TWO ? lane & 31 : lane;
+    const bool hi = TWO && lane >= 32;
+    const int nx = P.nx, ny = P.ny;
+    const unsigned slab0 = pl0 / NA, a0 = pl0 - slab0 * NA;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(P.psi + slab0 * P.NLINE), (short)0, (int)(2 * P.NLINE * TS), 0x00020000);
+    const unsigned K = PBS_PT * TS * (NA - 1);
+    // per plane (uniform): angle, mirroring, slab
+    T axp[NPL], ayp[NPL], idp[NPL];
+    bool mxp[NPL], myp[NPL];
+    unsigned bsp[NPL];
+#pragma unroll
+    for (int k = 0; k < NPL; ++k) {
+        unsigned a = a0 + k;
+        const bool next = a >= NA;
+        if (next) a -= NA;
+        const unsigned ai = a / m;
+        const T cx = P.theta[ai], cy = P.theta[a - ai * m];
+        mxp[k] = cx < T(0);
+        myp[k] = cy < T(0);
+        axp[k] = fabs(cx) * P.h_half_over_dx;
+        ayp[k] = fabs(cy) * P.h_half_over_dy;
+        idp[k] = T(1) / (T(1) + axp[k] + ayp[k]);
+        bsp[k] = pl0 + k < nplanes ? a * (PBS_PT * TS) + (next ? (unsigned)(P.NLINE * TS) : 0u) : 0x80000000u;
+    }
+    // per operation and lane: column, coefficients, cell walked
+    T ax[NO], ay[NO], idg[NO], c1[NO], c2[NO], c4[NO], c8[NO], m16[NO], m32[NO];
+    unsigned base[NO];
+    int step[NO], pld[NO], pst[NO];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+        const bool b = TWO && (o == 1 || (o == 2 && hi));   // plane B
+        const int q = TWO ? (o == 2 ? 64 + ql : lane) : o * 64 + lane;
+        const bool mx = b ? mxp[NPL - 1] : mxp[0], my = b ? myp[NPL - 1] : myp[0];
+        ax[o] = b ? axp[NPL - 1] : axp[0];
+        ay[o] = b ? ayp[NPL - 1] : ayp[0];
+        idg[o] = b ? idp[NPL - 1] : idp[0];
+        c1[o] = ay[o] * idg[o];
+        c2[o] = c1[o] * c1[o];
+        c4[o] = c2[o] * c2[o];
+        c8[o] = c4[o] * c4[o];
+        m16[o] = (lane >> 4) & 1 ? pow_lane(c1[o], (lane & 15) + 1) : T(0);
+        m32[o] = lane >= 32 ? pow_lane(c1[o], (lane & 31) + 1) : T(0);
+        const bool ok = q < ny;
+        base[o] = ok ? (b ? bsp[NPL - 1] : bsp[0]) : 0x80000000u;
+        step[o] = ok ? (mx ? -ny : ny) : 0;
+        pld[o] = ok ? (mx ? nx - 1 : 0) * ny + (my ? ny - 1 - q : q) : 0;
+        pst[o] = pld[o];
+    }
+    // carry of a plane's first operation into the columns from 64 on: c^(column - 63), by plane
+    const T mcA = hi ? T(0) : pow_lane(c1[0], ql + 1);
+    const T mcB = TWO && hi ? pow_lane(c1[NO - 1], ql + 1) : T(0);
+    T e63 = lane == 63 ? T(1) : T(0), e0 = lane == 0 ? T(1) : T(0), e32 = lane == 32 ? T(1) : T(0);
+    T keep_l = TWO && ql == 0 ? T(0) : T(1), keep_r = TWO && ql == 31 ? T(0) : T(1);
+    asm volatile("" : "+v"(e63), "+v"(e0), "+v"(e32), "+v"(keep_l), "+v"(keep_r));
+    auto addr = [&](int o, int pq) { return base[o] + ((unsigned)pq << SH) + ((unsigned)pq >> 5) * K; };
+    // left neighbour in the last operation: the lane below, but column 63 of its plane in the seam lanes (exact:
+    // every other term is a product with 0)
+    auto left_last = [&](T v, T sa, T sb) {
+        T l = keep_l * dpp_zt<0x138>(v) + e0 * sa;
+        if constexpr (TWO) l += e32 * sb;
+        return l;
+    };
+    constexpr int PF = TS == 8 ? 2 : TPASS_PK_PF;   // rows ahead, within the registers of two waves per SIMD
+    T rb[NO][2 * PF];
+    auto load = [&](int i) {
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+            rb[o][i] = buf_ld<T, AUX>(rs, addr(o, pld[o]));
+            pld[o] += step[o];
+        }
+    };
+    auto ghost = [&](int i) {
+#pragma unroll
+        for (int o = 0; o < NO; ++o) rb[o][i] = T(0);
+    };
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+        if (i < nx) load(i);
+        else ghost(i);
+    }
+    T dxb[NO], dxm[NO], ym1[NO];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+        dxb[o] = rb[o][0];
+        dxm[o] = ym1[o] = T(0);
+    }
+    constexpr int LAST = NO - 1;
+    auto row = [&](int i, bool end) {
+        T p0[NO], ayv[NO], bf[NO], dy[NO], dd[NO], y[NO];
+#pragma unroll
+        for (int o = 0; o < NO; ++o) p0[o] = rb[o][i];
+        const T lA = lane_of(p0[0], 63), lB = TWO ? lane_of(p0[1], 63) : T(0);
+        ayv[0] = p0[0] - dpp_zt<0x138>(p0[0]);
+        bf[0] = dpp_zt<0x130>(p0[0]) - p0[0] + e63 * lane_of(p0[LAST], 0);
+        if constexpr (TWO) {
+            ayv[1] = p0[1] - dpp_zt<0x138>(p0[1]);
+            bf[1] = dpp_zt<0x130>(p0[1]) - p0[1] + e63 * lane_of(p0[LAST], 32);
+        }
+        ayv[LAST] = p0[LAST] - left_last(p0[LAST], lA, lB);
+        bf[LAST] = keep_r * dpp_zt<0x130>(p0[LAST]) - p0[LAST];
+#pragma unroll
+        for (int o = 0; o < NO; ++o) dy[o] = superbee_slope(ayv[o], bf[o]);
+        dd[0] = dy[0] - dpp_zt<0x138>(dy[0]);
+        if constexpr (TWO) dd[1] = dy[1] - dpp_zt<0x138>(dy[1]);
+        dd[LAST] = dy[LAST] - left_last(dy[LAST], lane_of(dy[0], 63), TWO ? lane_of(dy[1], 63) : T(0));
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+            const T dxf = (end ? T(0) : rb[o][i + 1]) - p0[o];
+            const T dxp = superbee_slope(dxb[o], dxf);
+            const T R = p0[o] - ax[o] * (dxb[o] + (dxp - dxm[o])) - ay[o] * (ayv[o] + dd[o]);
+            y[o] = (R + ax[o] * ym1[o]) * idg[o];
+            dxb[o] = dxf;
+            dxm[o] = dxp;
+        }
+        scan_lanes<64>(y[0], c1[0], c2[0], c4[0], c8[0], m16[0], m32[0]);
+        if constexpr (TWO) {
+            scan_lanes<64>(y[1], c1[1], c2[1], c4[1], c8[1], m16[1], m32[1]);
+            scan_lanes<32>(y[2], c1[2], c2[2], c4[2], c8[2], m16[2], m32[2]);
+            y[2] += mcA * lane_of(y[0], 63);
+            y[2] += mcB * lane_of(y[1], 63);
+        } else {
+            scan_lanes<64>(y[1], c1[1], c2[1], c4[1], c8[1], m16[1], m32[1]);
+            y[1] += mcA * lane_of(y[0], 63);
+        }
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+            buf_st<AUX>(y[o], rs, addr(o, pst[o]));
+            pst[o] += step[o];
+            ym1[o] = y[o];
+        }
+    };
+    int r0 = 0;
+    for (; r0 + 2 * PF <= nx; r0 += PF) {
+#pragma unroll
+        for (int i = 0; i < PF; ++i) load(PF + i);
+#pragma unroll
+        for (int i = 0; i < PF; ++i) row(i, false);
+#pragma unroll
+        for (int i = 0; i < PF; ++i)
+#pragma unroll
+            for (int o = 0; o < NO; ++o) rb[o][i] = rb[o][PF + i];
+    }
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+        if (r0 + PF + i < nx) load(PF + i);
+        else ghost(PF + i);
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * PF; ++i)
+        if (r0 + i < nx) row(i, i + 1 == 2 * PF);
+}
+
+// planes that share a wave in the packed sweeps
+static inline int tpass_packed_planes(int ny) { return ny <= 16 ? 4 : ny <= 32 ? 2 : ny <= 64 ? 1 : ny <= 96 ? 2 : 1; }
+
+// V: 16, 32, 64 (lanes per plane), 96 (two planes in three operations), 128 (one plane in two).
+// NT: rows of whole lateral tiles pass the caches by (as the aligned sweeps; FP64, 64 x 64 cells: 685 us against
+// 708); where a row ends inside a tile, its 128-byte line is written by two rows and has to meet in the cache
+// (50 x 50 cells: 218 us against 293, 45 x 70: 860 against 1096).
+template <typename T, int V, bool NT>
+__device__ __forceinline__ void tpass_packed_body(const TParams<T> &P, unsigned wave)
+{
+    wave = __builtin_amdgcn_readfirstlane(wave);
+    if constexpr (V <= 64)
+        tpass_pack_body<T, V, NT ? 2 : 0>(P, wave);
+    else
+        tpass_packw_body<T, V == 96, NT ? 2 : 0>(P, wave);
+}
+
+template <typename T, int V, bool NT>
+__global__ __launch_bounds__(256) void tpass_packed_kernel(TParams<T> P)
+{
+    tpass_packed_body<T, V, NT>(P, blockIdx.x * 4 + (threadIdx.x >> 6));
+}
+
+// One instantiation per width and cache policy: f(V, NT) as compile-time constants.
+template <typename F>
+static void tpass_packed_select(int ny, F &&f)
+{
+    using std::integral_constant;
+    if (ny <= 16) f(integral_constant<int, 16>(), std::false_type());
+    else if (ny < 32) f(integral_constant<int, 32>(), std::false_type());
+    else if (ny == 32) f(integral_constant<int, 32>(), std::true_type());
+    else if (ny < 64) f(integral_constant<int, 64>(), std::false_type());
+    else if (ny == 64) f(integral_constant<int, 64>(), std::true_type());
+    else if (ny < 96) f(integral_constant<int, 96>(), std::false_type());
+    else if (ny == 96) f(integral_constant<int, 96>(), std::true_type());
+    else if (ny < 128) f(integral_constant<int, 128>(), std::false_type());
+    else f(integral_constant<int, 128>(), std::true_type());
+}
+
 template <typename T>
 hipError_t launch_tpass(const TParams<T> &P, hipStream_t st)
 {
@@ -1543,10 +1876,14 @@ hipError_t launch_tpass(const TParams<T> &P, hipStream_t st)
             hipLaunchKernelGGL(tpass_wide_kernel<128>, grid, dim3(256), 0, st, P);
             return hipGetLastError();
         }
-        if (P.ny <= 64) {
-            hipLaunchKernelGGL(tpass_dpp_kernel, grid, dim3(256), 0, st, P);
-            return hipGetLastError();
-        }
+    }
+    if (tpass_packed_fits(P)) {
+        const long waves = (P.nplanes + tpass_packed_planes(P.ny) - 1) / tpass_packed_planes(P.ny);
+        const dim3 grid((unsigned)((waves + 3) / 4));
+        tpass_packed_select(P.ny, [&](auto v, auto nt) {
+            hipLaunchKernelGGL((tpass_packed_kernel<T, decltype(v)::value, decltype(nt)::value>), grid, dim3(256), 0, st, P);
+        });
+        return hipGetLastError();
     }
     const unsigned nb = (unsigned)((P.nplanes + 3) / 4);
     const int nseg = (P.ny + 63) / 64;
@@ -2918,12 +3255,9 @@ __attribute__((amdgpu_waves_per_eu(BN == 0 && NPROD == 1 ? QG_WPE : 1))) void qg
         qgemm_bf16s_body<BN, NPROD>(P, Sh.Ahi, Sh.Alo, Sh.Kpb, nmt, nnt, nlog, per, blockIdx.x);
 }
 
-template <int NSEG, int WPB>
-__global__ __launch_bounds__(64 * WPB) void tpass_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh,
-                                                                 int s, int k)
+// the transport record of one beam of the batch (generation k, or all for k < 0)
+__device__ __forceinline__ TParams<float> batch_tparams(const BeamDev &B, const BatchShape &Sh, int k)
 {
-    const BeamDev &B = beams[blockIdx.y];
-    if (s >= B.nz) return;
     TParams<float> P;
     P.psi = k < 0 ? B.psi : B.psi + (long)k * B.G * 2 * Sh.NLINE;
     P.theta = Sh.theta;
@@ -2935,6 +3269,25 @@ __global__ __launch_bounds__(64 * WPB) void tpass_batched_kernel(const BeamDev *
     P.NA = Sh.NA;
     P.NLINE = Sh.NLINE;
     P.nplanes = (long)(k < 0 ? Sh.ngen : 1) * B.G * 2 * Sh.NA;
+    return P;
+}
+
+template <int V, bool NT>
+__global__ __launch_bounds__(256) void tpass_batched_packed_kernel(const BeamDev *__restrict__ beams, BatchShape Sh,
+                                                                    int s, int k)
+{
+    const BeamDev &B = beams[blockIdx.y];
+    if (s >= B.nz) return;
+    tpass_packed_body<float, V, NT>(batch_tparams(B, Sh, k), blockIdx.x * 4 + (threadIdx.x >> 6));
+}
+
+template <int NSEG, int WPB>
+__global__ __launch_bounds__(64 * WPB) void tpass_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh,
+                                                                 int s, int k)
+{
+    const BeamDev &B = beams[blockIdx.y];
+    if (s >= B.nz) return;
+    const TParams<float> P = batch_tparams(B, Sh, k);
     tpass_body<float, NSEG>(P, (long)blockIdx.x * WPB + (threadIdx.x >> 6));
 }
 
@@ -2944,17 +3297,7 @@ __global__ __launch_bounds__(64 * WPB) void tpass_batched_affine_kernel(const Be
 {
     const BeamDev &B = beams[blockIdx.y];
     if (s >= B.nz) return;
-    TParams<float> P;
-    P.psi = k < 0 ? B.psi : B.psi + (long)k * B.G * 2 * Sh.NLINE;
-    P.theta = Sh.theta;
-    P.h_half_over_dx = B.thx;
-    P.h_half_over_dy = B.thy;
-    P.nx = Sh.nx;
-    P.ny = Sh.ny;
-    P.m = Sh.m;
-    P.NA = Sh.NA;
-    P.NLINE = Sh.NLINE;
-    P.nplanes = (long)(k < 0 ? Sh.ngen : 1) * B.G * 2 * Sh.NA;
+    const TParams<float> P = batch_tparams(B, Sh, k);
     tpass_affine_body<NY>(P, (long)blockIdx.x * WPB + (threadIdx.x >> 6));
 }
 
@@ -2964,17 +3307,7 @@ __global__ __launch_bounds__(64 * WPB) void tpass_batched_wide_kernel(const Beam
 {
     const BeamDev &B = beams[blockIdx.y];
     if (s >= B.nz) return;
-    TParams<float> P;
-    P.psi = k < 0 ? B.psi : B.psi + (long)k * B.G * 2 * Sh.NLINE;
-    P.theta = Sh.theta;
-    P.h_half_over_dx = B.thx;
-    P.h_half_over_dy = B.thy;
-    P.nx = Sh.nx;
-    P.ny = Sh.ny;
-    P.m = Sh.m;
-    P.NA = Sh.NA;
-    P.NLINE = Sh.NLINE;
-    P.nplanes = (long)(k < 0 ? Sh.ngen : 1) * B.G * 2 * Sh.NA;
+    const TParams<float> P = batch_tparams(B, Sh, k);
     tpass_wide_body<NY>(P, (long)blockIdx.x * WPB + (threadIdx.x >> 6));
 }
 
@@ -2984,17 +3317,7 @@ __global__ __launch_bounds__(64 * WPB) void tpass_batched_pair_kernel(const Beam
 {
     const BeamDev &B = beams[blockIdx.y];
     if (s >= B.nz) return;
-    TParams<float> P;
-    P.psi = k < 0 ? B.psi : B.psi + (long)k * B.G * 2 * Sh.NLINE;
-    P.theta = Sh.theta;
-    P.h_half_over_dx = B.thx;
-    P.h_half_over_dy = B.thy;
-    P.nx = Sh.nx;
-    P.ny = Sh.ny;
-    P.m = Sh.m;
-    P.NA = Sh.NA;
-    P.NLINE = Sh.NLINE;
-    P.nplanes = (long)(k < 0 ? Sh.ngen : 1) * B.G * 2 * Sh.NA;
+    const TParams<float> P = batch_tparams(B, Sh, k);
     tpass_pair_body(P, (long)blockIdx.x * WPB + (threadIdx.x >> 6));
 }
 
@@ -3095,6 +3418,19 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
             }
             if (Sh.nx % TPASS_PF == 0 && Sh.ny == 128) {
                 PBS_TWW(128);
+                return;
+            }
+            TParams<float> size;   // the sizes the packed sweep's rule looks at, of the largest beam
+            size.ny = Sh.ny;
+            size.NLINE = Sh.NLINE;
+            size.nplanes = planes;
+            if (tpass_packed_fits(size)) {
+                const int np = tpass_packed_planes(Sh.ny);
+                const dim3 g((unsigned)(((planes + np - 1) / np + 3) / 4), nbeam);
+                tpass_packed_select(Sh.ny, [&](auto v, auto nt) {
+                    hipLaunchKernelGGL((tpass_batched_packed_kernel<decltype(v)::value, decltype(nt)::value>), g,
+                                       dim3(256), 0, q, beams, Sh, s, k);
+                });
                 return;
             }
             switch (nseg) {

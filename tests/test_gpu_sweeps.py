@@ -93,3 +93,20 @@ def test_batched_ring_is_the_single_beam_pass():
         d = s.dose()
         s.close()
         assert np.array_equal(d, doses[0][i]) and np.array_equal(d, doses[1][i])
+
+
+# widths around the lanes a plane takes in the packed transport (16, 32, 64, two planes in three operations, one in
+# two), rows around the rows loaded ahead (4; FP64's wide forms 2), odd plane counts (the last wave's missing planes)
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (3, 4), (4, 15), (5, 16), (7, 17), (8, 31), (9, 32), (12, 33), (2, 63), (10, 64),
+                                   (3, 65), (4, 70), (6, 80), (7, 95), (9, 96), (11, 97), (5, 127), (13, 128), (3, 129)])
+def test_transport_widths(O, nx, ny, prec):
+    print("case transport", nx, ny, prec, flush=True)
+    s, o, c, st = _setup(O, prec, dict(nx=nx, ny=ny, nth=6, ng=3, ngen=1))
+    ref = st.copy()
+    for k in range(ref.shape[0]):
+        o.transport_cn(ref[k], 0.05)
+    s.apply(2, 1, 0.05)
+    got = s.state()
+    s.close()
+    _check(got, ref, prec, "transport")
