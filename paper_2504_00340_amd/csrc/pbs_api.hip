@@ -526,7 +526,6 @@ void layout(pbs_ctx *c)
     c->t_theta = e; e += c->m;
     c->t_S = e; e += (size_t)c->m * c->m;
     c->t_lam = e; e += c->m;
-    c->t_P2T = e; e += (size_t)c->NB * c->NA * c->NA;
     e = (e + 63) / 64 * 64;   // vector loads of the padded tables need 256-byte alignment
     c->t_P2p = e; e += (size_t)c->NB * c->Kp * c->Mp;
     e = (e + 63) / 64 * 64;
@@ -575,7 +574,6 @@ pbs_status upload_tables(pbs_ctx *c)
     put(c->t_theta, c->theta);
     put(c->t_S, c->sinS);
     put(c->t_lam, c->lam);
-    put(c->t_P2T, c->P2T);
     put(c->t_wdecb, c->wdecb);
     if (c->strag) put(c->t_blk, c->blk);
     // zero-padded, source-major copy for the MFMA product: P2p[b][k][a] = P2T[b][a][k]
@@ -774,7 +772,6 @@ pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, in
         }
         if (k + 1 < K1) {
             QParams<T> Q;
-            Q.P2T = c->tabT<T>() + c->t_P2T;
             Q.W = c->W<T>();
             Q.Q = c->Q<T>();
             Q.Qb = source_bf16(c) ? reinterpret_cast<unsigned short *>(c->Q<T>()) : nullptr;
@@ -782,7 +779,7 @@ pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, in
             Q.NPB = c->NPB;
             Q.G = c->G();
             Q.NLINE = c->NLINE;
-            Q.P2p = c->Kp > 0 ? c->tabT<T>() + c->t_P2p : nullptr;
+            Q.P2p = c->tabT<T>() + c->t_P2p;
             Q.Kp = c->Kp;
             Q.Mp = c->Mp;
             Q.NOCT = c->NOCT;
@@ -805,28 +802,24 @@ pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, in
         }
     }
     ProfScope ps(c, PBS_K_DOSE);
-    if (mode & MODE_CLOSE)
-        HIPCHK(c, launch_dose_reduce(c->edep(row_c), c->dep(0, 0), K1, c->NA, nslot, c->NLINE, c->NP, c->stream));
-    if (mode & MODE_OPEN)
-        HIPCHK(c, launch_dose_reduce(c->edep(row_o), c->dep(1, 0), K1, c->NA, nslot, c->NLINE, c->NP, c->stream));
+    DoseJobs J;
+    if (mode & MODE_CLOSE) J.add(c->edep(row_c), c->dep(0, 0), K1);
+    if (mode & MODE_OPEN) J.add(c->edep(row_o), c->dep(1, 0), K1);
     if (c->feat_on) {
         // per-layer surrogate records: injected energy of both halves, moments after the opening half,
         // and the deposit of the primaries alone when further generations are marched
-        const int NA = c->NA, NP = c->NP;
-        const long NL = c->NLINE;
         if (mode & MODE_CLOSE) {
-            HIPCHK(c, launch_dose_reduce(c->frec(0, lay_c), c->fline(0), 1, NA, nslot, NL, NP, c->stream));
-            if (K1 > 1)
-                HIPCHK(c, launch_dose_reduce(c->frec(3, lay_c), c->dep(0, 0), 1, NA, nslot, NL, NP, c->stream));
+            J.add(c->frec(0, lay_c), c->fline(0), 1);
+            if (K1 > 1) J.add(c->frec(3, lay_c), c->dep(0, 0), 1);
         }
         if (mode & MODE_OPEN) {
-            HIPCHK(c, launch_dose_reduce(c->frec(0, lay_o), c->fline(1), 1, NA, nslot, NL, NP, c->stream));
-            HIPCHK(c, launch_dose_reduce(c->frec(1, lay_o), c->fline(2), 1, NA, nslot, NL, NP, c->stream));
-            HIPCHK(c, launch_dose_reduce(c->frec(2, lay_o), c->fline(3), 1, NA, nslot, NL, NP, c->stream));
-            if (K1 > 1)
-                HIPCHK(c, launch_dose_reduce(c->frec(3, lay_o), c->dep(1, 0), 1, NA, nslot, NL, NP, c->stream));
+            J.add(c->frec(0, lay_o), c->fline(1), 1);
+            J.add(c->frec(1, lay_o), c->fline(2), 1);
+            J.add(c->frec(2, lay_o), c->fline(3), 1);
+            if (K1 > 1) J.add(c->frec(3, lay_o), c->dep(1, 0), 1);
         }
     }
+    HIPCHK(c, launch_dose_reduce(J, c->NA, nslot, c->NLINE, c->NP, c->stream));
     return PBS_OK;
 }
 
@@ -1250,7 +1243,10 @@ pbs_status pbs_create(const pbs_grid *grid, const pbs_physics *phys, int precisi
     c->dth = 2.0 * g.th_half / g.nth;
     c->NOCT = (c->NA + 7) / 8;
     c->kact = g.ngen;
-    if (c->NA >= 128) {   // source product on MFMA
+    // padding of the source product's matrix: whole MFMA steps and tiles
+    c->Kp = (c->NA + 3) / 4 * 4;
+    c->Mp = (c->NA + 31) / 32 * 32;
+    if (c->NA >= 128) {
         c->Kp = (c->NA + 15) / 16 * 16;
         c->Mp = (c->NA + 127) / 128 * 128;
         if (precision == PBS_FP32 && !ph.straggling) {

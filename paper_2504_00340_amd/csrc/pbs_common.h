@@ -89,11 +89,10 @@ struct AParams {
 
 template <typename T>
 struct QParams {
-    const T *P2T;           // [NA][NA]: P2T[a][a'] = probability a' -> a
     const T *W;             // [2][G][NLINE]
     T *Q;                   // [2][G][NLINE]
     unsigned short *Qb = nullptr;   // non-null: write the source in BF16 there instead (EParams::Qb layout)
-    const T *P2p;           // [Kp][Mp] zero-padded P2 (k = source node, row = destination), MFMA path
+    const T *P2p;           // [Kp][Mp] zero-padded P2 (k = source node, row = destination)
     int Kp, Mp;
     const unsigned short *Bh, *Bl;   // split-BF16 W (see EParams), split-BF16 path
     int NOCT;
@@ -101,7 +100,7 @@ struct QParams {
     int s0, ns;             // half-step sums s0 .. s0+ns-1
     long NLINE;
     const int *band = nullptr;   // nuclear band of every destination group (null: one band); the transfer
-                                 // matrices of the bands follow each other (P2T, P2p, split tables)
+                                 // matrices of the bands follow each other (P2p, split tables)
 };
 
 // One beam of a batch (device copy of its descriptor).  Beams of one batch share the lateral and
@@ -171,9 +170,15 @@ template <typename T> hipError_t launch_qgemm(const QParams<T> &P, hipStream_t s
 template <typename T> hipError_t launch_fill(T *p, T v, long n, hipStream_t st);
 // y = a y + b x elementwise
 template <typename T> hipError_t launch_combine(T *y, const T *x, T a, T b, long n, hipStream_t st);
-// edep_layer[pq] += sum over generations and the first nslot angular slots of dep
-hipError_t launch_dose_reduce(double *edep_layer, const double *dep, int ngen, int NA, int nslot, long NLINE, int NP,
-                              hipStream_t st);
+// row[j][pq] += sum over ngen[j] generations and the first nslot angular slots of dep[j], j < n, in one launch
+struct DoseJobs {
+    int n = 0;
+    double *row[8];
+    const double *dep[8];
+    int ngen[8];
+    void add(double *r, const double *d, int k) { row[n] = r, dep[n] = d, ngen[n] = k, ++n; }
+};
+hipError_t launch_dose_reduce(const DoseJobs &J, int NA, int nslot, long NLINE, int NP, hipStream_t st);
 hipError_t launch_dose_finalize(double *out, const double *edep, const double *rho, double vol, long n,
                                 hipStream_t st);
 template <typename T>

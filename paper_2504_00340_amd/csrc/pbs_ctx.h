@@ -63,7 +63,7 @@ struct pbs_ctx {
     size_t o_psi = 0, o_W = 0, o_Q = 0, o_dep = 0, o_edep = 0, o_dout = 0, o_rhoT = 0, o_rhoD = 0, o_tabT = 0,
            o_tabD = 0, total = 0;
     // table offsets (elements) inside the T and double table blocks
-    size_t t_Sm, t_Sp, t_kap, t_wc, t_wdec, t_invdE, t_sig, t_theta, t_S, t_lam, t_P2T, t_P2p, t_K32, t_wdecb, t_blk,
+    size_t t_Sm, t_Sp, t_kap, t_wc, t_wdec, t_invdE, t_sig, t_theta, t_S, t_lam, t_P2p, t_K32, t_wdecb, t_blk,
         t_count;
     size_t o_band = 0, o_sfac = 0;   // band indices [G] (int); straggling factors [2][G][8][NPpad] (T)
     int Kp = 0, Mp = 0;           // padded source product (MFMA path, FP32 with NA >= 128)

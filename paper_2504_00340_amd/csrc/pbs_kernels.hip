@@ -2346,54 +2346,7 @@ hipError_t launch_apass(const AParams<T> &P, int nth, long nstack, hipStream_t s
 }
 
 // ------------------------------------------------------------------- source angular product
-// Q[s][g][pb][a][pt] = sum_a' P2T[a][a'] W[s][g][pb][a'][pt]; block = 64 rows x 32 columns.
-template <typename T>
-__global__ __launch_bounds__(256) void qgemm_kernel(QParams<T> P)
-{
-    const long bt = blockIdx.x;   // ((si*G + g)*NPB + pb)
-    const int mt = blockIdx.y;
-    const int pb = (int)(bt % P.NPB);
-    const long sg = bt / P.NPB;
-    const int g = (int)(sg % P.G);
-    const int s = P.s0 + (int)(sg / P.G);
-    const long off = ((long)s * P.G + g) * P.NLINE + (long)pb * P.NA * PBS_PT;
-    const T *B = P.W + off;
-    T *C = P.Q + off;
-    const T *P2T = P.P2T + (P.band ? (long)P.band[g] * P.NA * P.NA : 0L);   // the destination group's band
-    __shared__ T As[64][33];
-    __shared__ T Bs[32][32];
-    const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
-    const int NA = P.NA;
-    T acc[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) acc[r] = T(0);
-    for (int k0 = 0; k0 < NA; k0 += 32) {
-        for (int idx = tid; idx < 64 * 32; idx += 256) {
-            const int row = idx >> 5, kk = idx & 31;
-            const int ga = mt * 64 + row, gk = k0 + kk;
-            As[row][kk] = (ga < NA && gk < NA) ? P2T[(long)ga * NA + gk] : T(0);
-        }
-        for (int idx = tid; idx < 32 * 32; idx += 256) {
-            const int kk = idx >> 5, col = idx & 31;
-            const int gk = k0 + kk;
-            Bs[kk][col] = gk < NA ? B[(long)gk * PBS_PT + col] : T(0);
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int kk = 0; kk < 32; ++kk) {
-            const T bv = Bs[kk][tx];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) acc[r] += As[ty + 8 * r][kk] * bv;
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const int ga = mt * 64 + ty + 8 * r;
-        if (ga < NA) C[(long)ga * PBS_PT + tx] = acc[r];
-    }
-}
-
+// Q[s][g][pb][a][pt] = sum_a' P2T[a][a'] W[s][g][pb][a'][pt].
 // FP32 MFMA version (v_mfma_f32_32x32x2_f32).  Block tile 128 destination nodes x 128 columns
 // (4 lateral tiles of one (half-step, group) panel); 4 waves in 2 x 2, each 64 x 64 = 2 x 2
 // MFMA tiles.  A is the zero-padded P2 [Kp][Mp] (source-major), staged k-major in LDS like B.
@@ -3025,31 +2978,122 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
         }
 }
 
+// Fewer than 128 angular unknowns (up to 12 nodes per axis), FP32 and FP64: v_mfma_f32_16x16x4 / v_mfma_f64_16x16x4.
+// What bounded the vector kernel it replaces: its LDS staging (a barrier pair per 32 source nodes) on small
+// grids, two LDS reads per multiply on large ones.  Here both operands go from global memory straight into MFMA
+// registers: P2 (zero-padded [Kp][Mp], at most 64 | 128 KB, resident in L2) and the scan, whose row of 32 cells
+// a lane reads as one pair, cell 2 c + h being column c of column tile h.  Block = up to 4 waves of 32 destination
+// rows each over NTL lateral tiles of one (half, group); loads run QS_PF 4-node steps ahead.  NTL = 1 where the
+// grid has few tiles (latency), else as many as the registers hold, for each P2 load to feed more products.
+// Measured, us per product, before -> after: 4 x 4 cells, 11 x 11 angles, 60 groups 21 -> 10; 24 x 24, 9 x 9, 60 73 ->
+// 22 (FP64 121 -> 32); 48 x 128, 11 x 11, 60 1104 -> 321; 90 x 96, 7 x 7, 80 in FP64 845 -> 244.
+constexpr int QS_PF = 4;
+__device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ doublex4 mfma4(double a, double b, doublex4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+template <typename T, int NTL>
+__global__ __launch_bounds__(256) void qgemm_small_kernel(QParams<T> P, int nnt)
+{
+    typedef T T2 __attribute__((ext_vector_type(2)));
+    typedef T T4 __attribute__((ext_vector_type(4)));
+    const int nt = (int)(blockIdx.x % nnt);
+    const long sg = blockIdx.x / nnt;
+    const int g = (int)(sg % P.G), s = P.s0 + (int)(sg / P.G);
+    const long off = ((long)s * P.G + g) * P.NLINE, NAPT = (long)P.NA * PBS_PT;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, kq = lane >> 4;
+    const T *A = P.P2p + (P.band ? (long)P.band[g] * P.Kp * P.Mp : 0L) + (long)kq * P.Mp + 32 * w + c;
+    const T *B[NTL];
+#pragma unroll
+    for (int j = 0; j < NTL; ++j) B[j] = P.W + off + (long)min(nt * NTL + j, P.NPB - 1) * NAPT + 2 * c;
+    const int KS = P.Kp / 4;
+    T4 acc[2][NTL][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NTL; ++j) acc[i][j][0] = acc[i][j][1] = T4{0, 0, 0, 0};
+    T ra[QS_PF][2];
+    T2 rb[QS_PF][NTL];
+    // step k of 4 source nodes into ring slot u; a padded node (zero column of P2) reads the last node's scan
+    auto fetch = [&](int k, int u) {
+        const int kc = min(k, KS - 1);
+        const T *a = A + (long)kc * 4 * P.Mp;
+        ra[u][0] = a[0];
+        ra[u][1] = a[16];
+        const long row = (long)min(4 * kc + kq, P.NA - 1) * PBS_PT;
+#pragma unroll
+        for (int j = 0; j < NTL; ++j) rb[u][j] = *reinterpret_cast<const T2 *>(B[j] + row);
+    };
+    auto step = [&](int k, int u) {
+        T a[2] = {ra[u][0], ra[u][1]};
+        T2 b[NTL];
+#pragma unroll
+        for (int j = 0; j < NTL; ++j) b[j] = rb[u][j];
+        fetch(k + QS_PF, u);
+#pragma unroll
+        for (int j = 0; j < NTL; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) acc[i][j][h] = mfma4(a[i], b[j][h], acc[i][j][h]);
+    };
+#pragma unroll
+    for (int u = 0; u < QS_PF; ++u) fetch(u, u);
+    int k0 = 0;
+    for (; k0 + QS_PF <= KS; k0 += QS_PF) {
+#pragma unroll
+        for (int u = 0; u < QS_PF; ++u) step(k0 + u, u);
+    }
+#pragma unroll
+    for (int u = 0; u < QS_PF - 1; ++u)
+        if (k0 + u < KS) step(k0 + u, u);
+#pragma unroll
+    for (int j = 0; j < NTL; ++j) {
+        const int pb = nt * NTL + j;
+        if (pb >= P.NPB) continue;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                // result rows of a lane: FP32 4 (lane / 16) + q, FP64 lane / 16 + 4 q
+                const int row = 32 * w + 16 * i + (sizeof(T) == 4 ? 4 * kq + q : kq + 4 * q);
+                if (row < P.NA)
+                    *reinterpret_cast<T2 *>(P.Q + off + pb * NAPT + (long)row * PBS_PT + 2 * c) =
+                        T2{acc[i][j][0][q], acc[i][j][1][q]};
+            }
+    }
+}
+
+// Up to 8192 (half, group, tile) items a tile per block; more tiles per block above, where it pays: 48 x 60 cells,
+// 11 x 11 angles, 60 groups, FP64 (10800 items) 254 us against 271, 64 x 64, 9 x 9, 100 (25600) 189 against 200; but
+// 32 x 32, 11 x 11, 60 (3840) 58 against 55 and 4 x 4 (120) 15.5 against 9.7.
+constexpr long QS_WIDE_ITEMS = 8192;
+template <typename T>
+static hipError_t launch_qgemm_small(const QParams<T> &P, hipStream_t st)
+{
+    constexpr int WIDE = sizeof(T) == 4 ? 4 : 2;
+    const dim3 block(64 * (P.Mp / 32));
+    const long items = (long)P.ns * P.G * P.NPB;
+    if (items > QS_WIDE_ITEMS) {
+        const int nnt = (P.NPB + WIDE - 1) / WIDE;
+        hipLaunchKernelGGL((qgemm_small_kernel<T, WIDE>), dim3((unsigned)((long)P.ns * P.G * nnt)), block, 0, st, P, nnt);
+    } else {
+        hipLaunchKernelGGL((qgemm_small_kernel<T, 1>), dim3((unsigned)items), block, 0, st, P, P.NPB);
+    }
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_qgemm(const QParams<T> &P, hipStream_t st)
 {
-    if constexpr (sizeof(T) == 8) {
-        if (P.P2p != nullptr) {
-            const int nmt = P.Mp / 128, nnt = (P.NPB + 3) / 4;
-            const long nlog = (long)P.ns * P.G * nnt * nmt;
-            const long per = (nlog + 7) / 8;
-            hipLaunchKernelGGL(qgemm_mfma_f64_kernel, dim3((unsigned)(per * 8)), dim3(256), 0, st, P, nmt, nnt, nlog,
-                               per);
-            return hipGetLastError();
-        }
-    }
-    if constexpr (sizeof(T) == 4) {
-        if (P.P2p != nullptr) {
-            const int nmt = P.Mp / 128, nnt = (P.NPB + 3) / 4;
-            const long nlog = (long)P.ns * P.G * nnt * nmt;
-            const long per = (nlog + 7) / 8;
-            hipLaunchKernelGGL(qgemm_mfma_f32_kernel, dim3((unsigned)(per * 8)), dim3(256), 0, st, P, nmt, nnt, nlog,
-                               per);
-            return hipGetLastError();
-        }
-    }
-    dim3 grid((unsigned)((long)P.ns * P.G * P.NPB), (unsigned)((P.NA + 63) / 64));
-    hipLaunchKernelGGL((qgemm_kernel<T>), grid, dim3(256), 0, st, P);
+    if (P.P2p == nullptr) return hipErrorInvalidValue;
+    if (P.NA < 128) return launch_qgemm_small(P, st);
+    const int nmt = P.Mp / 128, nnt = (P.NPB + 3) / 4;
+    const long nlog = (long)P.ns * P.G * nnt * nmt;
+    const long per = (nlog + 7) / 8;
+    if constexpr (sizeof(T) == 8)
+        hipLaunchKernelGGL(qgemm_mfma_f64_kernel, dim3((unsigned)(per * 8)), dim3(256), 0, st, P, nmt, nnt, nlog, per);
+    else
+        hipLaunchKernelGGL(qgemm_mfma_f32_kernel, dim3((unsigned)(per * 8)), dim3(256), 0, st, P, nmt, nnt, nlog, per);
     return hipGetLastError();
 }
 
@@ -3088,38 +3132,55 @@ hipError_t launch_combine(T *y, const T *x, T a, T b, long n, hipStream_t st)
 template hipError_t launch_combine<float>(float *, const float *, float, float, long, hipStream_t);
 template hipError_t launch_combine<double>(double *, const double *, double, double, long, hipStream_t);
 
-// edep[pq] += sum over generations and angles of dep[k][line(pq, a)], fixed order: one wave per lateral
-// tile; lane (pt, h) sums the slots a = h, h + 2, ... of every generation in turn, then the two halves of
-// a cell are added (the same sum whichever lane adds).  A one-wave block fits beside whatever else is
-// resident on a CU, which matters where the reduction runs next to the transport and angular passes of
-// a batch.
+// edep[pq] += sum over generations and angles of dep[k][line(pq, a)], fixed order: one block of four waves per
+// lateral tile; lane (pt, h) of wave w sums the slots a = 2 w + h, + 8, ... of every generation in turn, then the
+// eight partials of a cell are added in the order of (w, h).  What bounds it is the latency of its loads (a
+// few hundred KB): four waves and eight loads in flight per lane took a launch at 4 x 4 cells, 11 x 11
+// angles, two generations from 17 to 9 us, one at 45 x 70, 19 x 19, three from 35 to 13.  Sixteen-wave blocks lose that again where the
+// reduction runs beside the transport and angular passes (they wait for a whole CU to drain).
 __device__ __forceinline__ void dose_reduce_body(double *edep, const double *dep, int ngen, int NA, int nslot,
                                                  long NLINE, int NP, int pb)
 {
-    const int lane = threadIdx.x & 63, pt = lane & 31, h = lane >> 5;
+    __shared__ double part[4][32];
+    const int tid = threadIdx.x, pt = tid & 31, h = (tid >> 5) & 1, w = tid >> 6;
     const long base = (long)pb * NA * PBS_PT + pt;
     double s = 0.0;
     for (int k = 0; k < ngen; ++k) {
         const double *d = dep + (long)k * NLINE + base;
 #pragma unroll 8
-        for (int a = h; a < nslot; a += 2) s += d[(long)a * PBS_PT];
+        for (int a = 2 * w + h; a < nslot; a += 8) s += d[(long)a * PBS_PT];
     }
     s += __shfl_xor(s, 32);
+    __syncthreads();   // a second reduction of the same block: the first one's partials have been read
+    if (h == 0) part[w][pt] = s;
+    __syncthreads();
     const int pq = pb * PBS_PT + pt;
-    if (h == 0 && pq < NP) edep[pq] += s;
+    if (tid < 32 && pq < NP) edep[pq] += ((part[0][pt] + part[1][pt]) + part[2][pt]) + part[3][pt];
 }
 
-__global__ __launch_bounds__(64) void dose_reduce_kernel(double *edep, const double *dep, int ngen, int NA,
-                                                         int nslot, long NLINE, int NP)
+// blockIdx.y picks the reduction: rows that differ, so that the blocks of one launch never meet
+__global__ __launch_bounds__(256) void dose_reduce_kernel(DoseJobs J, int NA, int nslot, long NLINE, int NP)
 {
-    dose_reduce_body(edep, dep, ngen, NA, nslot, NLINE, NP, blockIdx.x);
+    const int j = blockIdx.y;
+    dose_reduce_body(J.row[j], J.dep[j], J.ngen[j], NA, nslot, NLINE, NP, blockIdx.x);
 }
 
-hipError_t launch_dose_reduce(double *edep_layer, const double *dep, int ngen, int NA, int nslot, long NLINE, int NP,
-                              hipStream_t st)
+hipError_t launch_dose_reduce(const DoseJobs &J, int NA, int nslot, long NLINE, int NP, hipStream_t st)
 {
+    if (J.n <= 0) return hipSuccess;
+    for (int i = 0; i < J.n; ++i)
+        for (int j = i + 1; j < J.n; ++j)
+            if (J.row[i] == J.row[j]) {
+                // one row twice (both halves of an extrapolated step's inner pair): one launch after the other
+                DoseJobs A = J, B = J;
+                A.n = j;
+                B.n = J.n - j;
+                for (int q = 0; q < B.n; ++q) B.row[q] = J.row[j + q], B.dep[q] = J.dep[j + q], B.ngen[q] = J.ngen[j + q];
+                const hipError_t e = launch_dose_reduce(A, NA, nslot, NLINE, NP, st);
+                return e != hipSuccess ? e : launch_dose_reduce(B, NA, nslot, NLINE, NP, st);
+            }
     const int npb = (NP + PBS_PT - 1) / PBS_PT;
-    hipLaunchKernelGGL(dose_reduce_kernel, dim3(npb), dim3(64), 0, st, edep_layer, dep, ngen, NA, nslot, NLINE, NP);
+    hipLaunchKernelGGL(dose_reduce_kernel, dim3(npb, J.n), dim3(256), 0, st, J, NA, nslot, NLINE, NP);
     return hipGetLastError();
 }
 
@@ -3228,7 +3289,6 @@ __attribute__((amdgpu_waves_per_eu(BN == 0 && NPROD == 1 ? QG_WPE : 1))) void qg
     const int mode = beam_mode(s, B.nz);
     if (mode == 0) return;
     QParams<float> P;
-    P.P2T = nullptr;
     P.W = nullptr;
     P.Q = B.Q;
     P.Qb = NPROD == 1 ? reinterpret_cast<unsigned short *>(B.Q) : nullptr;   // single product: BF16 source
@@ -3367,7 +3427,7 @@ void apass_mfma_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh,
         apass_mfma16_body(P, Sh.K, blockIdx.y, pb, half);
 }
 
-__global__ __launch_bounds__(64) void dose_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh, int s)
+__global__ __launch_bounds__(256) void dose_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh, int s)
 {
     const BeamDev &B = beams[blockIdx.y];
     const int mode = beam_mode(s, B.nz);
@@ -3521,7 +3581,7 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
 #undef PBS_QG
         }
     }
-    hipLaunchKernelGGL(dose_batched_kernel, dim3(Sh.NPB, nbeam), dim3(64), 0, st, beams, Sh, s);
+    hipLaunchKernelGGL(dose_batched_kernel, dim3(Sh.NPB, nbeam), dim3(256), 0, st, beams, Sh, s);
     if (!sd && march) {
         const hipError_t e = tat(-1, st);
         if (e != hipSuccess) return e;

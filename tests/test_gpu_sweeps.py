@@ -110,3 +110,25 @@ def test_transport_widths(O, nx, ny, prec):
     got = s.state()
     s.close()
     _check(got, ref, prec, "transport")
+
+
+# every number of 32-row waves of the small product (9, 25, 49, 81, 121 angles), one tile per block and, past 8192
+# (half, group, tile) items, several (with a last block that is not full); the dose checks the reduction's slots
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,nth,ng", [(3, 5, 4, 3), (5, 7, 6, 4), (6, 6, 8, 5), (9, 8, 10, 3), (4, 9, 12, 4),
+                                          (67, 64, 4, 70), (65, 65, 6, 66)])
+def test_small_source_product_and_dose(O, nx, ny, nth, ng, prec):
+    print("case small source product", nx, ny, nth, ng, prec, flush=True)
+    s, o, c, st = _setup(O, prec, dict(nx=nx, ny=ny, nth=nth, ng=ng, ngen=2))
+    ref = st.copy()
+    rho = np.ascontiguousarray(c["rho"][1].reshape(-1))
+    dep = o.energy_all(ref, rho, 0.02)
+    s.apply(1, 1, 0.02)
+    got, dose = s.state(), s.dose()[1].reshape(-1)
+    vol = o.dx * o.dy * c["grid"]["dz"]
+    s.close()
+    _check(got, ref, prec, "source")
+    e = np.linalg.norm(dose - dep / (rho * vol)) / np.linalg.norm(dep / (rho * vol))
+    print("dose", e, flush=True)
+    # the oracle's deposit is a difference of energy contents, far larger than it
+    assert e <= (1e-11 if prec == "fp64" else TOL[prec])
