@@ -2884,115 +2884,27 @@ hipError_t launch_qgemm_bf16s(const QParams<float> &P, const unsigned short *Ahi
     return hipGetLastError();
 }
 
-// FP64 MFMA version (v_mfma_f64_16x16x4_f64, output row = lane/16 + 4 q, column = lane % 16).
-// Block tile 128 x 128 (4 lateral tiles), BK = 16; 4 waves in 2 x 2, each 64 x 64 = 4 x 4 MFMA tiles.
-// Up to 2 waves per SIMD: with the compiler's default target it spilled 80 bytes per thread.
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void qgemm_mfma_f64_kernel(QParams<double> P, int nmt, int nnt, long nlogical,
-                                                             long per_xcd)
-{
-    const long bid = blockIdx.x;
-    const long logical = (bid & 7) * per_xcd + (bid >> 3);
-    if (logical >= nlogical) return;
-    const int mt = (int)(logical % nmt);
-    const long rest = logical / nmt;
-    const int nt = (int)(rest % nnt);
-    const long batch = rest / nnt;
-    const int s = P.s0 + (int)(batch / P.G), g = (int)(batch % P.G);
-    const long off = ((long)s * P.G + g) * P.NLINE;
-    const double *__restrict__ B = P.W + off;
-    double *__restrict__ C = P.Q + off;
-    const double *__restrict__ P2p = P.P2p + (P.band ? (long)P.band[g] * P.Kp * P.Mp : 0L);
-    const long NAPT = (long)P.NA * PBS_PT;
-    __shared__ double As[16][130];
-    __shared__ double Bs[16][130];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int wm = wid >> 1, wn = wid & 1;
-    doublex4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
-    const int nk = P.Kp / 16;
-    double2 ra[4], rb[4];
-    auto gload = [&](int kt) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int idx = tid + 256 * i;
-            const int k = idx >> 6, q2 = idx & 63;
-            ra[i] = *reinterpret_cast<const double2 *>(P2p + (long)(kt * 16 + k) * P.Mp + mt * 128 + q2 * 2);
-            const int col = q2 * 2, pb = nt * 4 + (col >> 5), pt = col & 31;
-            const int gk = kt * 16 + k;
-            if (gk < P.NA && pb < P.NPB)
-                rb[i] = *reinterpret_cast<const double2 *>(B + pb * NAPT + (long)gk * PBS_PT + pt);
-            else
-                rb[i] = make_double2(0.0, 0.0);
-        }
-    };
-    auto sstore = [&]() {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int idx = tid + 256 * i;
-            const int k = idx >> 6, q2 = idx & 63;
-            *reinterpret_cast<double2 *>(&As[k][q2 * 2]) = ra[i];
-            *reinterpret_cast<double2 *>(&Bs[k][q2 * 2]) = rb[i];
-        }
-    };
-    gload(0);
-    sstore();
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        if (kt + 1 < nk) gload(kt + 1);
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const int kr = 4 * kk + (lane >> 4);
-            double a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kr][wm * 64 + i * 16 + (lane & 15)];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kr][wn * 64 + j * 16 + (lane & 15)];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
-        if (kt + 1 < nk) {
-            sstore();
-            __syncthreads();
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int col = wn * 64 + j * 16 + (lane & 15);
-            const int pb = nt * 4 + (col >> 5), pt = col & 31;
-            if (pb >= P.NPB) continue;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = mt * 128 + wm * 64 + i * 16 + (lane >> 4) + 4 * q;
-                if (row < P.NA) C[pb * NAPT + (long)row * PBS_PT + pt] = acc[i][j][q];
-            }
-        }
-}
-
-// Fewer than 128 angular unknowns (up to 12 nodes per axis), FP32 and FP64: v_mfma_f32_16x16x4 / v_mfma_f64_16x16x4.
+// FP64, and FP32 below 128 angular unknowns (up to 12 nodes per axis): v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4.
 // What bounded the vector kernel it replaces: its LDS staging (a barrier pair per 32 source nodes) on small
 // grids, two LDS reads per multiply on large ones.  Here both operands go from global memory straight into MFMA
-// registers: P2 (zero-padded [Kp][Mp], at most 64 | 128 KB, resident in L2) and the scan, whose row of 32 cells
+// registers: P2 (zero-padded [Kp][Mp], resident in L2) and the scan, whose row of 32 cells
 // a lane reads as one pair, cell 2 c + h being column c of column tile h.  Block = up to 4 waves of 32 destination
-// rows each over NTL lateral tiles of one (half, group); loads run QS_PF 4-node steps ahead.  NTL = 1 where the
+// rows each (blockIdx.y: the next 128 rows) over NTL lateral tiles of one (half, group); loads run QS_PF 4-node steps ahead.  NTL = 1 where the
 // grid has few tiles (latency), else as many as the registers hold, for each P2 load to feed more products.
 // Measured, us per product, before -> after: 4 x 4 cells, 11 x 11 angles, 60 groups 21 -> 10; 24 x 24, 9 x 9, 60 73 ->
 // 22 (FP64 121 -> 32); 48 x 128, 11 x 11, 60 1104 -> 321; 90 x 96, 7 x 7, 80 in FP64 845 -> 244.
+// In FP64 it also beats a 128 x 128 block tile staged in LDS at every size (64 x 64 cells, 15 x 15 angles, 64 groups 1472 ->
+// 1200, 44 TFLOP/s; 32 x 32, 31 x 31, 32 2688 -> 2390); in FP32 that kernel (qgemm_mfma_f32_kernel) wins from 128
+// unknowns on (685 against 788, 4678 against 6297 at 64 x 64, 31 x 31, 32 groups): a matrix step there takes half the
+// time and the operand loads no longer hide behind it.
 constexpr int QS_PF = 4;
 __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ doublex4 mfma4(double a, double b, doublex4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 template <typename T, int NTL>
-__global__ __launch_bounds__(256) void qgemm_small_kernel(QParams<T> P, int nnt)
+__global__ __launch_bounds__(256) void qgemm_direct_kernel(QParams<T> P, int nnt)
 {
     typedef T T2 __attribute__((ext_vector_type(2)));
     typedef T T4 __attribute__((ext_vector_type(4)));
@@ -3001,7 +2913,8 @@ __global__ __launch_bounds__(256) void qgemm_small_kernel(QParams<T> P, int nnt)
     const int g = (int)(sg % P.G), s = P.s0 + (int)(sg / P.G);
     const long off = ((long)s * P.G + g) * P.NLINE, NAPT = (long)P.NA * PBS_PT;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, kq = lane >> 4;
-    const T *A = P.P2p + (P.band ? (long)P.band[g] * P.Kp * P.Mp : 0L) + (long)kq * P.Mp + 32 * w + c;
+    const int row0 = 128 * (int)blockIdx.y + 32 * w;   // this wave's destination rows
+    const T *A = P.P2p + (P.band ? (long)P.band[g] * P.Kp * P.Mp : 0L) + (long)kq * P.Mp + row0 + c;
     const T *B[NTL];
 #pragma unroll
     for (int j = 0; j < NTL; ++j) B[j] = P.W + off + (long)min(nt * NTL + j, P.NPB - 1) * NAPT + 2 * c;
@@ -3055,7 +2968,7 @@ __global__ __launch_bounds__(256) void qgemm_small_kernel(QParams<T> P, int nnt)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 // result rows of a lane: FP32 4 (lane / 16) + q, FP64 lane / 16 + 4 q
-                const int row = 32 * w + 16 * i + (sizeof(T) == 4 ? 4 * kq + q : kq + 4 * q);
+                const int row = row0 + 16 * i + (sizeof(T) == 4 ? 4 * kq + q : kq + 4 * q);
                 if (row < P.NA)
                     *reinterpret_cast<T2 *>(P.Q + off + pb * NAPT + (long)row * PBS_PT + 2 * c) =
                         T2{acc[i][j][0][q], acc[i][j][1][q]};
@@ -3068,16 +2981,17 @@ __global__ __launch_bounds__(256) void qgemm_small_kernel(QParams<T> P, int nnt)
 // 32 x 32, 11 x 11, 60 (3840) 58 against 55 and 4 x 4 (120) 15.5 against 9.7.
 constexpr long QS_WIDE_ITEMS = 8192;
 template <typename T>
-static hipError_t launch_qgemm_small(const QParams<T> &P, hipStream_t st)
+static hipError_t launch_qgemm_direct(const QParams<T> &P, hipStream_t st)
 {
     constexpr int WIDE = sizeof(T) == 4 ? 4 : 2;
-    const dim3 block(64 * (P.Mp / 32));
+    const dim3 block(P.Mp >= 128 ? 256 : 64 * (P.Mp / 32));
+    const unsigned nmt = (unsigned)((P.Mp + 127) / 128);
     const long items = (long)P.ns * P.G * P.NPB;
     if (items > QS_WIDE_ITEMS) {
         const int nnt = (P.NPB + WIDE - 1) / WIDE;
-        hipLaunchKernelGGL((qgemm_small_kernel<T, WIDE>), dim3((unsigned)((long)P.ns * P.G * nnt)), block, 0, st, P, nnt);
+        hipLaunchKernelGGL((qgemm_direct_kernel<T, WIDE>), dim3((unsigned)((long)P.ns * P.G * nnt), nmt), block, 0, st, P, nnt);
     } else {
-        hipLaunchKernelGGL((qgemm_small_kernel<T, 1>), dim3((unsigned)items), block, 0, st, P, P.NPB);
+        hipLaunchKernelGGL((qgemm_direct_kernel<T, 1>), dim3((unsigned)items, nmt), block, 0, st, P, P.NPB);
     }
     return hipGetLastError();
 }
@@ -3086,15 +3000,17 @@ template <typename T>
 hipError_t launch_qgemm(const QParams<T> &P, hipStream_t st)
 {
     if (P.P2p == nullptr) return hipErrorInvalidValue;
-    if (P.NA < 128) return launch_qgemm_small(P, st);
-    const int nmt = P.Mp / 128, nnt = (P.NPB + 3) / 4;
-    const long nlog = (long)P.ns * P.G * nnt * nmt;
-    const long per = (nlog + 7) / 8;
-    if constexpr (sizeof(T) == 8)
-        hipLaunchKernelGGL(qgemm_mfma_f64_kernel, dim3((unsigned)(per * 8)), dim3(256), 0, st, P, nmt, nnt, nlog, per);
-    else
-        hipLaunchKernelGGL(qgemm_mfma_f32_kernel, dim3((unsigned)(per * 8)), dim3(256), 0, st, P, nmt, nnt, nlog, per);
-    return hipGetLastError();
+    if constexpr (sizeof(T) == 4) {
+        if (P.NA >= 128) {
+            const int nmt = P.Mp / 128, nnt = (P.NPB + 3) / 4;
+            const long nlog = (long)P.ns * P.G * nnt * nmt;
+            const long per = (nlog + 7) / 8;
+            hipLaunchKernelGGL(qgemm_mfma_f32_kernel, dim3((unsigned)(per * 8)), dim3(256), 0, st, P, nmt, nnt, nlog,
+                               per);
+            return hipGetLastError();
+        }
+    }
+    return launch_qgemm_direct(P, st);
 }
 
 // ----------------------------------------------------------------------------------- misc
