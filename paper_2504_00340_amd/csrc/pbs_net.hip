@@ -302,29 +302,39 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const __bf16 *__restrict__ i
     }
 }
 
-// grad (parameter order) = sum over blocks of the partials, real channels only.  A block sums 32 entries over 8
-// interleaved subsets of the partials, then the 8 sums in order (fixed order: bitwise reproducible).  One thread
-// per entry walking every partial in turn waited out one load latency after another: 121 us for the 512
-// partials of 32 slices of 64 x 64 pixels.
-constexpr int WR_SUB = 8;
+// grad (parameter order) = sum over blocks of the partials in their order, real channels only.  The order of the
+// sum is part of a training run's bits, so it stays serial; what it waited for was one load after another.  Here a
+// block brings 256 partials of 32 entries at a time to LDS, all loads in flight and the next 256 behind them, and 32
+// lanes add them up: 121 -> 8 us for the 512 partials of 32 slices of 64 x 64 pixels.
+constexpr int WR_NB = 256;
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ part, long nblk, int CIN, int COP,
                                                            int cin, int cout, float *__restrict__ gw,
                                                            float *__restrict__ gb)
 {
-    __shared__ float red[WR_SUB][32];
+    __shared__ float red[WR_NB][32];
     const long PSZ = 9L * COP * CIN + COP;
     const int le = threadIdx.x & 31, sub = threadIdx.x >> 5;
-    const long e = (long)blockIdx.x * 32 + le;
-    float s = 0.f;
-    if (e < PSZ) {
-#pragma unroll 16
-        for (long b = sub; b < nblk; b += WR_SUB) s += part[b * PSZ + e];
-    }
-    red[sub][le] = s;
-    __syncthreads();
-    if (sub != 0 || e >= PSZ) return;
+    const long e = (long)blockIdx.x * 32 + le, ec = min(e, PSZ - 1);
+    float v[WR_NB / 8];
+    auto fetch = [&](long c0) {   // partials past the last one re-read it and are not added
 #pragma unroll
-    for (int k = 1; k < WR_SUB; ++k) s += red[k][le];
+        for (int i = 0; i < WR_NB / 8; ++i) v[i] = part[min(c0 + sub + 8 * i, nblk - 1) * PSZ + ec];
+    };
+    fetch(0);
+    float s = 0.f;
+    for (long c0 = 0; c0 < nblk; c0 += WR_NB) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < WR_NB / 8; ++i) red[sub + 8 * i][le] = v[i];
+        __syncthreads();
+        if (c0 + WR_NB < nblk) fetch(c0 + WR_NB);
+        if (sub == 0) {
+            const int n = (int)min((long)WR_NB, nblk - c0);
+#pragma unroll 16
+            for (int b = 0; b < n; ++b) s += red[b][le];
+        }
+    }
+    if (sub != 0 || e >= PSZ) return;
     if (e >= 9L * COP * CIN) {
         const int co = (int)(e - 9L * COP * CIN);
         if (co < cout) gb[co] = s;
