@@ -749,7 +749,7 @@ pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, in
         {
             ProfScope ps(c, PBS_K_EPASS);
             if (c->strag) {
-                HIPCHK(c, launch_epass_strag<T>(P, mode, c->stream));
+                HIPCHK(c, launch_epass_strag<T>(P, mode, k == 0, c->stream));
             } else if constexpr (sizeof(T) == 4) {
                 if (e8) {
                     HIPCHK(c, launch_epass8(P, mode, c->stream));

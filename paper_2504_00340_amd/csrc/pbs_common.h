@@ -156,8 +156,9 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
 
 // launchers (explicitly instantiated for float and double); return hipGetLastError()
 template <typename T> hipError_t launch_epass(const EParams<T> &P, int mode, hipStream_t st);
-// energy pass with straggling (P.blk set): factor kernel per cell and half-step, then one thread per line
-template <typename T> hipError_t launch_epass_strag(const EParams<T> &P, int mode, hipStream_t st);
+// energy pass with straggling (P.blk set), one thread per line; factors: compute the elimination factors of the
+// cells first (the same for every generation of a chain)
+template <typename T> hipError_t launch_epass_strag(const EParams<T> &P, int mode, bool factors, hipStream_t st);
 // FP32 with split-BF16 scans (Wh set or no next generation): thread per (cell, group of
 // PBS_EPASS_LPT lines of an octet); deposits and records summed per group at line slot a = group
 // (reduce over epass8_slots(NOCT) slots)

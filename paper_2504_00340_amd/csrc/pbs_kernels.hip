@@ -239,35 +239,41 @@ hipError_t launch_epass(const EParams<T> &P, int mode, hipStream_t st)
 // (X*_g = Dt_g^-1 (bt_g + a Lo_g X*_{g-1})).  The energy scans of the next generation's source take a
 // third sweep down over X*.
 
+// One thread per cell, both half-steps of a chain in one launch (blockIdx.y), once for all generations.  It is a
+// serial FP64 chain over the groups, so what counts is its length: the table entries arrive as scalar loads and
+// the determinant is inverted once (four divisions before): 69 us per half-step and generation, four
+// times a step of two generations, -> 59 us once (24 x 24 cells, 110 groups).
 template <typename T>
-__global__ __launch_bounds__(256) void strag_factor_kernel(const T *__restrict__ blk, const T *__restrict__ rho, T h,
-                                                             int G, long NPpad, T *__restrict__ sfac)
+__global__ __launch_bounds__(64) void strag_factor_kernel(EParams<T> P, int first)
 {
-    const long pq = (long)blockIdx.x * 256 + threadIdx.x;
+    const long pq = (long)blockIdx.x * 64 + threadIdx.x, NPpad = P.NPpad;
     if (pq >= NPpad) return;
-    const double a = 0.5 * (double)h * (double)rho[pq];
-    double di[4] = {0, 0, 0, 0};   // Dt_{g+1}^-1
-    for (int g = G - 1; g >= 0; --g) {
-        const T *B = blk + (size_t)g * 12;
-        double M[4] = {1.0 - a * (double)B[4], -a * (double)B[5], -a * (double)B[6], 1.0 - a * (double)B[7]};
-        double F[4] = {0, 0, 0, 0};
-        if (g + 1 < G) {
-            const T *Bn = blk + (size_t)(g + 1) * 12;   // Lo of group g+1
-            const double U[4] = {a * (double)B[8], a * (double)B[9], a * (double)B[10], a * (double)B[11]};
-            F[0] = U[0] * di[0] + U[1] * di[2], F[1] = U[0] * di[1] + U[1] * di[3];
-            F[2] = U[2] * di[0] + U[3] * di[2], F[3] = U[2] * di[1] + U[3] * di[3];
-            const double L[4] = {a * (double)Bn[0], a * (double)Bn[1], a * (double)Bn[2], a * (double)Bn[3]};
-            M[0] -= F[0] * L[0] + F[1] * L[2], M[1] -= F[0] * L[1] + F[1] * L[3];
-            M[2] -= F[2] * L[0] + F[3] * L[2], M[3] -= F[2] * L[1] + F[3] * L[3];
-        }
-        const double det = M[0] * M[3] - M[1] * M[2];
-        di[0] = M[3] / det, di[1] = -M[1] / det, di[2] = -M[2] / det, di[3] = M[0] / det;
+    const bool open = first + (int)blockIdx.y == 1;
+    const T *rho = open ? P.rho_o : P.rho_c;
+    T *sfac = open ? P.sfac_o : P.sfac_c;
+    const double a = 0.5 * (double)P.h * (double)rho[pq];
+    double di[4] = {0, 0, 0, 0};     // Dt_{g+1}^-1
+    double L[4] = {0, 0, 0, 0};      // a Lo of group g+1
+    for (int g = P.G - 1; g >= 0; --g) {
+        double B[12];
+#pragma unroll
+        for (int i = 0; i < 12; ++i) B[i] = a * (double)tab(P.blk, 12L * g + i);
+        // F = a Up Dt_{g+1}^-1; zero above the top group, where di is
+        const double F0 = B[8] * di[0] + B[9] * di[2], F1 = B[8] * di[1] + B[9] * di[3];
+        const double F2 = B[10] * di[0] + B[11] * di[2], F3 = B[10] * di[1] + B[11] * di[3];
+        const double m0 = (1.0 - B[4]) - (F0 * L[0] + F1 * L[2]), m1 = -B[5] - (F0 * L[1] + F1 * L[3]);
+        const double m2 = -B[6] - (F2 * L[0] + F3 * L[2]), m3 = (1.0 - B[7]) - (F2 * L[1] + F3 * L[3]);
+        const double idet = 1.0 / (m0 * m3 - m1 * m2);
+        di[0] = m3 * idet, di[1] = -m1 * idet, di[2] = -m2 * idet, di[3] = m0 * idet;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) L[i] = B[i];
         T *o = sfac + (size_t)g * 8 * NPpad + pq;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            o[q * NPpad] = (T)di[q];
-            o[(4 + q) * NPpad] = (T)F[q];
-        }
+        for (int q = 0; q < 4; ++q) o[q * NPpad] = (T)di[q];
+        o[4 * NPpad] = (T)F0;
+        o[5 * NPpad] = (T)F1;
+        o[6 * NPpad] = (T)F2;
+        o[7 * NPpad] = (T)F3;
     }
 }
 
@@ -289,70 +295,136 @@ __device__ __forceinline__ T scan_step(const EParams<T> &P, int g, T x, T &U, T 
     }
 }
 
-template <typename T, bool BANDS>
-__device__ void strag_half(const EParams<T> &P, long line, long pq, int half, double &dep_out)
-{
-    const long S = P.NLINE, QS = (long)P.G * S;
-    const T *rho = half ? P.rho_o : P.rho_c;
-    const T *sf = (half ? P.sfac_o : P.sfac_c) + pq;
-    const long FS = P.NPpad;
-    const double ad = 0.5 * (double)P.h * (double)rho[pq];
-    const T a = (T)ad;
-    const bool hasQ = P.Q != nullptr, hasW = P.W != nullptr;
-    T *W = hasW ? P.W + (long)half * QS : nullptr;
-    const T *Q = hasQ ? P.Q + (long)half * QS : nullptr;
-    double phn = 0, phs = 0, inj = 0;
-    // sweep down: right-hand side, elimination (bt kept in place of X), scan of X^n
-    T xu1 = 0, xu2 = 0, bu1 = 0, bu2 = 0;   // X^n and bt of group g+1
-    T x1 = P.psi[(2L * (P.G - 1)) * S + line], x2 = P.psi[(2L * (P.G - 1) + 1) * S + line];
-    T U = 0, Ub[4] = {};
-    for (int g = P.G - 1; g >= 0; --g) {
-        T xl1 = 0, xl2 = 0;   // X^n of group g-1
-        if (g > 0) {
-            xl1 = P.psi[(2L * (g - 1)) * S + line];
-            xl2 = P.psi[(2L * (g - 1) + 1) * S + line];
-        }
-        const T *B = P.blk + (size_t)g * 12;
-        const T q = hasQ ? Q[(long)g * S + line] : T(0);
-        T b1 = x1 + a * (B[0] * xl1 + B[1] * xl2 + B[4] * x1 + B[5] * x2 + B[8] * xu1 + B[9] * xu2 + q);
-        T b2 = x2 + a * (B[2] * xl1 + B[3] * xl2 + B[6] * x1 + B[7] * x2 + B[10] * xu1 + B[11] * xu2);
-        const T *Fg = sf + (size_t)g * 8 * FS + 4 * FS;
-        b1 += Fg[0] * bu1 + Fg[FS] * bu2;
-        b2 += Fg[2 * FS] * bu1 + Fg[3 * FS] * bu2;
-        P.psi[(2L * g) * S + line] = b1;
-        P.psi[(2L * g + 1) * S + line] = b2;
-        phn += tab(P.dA2, g) * (double)x1 + tab(P.dB2, g) * (double)x2;
-        if (hasQ) inj += tab(P.dInj, g) * (double)q;
-        if (hasW) W[(long)g * S + line] = scan_step<T, BANDS>(P, g, x1, U, Ub) * tab(P.invdE, g);
-        xu1 = x1, xu2 = x2, bu1 = b1, bu2 = b2;
-        x1 = xl1, x2 = xl2;
-    }
-    // sweep up: back-substitution
-    T y1p = 0, y2p = 0;
-    for (int g = 0; g < P.G; ++g) {
-        const T *B = P.blk + (size_t)g * 12;
-        T c1 = P.psi[(2L * g) * S + line], c2 = P.psi[(2L * g + 1) * S + line];
-        c1 += a * (B[0] * y1p + B[1] * y2p);
-        c2 += a * (B[2] * y1p + B[3] * y2p);
-        const T *Di = sf + (size_t)g * 8 * FS;
-        const T y1 = Di[0] * c1 + Di[FS] * c2, y2 = Di[2 * FS] * c1 + Di[3 * FS] * c2;
-        P.psi[(2L * g) * S + line] = y1;
-        P.psi[(2L * g + 1) * S + line] = y2;
-        phs += tab(P.dA2, g) * (double)y1 + tab(P.dB2, g) * (double)y2;
-        y1p = y1, y2p = y2;
-    }
-    // sweep down: the scan of X*, added to that of X^n
-    if (hasW) {
-        U = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) Ub[b] = 0;
-        for (int g = P.G - 1; g >= 0; --g)
-            W[(long)g * S + line] += scan_step<T, BANDS>(P, g, P.psi[(2L * g) * S + line], U, Ub) * tab(P.invdE, g);
-    }
-    dep_out = ad * (phn + phs - inj) * P.scale;
-}
+// The sweeps of one line, each with EP_RING groups in flight (as the plain pass: a group's loads are issued before
+// the stores of the groups ahead of it, without a branch; past the last group they re-read it and are not used).
+// Three sweeps a half-step, but the scan of a closing half-step's result is the scan of the opening one's start:
+// a fused pair takes that sum along in the opening sweep down, five sweeps instead of six.
+// Measured with the factors, us per generation: 24 x 24 cells, 15 x 15 angles, 110 groups 426 -> 294 (FP64 936 ->
+// 630); 10 x 12, 9 x 9, 60 174 -> 84; 64 x 64, 11 x 11, 60 664 -> 496.
+template <typename T, bool BANDS, bool HASQ>
+struct StragLine {
+    const EParams<T> &P;
+    const long line, pq, S, FS;
 
-template <typename T, int MODE, bool BANDS>
+    template <typename F>
+    __device__ __forceinline__ void groups(F &&step) const   // step(k, slot) for k = 0 .. G-1
+    {
+        int k = 0;
+        for (; k + EP_RING <= P.G; k += EP_RING) {
+#pragma unroll
+            for (int u = 0; u < EP_RING; ++u) step(k + u, u);
+        }
+#pragma unroll
+        for (int u = 0; u < EP_RING - 1; ++u)
+            if (k + u < P.G) step(k + u, u);
+    }
+
+    // right-hand side and elimination from the top (bt kept in place of X), deposit and scan of X^n; ADDPREV adds the
+    // scan to the closing half-step's sum as well
+    template <bool ADDPREV>
+    __device__ __forceinline__ void down(int half, T a, double &phn, double &inj) const
+    {
+        const T *sf = (half ? P.sfac_o : P.sfac_c) + pq;
+        const bool hasW = P.W != nullptr;
+        const long QS = (long)P.G * S;
+        T *W = hasW ? P.W + (long)half * QS + line : nullptr, *W0 = P.W + line;
+        T xl1[EP_RING], xl2[EP_RING], f[EP_RING][4], q[EP_RING], wp[EP_RING];
+        auto fetch = [&](int k, int u) {   // k-th group from the top
+            const long g = max(P.G - 1 - k, 0), gl = max(P.G - 2 - k, 0);
+            const T *p = P.psi + 2 * gl * S + line;
+            xl1[u] = p[0];
+            xl2[u] = p[S];
+            const T *F = sf + g * 8 * FS + 4 * FS;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f[u][i] = F[i * FS];
+            if constexpr (HASQ) q[u] = P.Q[(long)half * QS + g * S + line];
+            if constexpr (ADDPREV) wp[u] = W0[g * S];
+        };
+        T xu1 = 0, xu2 = 0, bu1 = 0, bu2 = 0;   // X^n and bt of group g+1
+        T x1 = P.psi[2L * (P.G - 1) * S + line], x2 = P.psi[(2L * (P.G - 1) + 1) * S + line];
+        T U = 0, Ub[4] = {};
+#pragma unroll
+        for (int u = 0; u < EP_RING; ++u) fetch(u, u);
+        groups([&](int k, int u) {
+            const int g = P.G - 1 - k;
+            const T l1 = g > 0 ? xl1[u] : T(0), l2 = g > 0 ? xl2[u] : T(0);   // X^n of group g-1
+            const T F[4] = {f[u][0], f[u][1], f[u][2], f[u][3]};
+            const T qg = HASQ ? q[u] : T(0), w0 = ADDPREV ? wp[u] : T(0);
+            fetch(k + EP_RING, u);
+            T B[12];
+#pragma unroll
+            for (int i = 0; i < 12; ++i) B[i] = tab(P.blk, 12L * g + i);
+            T b1 = x1 + a * (B[0] * l1 + B[1] * l2 + B[4] * x1 + B[5] * x2 + B[8] * xu1 + B[9] * xu2 + qg);
+            T b2 = x2 + a * (B[2] * l1 + B[3] * l2 + B[6] * x1 + B[7] * x2 + B[10] * xu1 + B[11] * xu2);
+            b1 += F[0] * bu1 + F[1] * bu2;
+            b2 += F[2] * bu1 + F[3] * bu2;
+            P.psi[2L * g * S + line] = b1;
+            P.psi[(2L * g + 1) * S + line] = b2;
+            phn += tab(P.dA2, g) * (double)x1 + tab(P.dB2, g) * (double)x2;
+            if constexpr (HASQ) inj += tab(P.dInj, g) * (double)qg;
+            if (hasW) {
+                const T u1 = scan_step<T, BANDS>(P, g, x1, U, Ub), idE = tab(P.invdE, g);
+                W[(long)g * S] = u1 * idE;
+                if constexpr (ADDPREV) W0[(long)g * S] = w0 + u1 * idE;
+            }
+            xu1 = x1, xu2 = x2, bu1 = b1, bu2 = b2;
+            x1 = l1, x2 = l2;
+        });
+    }
+
+    // back-substitution, deposit of X*
+    __device__ __forceinline__ void up(int half, T a, double &phs) const
+    {
+        const T *sf = (half ? P.sfac_o : P.sfac_c) + pq;
+        T c1[EP_RING], c2[EP_RING], d[EP_RING][4];
+        auto fetch = [&](int k, int u) {
+            const long g = min(k, P.G - 1);
+            c1[u] = P.psi[2 * g * S + line];
+            c2[u] = P.psi[(2 * g + 1) * S + line];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[u][i] = sf[g * 8 * FS + i * FS];
+        };
+        T y1p = 0, y2p = 0;
+#pragma unroll
+        for (int u = 0; u < EP_RING; ++u) fetch(u, u);
+        groups([&](int g, int u) {
+            T b1 = c1[u], b2 = c2[u];
+            const T D[4] = {d[u][0], d[u][1], d[u][2], d[u][3]};
+            fetch(g + EP_RING, u);
+            b1 += a * (tab(P.blk, 12L * g) * y1p + tab(P.blk, 12L * g + 1) * y2p);
+            b2 += a * (tab(P.blk, 12L * g + 2) * y1p + tab(P.blk, 12L * g + 3) * y2p);
+            const T y1 = D[0] * b1 + D[1] * b2, y2 = D[2] * b1 + D[3] * b2;
+            P.psi[2L * g * S + line] = y1;
+            P.psi[(2L * g + 1) * S + line] = y2;
+            phs += tab(P.dA2, g) * (double)y1 + tab(P.dB2, g) * (double)y2;
+            y1p = y1, y2p = y2;
+        });
+    }
+
+    // the scan of X*, added to that of X^n
+    __device__ __forceinline__ void rescan(int half) const
+    {
+        if (P.W == nullptr) return;
+        T *W = P.W + (long)half * P.G * S + line;
+        T x[EP_RING], w[EP_RING];
+        auto fetch = [&](int k, int u) {
+            const long g = max(P.G - 1 - k, 0);
+            x[u] = P.psi[2 * g * S + line];
+            w[u] = W[g * S];
+        };
+        T U = 0, Ub[4] = {};
+#pragma unroll
+        for (int u = 0; u < EP_RING; ++u) fetch(u, u);
+        groups([&](int k, int u) {
+            const int g = P.G - 1 - k;
+            const T xg = x[u], wg = w[u];
+            fetch(k + EP_RING, u);
+            W[(long)g * S] = wg + scan_step<T, BANDS>(P, g, xg, U, Ub) * tab(P.invdE, g);
+        });
+    }
+};
+
+template <typename T, int MODE, bool BANDS, bool HASQ>
 __global__ __launch_bounds__(256) void epass_strag_kernel(EParams<T> P)
 {
     const int NA = (int)(P.NAPT / PBS_PT);
@@ -362,46 +434,58 @@ __global__ __launch_bounds__(256) void epass_strag_kernel(EParams<T> P)
     if (a >= NA) return;
     const long line = ((long)pbk * NA + a) * PBS_PT + ptc;
     const long pq = (long)pbk * PBS_PT + ptc;
-    double d;
+    const StragLine<T, BANDS, HASQ> L{P, line, pq, P.NLINE, P.NPpad};
     if (MODE & MODE_CLOSE) {
-        strag_half<T, BANDS>(P, line, pq, 0, d);
-        P.dep_c[line] = d;
+        const double ad = 0.5 * (double)P.h * (double)P.rho_c[pq];
+        double phn = 0, phs = 0, inj = 0;
+        L.template down<false>(0, (T)ad, phn, inj);
+        L.up(0, (T)ad, phs);
+        if (MODE == MODE_CLOSE) L.rescan(0);
+        P.dep_c[line] = ad * (phn + phs - inj) * P.scale;
     }
     if (MODE & MODE_OPEN) {
-        strag_half<T, BANDS>(P, line, pq, 1, d);
-        P.dep_o[line] = d;
+        const double ad = 0.5 * (double)P.h * (double)P.rho_o[pq];
+        double phn = 0, phs = 0, inj = 0;
+        if (MODE == MODE_PAIR && P.W != nullptr)
+            L.template down<true>(1, (T)ad, phn, inj);
+        else
+            L.template down<false>(1, (T)ad, phn, inj);
+        L.up(1, (T)ad, phs);
+        L.rescan(1);
+        P.dep_o[line] = ad * (phn + phs - inj) * P.scale;
     }
 }
 
-template <typename T, bool BANDS>
+template <typename T, bool BANDS, bool HASQ>
 static void launch_epass_strag_t(const EParams<T> &P, int mode, unsigned nb, hipStream_t st)
 {
     if (mode == MODE_PAIR)
-        hipLaunchKernelGGL((epass_strag_kernel<T, MODE_PAIR, BANDS>), dim3(nb), dim3(256), 0, st, P);
+        hipLaunchKernelGGL((epass_strag_kernel<T, MODE_PAIR, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
     else if (mode == MODE_OPEN)
-        hipLaunchKernelGGL((epass_strag_kernel<T, MODE_OPEN, BANDS>), dim3(nb), dim3(256), 0, st, P);
+        hipLaunchKernelGGL((epass_strag_kernel<T, MODE_OPEN, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
     else
-        hipLaunchKernelGGL((epass_strag_kernel<T, MODE_CLOSE, BANDS>), dim3(nb), dim3(256), 0, st, P);
+        hipLaunchKernelGGL((epass_strag_kernel<T, MODE_CLOSE, BANDS, HASQ>), dim3(nb), dim3(256), 0, st, P);
 }
 
 template <typename T>
-hipError_t launch_epass_strag(const EParams<T> &P, int mode, hipStream_t st)
+hipError_t launch_epass_strag(const EParams<T> &P, int mode, bool factors, hipStream_t st)
 {
     if (!P.blk || !P.dA2 || !P.dB2 || P.Wh != nullptr || P.inj_c != nullptr || P.NB > 4) return hipErrorInvalidValue;
-    const unsigned nf = (unsigned)((P.NPpad + 255) / 256);
-    if (mode & MODE_CLOSE) hipLaunchKernelGGL(strag_factor_kernel<T>, dim3(nf), dim3(256), 0, st, P.blk, P.rho_c, P.h,
-                                              P.G, P.NPpad, P.sfac_c);
-    if (mode & MODE_OPEN) hipLaunchKernelGGL(strag_factor_kernel<T>, dim3(nf), dim3(256), 0, st, P.blk, P.rho_o, P.h,
-                                             P.G, P.NPpad, P.sfac_o);
+    if (factors)
+        hipLaunchKernelGGL(strag_factor_kernel<T>, dim3((unsigned)((P.NPpad + 63) / 64), mode == MODE_PAIR ? 2 : 1),
+                           dim3(64), 0, st, P, mode == MODE_OPEN ? 1 : 0);
     const unsigned nb = (unsigned)((P.NLINE / P.NAPT) * P.NOCT);
-    if (P.NB > 1)
-        launch_epass_strag_t<T, true>(P, mode, nb, st);
-    else
-        launch_epass_strag_t<T, false>(P, mode, nb, st);
+    if (P.NB > 1) {
+        if (P.Q) launch_epass_strag_t<T, true, true>(P, mode, nb, st);
+        else launch_epass_strag_t<T, true, false>(P, mode, nb, st);
+    } else {
+        if (P.Q) launch_epass_strag_t<T, false, true>(P, mode, nb, st);
+        else launch_epass_strag_t<T, false, false>(P, mode, nb, st);
+    }
     return hipGetLastError();
 }
-template hipError_t launch_epass_strag<float>(const EParams<float> &, int, hipStream_t);
-template hipError_t launch_epass_strag<double>(const EParams<double> &, int, hipStream_t);
+template hipError_t launch_epass_strag<float>(const EParams<float> &, int, bool, hipStream_t);
+template hipError_t launch_epass_strag<double>(const EParams<double> &, int, bool, hipStream_t);
 
 // Energy pass of FP32 contexts with the split-BF16 source product: one thread per (lateral cell,
 // group of PBS_EPASS_LPT consecutive angular lines of an octet a = 8 oct + e).  The thread sweeps the

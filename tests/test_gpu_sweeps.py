@@ -132,3 +132,27 @@ def test_small_source_product_and_dose(O, nx, ny, nth, ng, prec):
     print("dose", e, flush=True)
     # the oracle's deposit is a difference of energy contents, far larger than it
     assert e <= (1e-11 if prec == "fp64" else TOL[prec])
+
+
+# the straggling sweeps around their ring of two groups, with and without a source and a next generation; a whole
+# march takes every mode (open, fused pair, close) and the factors of both halves
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("ng,ngen", [(2, 1), (3, 2), (4, 3), (5, 2)])
+def test_straggling_march_around_the_group_ring(O, ng, ngen, prec):
+    from paper_2504_00340_amd import pbsplit as P
+
+    print("case straggling ring", ng, ngen, prec, flush=True)
+    c = I.small(nx=5, ny=9, nth=6, ng=ng, nz=3, ngen=ngen, e0=60.0, e_hi=70.0, depth=0.3, seed=9)
+    c["phys"] = I.paper_physics(I.MAT_BONE)
+    dref, fref = O.Oracle(c["grid"], c["phys"]).run(c["beam"], c["rho"])
+    s = P.Solver(c["grid"], c["phys"], precision=prec)
+    s.set_phantom(c["rho"])
+    s.set_beam(c["beam"])
+    s.run()
+    d, f = s.dose(), s.state()
+    s.close()
+    e = np.linalg.norm(d - dref) / np.linalg.norm(dref)
+    print("dose", e, flush=True)
+    assert e <= (1e-12 if prec == "fp64" else 1e-4)
+    for k in range(ngen):
+        assert np.abs(f[k] - fref[k]).max() <= (1e-12 if prec == "fp64" else 1e-4) * np.abs(fref[k]).max(), k
