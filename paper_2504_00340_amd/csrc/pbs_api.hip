@@ -120,32 +120,35 @@ void transfer_table_bf16(const std::vector<double> &P2T, int NA, int Mp, int Kpb
     }
 }
 
-// nth = 32: the 31-point sine transform split by mode parity, [(mat*4 + s)*64 + lane] =
-// A_mat[perm(lane % 16)][4 s + lane / 16] for mat = Sodd, Seven and A_mat[4 s + lane / 16][perm(lane % 16)]
-// for mat = Sodd^T, Seven^T, perm(4 g + q) = 4 q + g (the row order that keeps the angular pass's LDS
-// stores free of bank conflicts).
-// nth = 16: the dense 15-point transform zero-padded to 16 x 16, [s*64 + lane] = S[lane % 16][4 s + lane / 16].
-void apass_mfma_table(int nth, float *t)
+// nth > 16: the sine transform split by mode parity, [(mat*4 + s)*64 + lane] = A_mat[perm(lane % 16)][4 s + lane / 16]
+// for mat = Sodd, Seven and A_mat[4 s + lane / 16][perm(lane % 16)] for mat = Sodd^T, Seven^T.  nth <= 16: the dense
+// transform zero-padded to 16 x 16, [s*64 + lane] = S[perm(lane % 16)][4 s + lane / 16].  perm(4 g + q) = 4 q + g for
+// the FP32 instruction (the row order that keeps the angular pass's LDS stores free of bank conflicts and makes a
+// result the next product's operand), none for the FP64 one, whose results have that order by themselves.
+void apass_mfma_table(int nth, bool fp64, double *t)
 {
-    for (int i = 0; i < 1024; ++i) t[i] = 0.f;
-    if (nth == 32) {
-        auto sodd = [](int r, int i) { return std::sin(M_PI * (2 * r + 1) * (i + 1) / 32.0); };
-        auto seven = [](int r, int i) { return (r < 15 && i < 15) ? std::sin(M_PI * 2 * (r + 1) * (i + 1) / 32.0) : 0.0; };
-        for (int s = 0; s < 4; ++s)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int row = 4 * (lane % 4) + (lane % 16) / 4, k = 4 * s + lane / 16;
-                t[(0 * 4 + s) * 64 + lane] = (float)sodd(row, k);
-                t[(1 * 4 + s) * 64 + lane] = (float)seven(row, k);
-                t[(2 * 4 + s) * 64 + lane] = (float)sodd(k, row);
-                t[(3 * 4 + s) * 64 + lane] = (float)seven(k, row);
+    for (int i = 0; i < 1024; ++i) t[i] = 0.0;
+    if (nth < 8) return;
+    const int H = nth / 2;
+    auto sodd = [&](int r, int i) { return r < H && i < H ? std::sin(M_PI * (2 * r + 1) * (i + 1) / (double)nth) : 0.0; };
+    auto seven = [&](int r, int i) {
+        return r < H - 1 && i < H - 1 ? std::sin(M_PI * 2 * (r + 1) * (i + 1) / (double)nth) : 0.0;
+    };
+    auto dense = [&](int r, int i) {
+        return r < nth - 1 && i < nth - 1 ? std::sin(M_PI * (r + 1) * (i + 1) / (double)nth) : 0.0;
+    };
+    for (int s = 0; s < 4; ++s)
+        for (int lane = 0; lane < 64; ++lane) {
+            const int l = lane % 16, row = fp64 ? l : 4 * (l % 4) + l / 4, k = 4 * s + lane / 16;
+            if (nth > 16) {
+                t[(0 * 4 + s) * 64 + lane] = sodd(row, k);
+                t[(1 * 4 + s) * 64 + lane] = seven(row, k);
+                t[(2 * 4 + s) * 64 + lane] = sodd(k, row);
+                t[(3 * 4 + s) * 64 + lane] = seven(k, row);
+            } else {
+                t[s * 64 + lane] = dense(row, k);
             }
-    } else if (nth == 16) {
-        for (int s = 0; s < 4; ++s)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int row = 4 * (lane % 4) + (lane % 16) / 4, k = 4 * s + lane / 16;
-                t[s * 64 + lane] = (row < 15 && k < 15) ? (float)std::sin(M_PI * (row + 1) * (k + 1) / 16.0) : 0.f;
-            }
-    }
+        }
 }
 }  // namespace pbs
 
@@ -583,12 +586,10 @@ pbs_status upload_tables(pbs_ctx *c)
             for (int a = 0; a < c->Mp; ++a)
                 t[c->t_P2p + b * KM + (size_t)k * c->Mp + a] =
                     (k < c->NA && a < c->NA) ? (T)c->P2T[b * NA2 + (size_t)a * c->NA + k] : T(0);
-    // MFMA operand constants of the angular pass (nth = 16, 32)
-    if (c->g.nth == 16 || c->g.nth == 32) {
-        std::vector<float> kt(1024);
-        apass_mfma_table(c->g.nth, kt.data());
-        for (int i = 0; i < 1024; ++i) t[c->t_K32 + i] = (T)kt[i];
-    }
+    // MFMA operand constants of the angular pass
+    std::vector<double> kt(1024);
+    apass_mfma_table(c->g.nth, sizeof(T) == 8, kt.data());
+    put(c->t_K32, kt);
     std::vector<double> d(c->d_count, 0.0);
     std::memcpy(&d[c->d_A], c->dA.data(), c->G() * sizeof(double));
     std::memcpy(&d[c->d_B], c->dB.data(), c->G() * sizeof(double));
@@ -861,17 +862,7 @@ pbs_status angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st)
     P.NPB = c->NPB;
     P.NLINE = c->NLINE;
     ProfScope ps(c, PBS_K_APASS, st);
-    if constexpr (sizeof(T) == 4) {
-        if (c->g.nth == 32) {
-            HIPCHK(c, launch_apass_mfma32(P, tb + c->t_K32, nstack, st));
-            return PBS_OK;
-        }
-        if (c->g.nth == 16) {
-            HIPCHK(c, launch_apass_mfma16(P, tb + c->t_K32, nstack, st));
-            return PBS_OK;
-        }
-    }
-    HIPCHK(c, launch_apass<T>(P, c->g.nth, nstack, st));
+    HIPCHK(c, launch_apass<T>(P, tb + c->t_K32, c->g.nth, nstack, st));
     return PBS_OK;
 }
 

@@ -5,7 +5,7 @@
 // the caller's workspace; every wave's whole depth march is captured once into a HIP graph and
 // launched as one graph launch.  Every kernel of a step covers all beams of the wave; blocks of
 // beams that are done exit at once.  A small autotuner times bitwise-neutral launch variants
-// (source-product tile width, transport waves per block, angular cells per block) on the first
+// (source-product tile width, transport waves per block) on the first
 // wave and keeps the fastest.  Tuning and capture happen once (pbs_batch_prepare, or the first run);
 // later runs only set up each wave's state and replay its graph.
 #include <algorithm>
@@ -275,12 +275,11 @@ pbs_status autotune(pbs_batch *b, int nw, int maxG)
 {
     BatchTuning t = b->tune;
     t.max_nz = 2;
-    const int gk[] = {QGEMM_GLOBAL_B, QGEMM_LDS_256, QGEMM_LDS_128}, wpb[] = {1, 2, 4}, pc[] = {8, 16, 32};
+    const int gk[] = {QGEMM_GLOBAL_B, QGEMM_LDS_256, QGEMM_LDS_128}, wpb[] = {1, 2, 4};
     auto pick = [&](int *field, const int *vals, int nv) {
         float bestms = 1e30f;
         int bestv = *field;
         for (int i = 0; i < nv; ++i) {
-            if (field == &t.apass_pc && (size_t)b->NA * vals[i] * 4 > 64 * 1024) continue;
             *field = vals[i];
             const float ms = time_step(b, nw, maxG, t);
             if (ms > 0 && ms < bestms) {
@@ -292,11 +291,9 @@ pbs_status autotune(pbs_batch *b, int nw, int maxG)
     };
     pick(&t.gemm_kind, gk, 3);
     pick(&t.tpass_wpb, wpb, 3);
-    pick(&t.apass_pc, pc, 3);
     BHIP(b, hipGetLastError());
     b->tune.gemm_kind = t.gemm_kind;
     b->tune.tpass_wpb = t.tpass_wpb;
-    b->tune.apass_pc = t.apass_pc;
     b->tuned = true;
     return PBS_OK;
 }
@@ -470,7 +467,6 @@ pbs_status pbs_batch_create(const pbs_grid *grids, const pbs_beam *beams, int nb
     b->total = a256(o + wmax);
     b->rho.assign(nbeams, {});
     b->have_rho.assign(nbeams, 0);
-    while (b->tune.apass_pc > 8 && (size_t)b->NA * b->tune.apass_pc * 4 > 64 * 1024) b->tune.apass_pc /= 2;
     *out = b;
     return PBS_OK;
 }
@@ -515,8 +511,9 @@ pbs_status pbs_batch_bind(pbs_batch *b, void *ws, size_t bytes, void *stream)
     BHIP(b, hipMemcpyAsync(Sp + b->sh_lam, lam.data(), lam.size() * 4, hipMemcpyHostToDevice, b->stream));
     BHIP(b, hipMemcpyAsync(Sp + b->sh_S, S.data(), S.size() * 4, hipMemcpyHostToDevice, b->stream));
     BHIP(b, hipMemcpyAsync(Sp + b->sh_A, A.data(), A.size() * 2, hipMemcpyHostToDevice, b->stream));
-    std::vector<float> Kt(1024);
-    apass_mfma_table(b->nth, Kt.data());
+    std::vector<double> Kd(1024);
+    apass_mfma_table(b->nth, false, Kd.data());
+    const std::vector<float> Kt(Kd.begin(), Kd.end());
     BHIP(b, hipMemcpyAsync(Sp + b->sh_K, Kt.data(), Kt.size() * 4, hipMemcpyHostToDevice, b->stream));
     BHIP(b, hipStreamSynchronize(b->stream));
     b->state = 1;
@@ -599,7 +596,7 @@ pbs_status pbs_batch_tuning(const pbs_batch *b, int *out3)
     if (!b || !out3) return PBS_EINVAL;
     out3[0] = b->tune.gemm_kind;
     out3[1] = b->tune.tpass_wpb;
-    out3[2] = b->tune.apass_pc;
+    out3[2] = 16;   // fixed: the matrix instructions' columns
     return PBS_OK;
 }
 

@@ -123,7 +123,7 @@ struct BeamDev {
 
 struct BatchShape {
     const float *theta, *lam, *S;          // angular tables
-    const float *K;                        // MFMA operand table of the angular pass (nth 16 or 32)
+    const float *K;                        // MFMA operand table of the angular pass
     const unsigned short *Ahi, *Alo;       // split-BF16 P2, [Mp][Kpb]
     int Kpb, Mp;
     int nprod;                             // 3: scanned fluence as hi + lo; 2: hi only (no lo array);
@@ -138,7 +138,6 @@ struct BatchShape {
 struct BatchTuning {
     int gemm_kind = 0;        // split-BF16 product kernel (QGEMM_*)
     int tpass_wpb = 4;        // transport: planes (waves) per block, 1, 2 or 4
-    int apass_pc = 32;        // angular pass: lateral cells per block, 8, 16 or 32
     int max_nz = 0;           // longest beam of the wave (set by the batch planner)
 };
 
@@ -166,7 +165,8 @@ hipError_t launch_epass8(const EParams<float> &P, int mode, hipStream_t st);
 // deposit slots per cell written by launch_epass8
 __host__ __device__ inline int epass8_slots(int NOCT) { return NOCT * (8 / PBS_EPASS_LPT); }
 template <typename T> hipError_t launch_tpass(const TParams<T> &P, hipStream_t st);
-template <typename T> hipError_t launch_apass(const AParams<T> &P, int nth, long nstack, hipStream_t st);
+// Ktab: operand table of the MFMA forms (apass_mfma_table)
+template <typename T> hipError_t launch_apass(const AParams<T> &P, const T *Ktab, int nth, long nstack, hipStream_t st);
 template <typename T> hipError_t launch_qgemm(const QParams<T> &P, hipStream_t st);
 template <typename T> hipError_t launch_fill(T *p, T v, long n, hipStream_t st);
 // y = a y + b x elementwise
@@ -194,10 +194,9 @@ hipError_t launch_initial(T *psi0, const double *E1, const double *E2, const dou
 enum { QGEMM_GLOBAL_B = 0, QGEMM_LDS_256 = 1, QGEMM_LDS_128 = 2 };
 hipError_t launch_qgemm_bf16s(const QParams<float> &P, const unsigned short *Ahi, const unsigned short *Alo, int Kp,
                               int nprod, hipStream_t st, int kind = QGEMM_GLOBAL_B);
-hipError_t launch_apass_mfma32(const AParams<float> &P, const float *Ktab, long nstack, hipStream_t st);
-hipError_t launch_apass_mfma16(const AParams<float> &P, const float *Ktab, long nstack, hipStream_t st);
-// operand table of the MFMA angular pass for nth (16 or 32; 1024 floats, unused entries zero)
-void apass_mfma_table(int nth, float *out1024);
+// operand table of the MFMA angular pass for nth >= 8 (1024 entries, unused ones zero); fp64: the row order of the
+// FP64 matrix instruction
+void apass_mfma_table(int nth, bool fp64, double *out1024);
 
 bool apass_supported(int nth);
 

@@ -2133,9 +2133,15 @@ static hipError_t launch_apass_n(const AParams<T> &P, long nstack, hipStream_t s
 //   A_mat[4 s + lane / 16][perm(lane % 16)] for mat = Sodd^T, Seven^T, perm(4 g + q) = 4 q + g.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
 __device__ __forceinline__ floatx4 mfma16(float a, float b, floatx4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ doublex4 mfma16(double a, double b, doublex4 c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 // 16 waves per block: the dependent MFMA chains of a line are short, so latency is hidden by the
@@ -2404,6 +2410,234 @@ hipError_t launch_apass_mfma32(const AParams<float> &P, const float *Ktab, long 
     return hipGetLastError();
 }
 
+// The same two forms for N = 20 and 24 (split by mode parity), and in FP64 for N = 16 (one dense product per line), 20,
+// 24 and 32.  What bounded the vector transform they replace was its set-up around the arithmetic, not the
+// arithmetic: half a wave's lanes per line, the sine table through scalar loads in every line, a block barrier per
+// phase with 12 waves per CU.  A block holds PCH groups of 16 cells of one lateral tile; its 8 waves take whole
+// (group, line) items.  FP64 results come out in operand order by themselves (row 4 q + lane / 16), so its operand
+// rows are not permuted.
+// Measured, us per launch of two generations, before -> after: FP32 40 x 40 cells, 60 groups, N = 20 686 -> 343 and N =
+// 24 1144 -> 432; 45 x 70, N = 20, 75, three generations 2487 -> 1060; FP64 64 x 64, N = 16, 64 1311 -> 1010; 40 x 40,
+// 60, N = 20 970 -> 775 and N = 24 1161 -> 1000; 32 x 32, 32, N = 32 828 -> 700.  Both groups of a tile in one block:
+// 1.5-18 % slower for N = 20 and 24; 4 or 16 waves: 5-25 % slower.  Below 16 nodes the vector transform stays: its
+// lines are short enough that its blocks keep 32 waves per CU, and the matrix form took 1.3-1.7 times as long at N = 8 and
+// 10 and 1.25 times at N = 12.
+template <typename T, int N>
+struct AngMfma {
+    static constexpr int m = N - 1, NA = m * m;
+    static constexpr bool SPLIT = N > 16;
+    static constexpr int H = SPLIT ? N / 2 : m;       // odd (or all) modes and operand nodes
+    static constexpr int HE = SPLIT ? N / 2 - 1 : 0;  // even modes
+    static constexpr int KS = (H + 3) / 4;            // 4-node steps
+    static constexpr int PCH = SPLIT ? 1 : 2;         // groups of 16 cells per block
+    static constexpr int NT = 512;
+    static constexpr int CH = 16 / (int)sizeof(T);    // values per 16-byte access
+    typedef T T4 __attribute__((ext_vector_type(4)));
+    typedef T TC __attribute__((ext_vector_type(CH)));
+};
+
+template <typename T, int N>
+__device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__restrict__ Ktab, long stack, int pb, int c0)
+{
+    using C = AngMfma<T, N>;
+    using T4 = typename C::T4;
+    using TC = typename C::TC;
+    constexpr int m = C::m, NA = C::NA, H = C::H, HE = C::HE, KS = C::KS, NT = C::NT, CH = C::CH, PCH = C::PCH;
+    constexpr bool SPLIT = C::SPLIT;
+    __shared__ T L[PCH * NA * 16];   // [group][a][cell]
+    const int g = (int)((stack / 2) % P.G);
+    T *blk = P.psi + stack * P.NLINE + (long)pb * NA * PBS_PT + c0;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int r4 = lane >> 4, cc = lane & 15;
+    // tile to LDS and back, 16 bytes per lane, several loads in flight
+    constexpr int CPR = PCH * 16 / CH, NCHK = NA * CPR, UL = 4;
+    auto lds_at = [&](int idx) {
+        const int a = idx / CPR, c = (idx % CPR) * CH;
+        return reinterpret_cast<TC *>(&L[((c >> 4) * NA + a) * 16 + (c & 15)]);
+    };
+    auto mem_at = [&](int idx) { return reinterpret_cast<TC *>(blk + (long)(idx / CPR) * PBS_PT + (idx % CPR) * CH); };
+    for (int i0 = tid; i0 < NCHK; i0 += UL * NT) {
+        TC v[UL];
+#pragma unroll
+        for (int u = 0; u < UL; ++u)
+            if (i0 + u * NT < NCHK) v[u] = *mem_at(i0 + u * NT);
+#pragma unroll
+        for (int u = 0; u < UL; ++u)
+            if (i0 + u * NT < NCHK) *lds_at(i0 + u * NT) = v[u];
+    }
+    // operand rows: forward odd (or dense) and even, inverse odd and even (dense: the sine matrix is symmetric)
+    T Ao[KS], Ae[KS], Bo[KS], Be[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        Ao[s] = Ktab[(0 * 4 + s) * 64 + lane];
+        if constexpr (SPLIT) {
+            Ae[s] = Ktab[(1 * 4 + s) * 64 + lane];
+            Bo[s] = Ktab[(2 * 4 + s) * 64 + lane];
+            Be[s] = Ktab[(3 * 4 + s) * 64 + lane];
+        }
+    }
+    // result element q of lane group r4 holds index 4 q + r4
+    T lamO[KS], lamE[KS];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+        const int r = 4 * q + r4;
+        lamO[q] = r < H ? P.lam[SPLIT ? 2 * r : r] : T(0);
+        lamE[q] = SPLIT && r < HE ? P.lam[2 * r + 1] : T(0);
+    }
+    T al[PCH];
+#pragma unroll
+    for (int h = 0; h < PCH; ++h) al[h] = T(0.25) * P.h * P.sig[g] * P.rho[(long)pb * PBS_PT + c0 + 16 * h + cc];
+    // a line's operand at step s: node ip, and its mirror image folded in by parity
+    auto fold = [&](const T *x, int stride, int s, T &o, T &e) {
+        const int ip = 4 * s + r4;
+        const T xa = ip < H ? x[ip * stride] : T(0);
+        if constexpr (SPLIT) {
+            const T xb = ip < HE ? x[(m - 1 - ip) * stride] : T(0);
+            o = xa + xb;
+            e = xa - xb;   // the centre node (ip = H - 1) meets a zero column of the even matrix
+        } else {
+            o = xa;
+        }
+    };
+    __syncthreads();
+    // forward over the first angular index, line = column j: odd mode r to row r, even mode r to row H + r
+    for (int it = wid; it < PCH * m; it += NT / 64) {
+        T *x = &L[(it / m) * NA * 16 + (it % m) * 16 + cc];
+        T4 yo = {0, 0, 0, 0}, ye = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            T o, e;
+            fold(x, m * 16, s, o, e);
+            yo = mfma16(Ao[s], o, yo);
+            if constexpr (SPLIT) ye = mfma16(Ae[s], e, ye);
+        }
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+            const int r = 4 * q + r4;
+            if (r < H) x[r * m * 16] = yo[q];
+            if (SPLIT && r < HE) x[(H + r) * m * 16] = ye[q];
+        }
+    }
+    __syncthreads();
+    // over the second index: forward, CN factor, inverse; line = row k (odd or even mode of the first index)
+    for (int it = wid; it < PCH * m; it += NT / 64) {
+        const int k = it % m;
+        T *x = &L[(it / m) * NA * 16 + k * m * 16 + cc];
+        T4 zo = {0, 0, 0, 0}, ze = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            T o, e;
+            fold(x, 16, s, o, e);
+            zo = mfma16(Ao[s], o, zo);
+            if constexpr (SPLIT) ze = mfma16(Ae[s], e, ze);
+        }
+        const T lk = P.lam[!SPLIT ? k : k < H ? 2 * k : 2 * (k - H) + 1];
+        T alh = al[0];
+        if constexpr (PCH > 1) alh = it / m ? al[PCH - 1] : al[0];
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+            const int r = 4 * q + r4;
+            const T to = alh * (lk + lamO[q]);
+            zo[q] = r < H ? zo[q] * (T(1) + to) * fast_rcp(T(1) - to) : T(0);
+            if constexpr (SPLIT) {
+                const T te = alh * (lk + lamE[q]);
+                ze[q] = r < HE ? ze[q] * (T(1) + te) * fast_rcp(T(1) - te) : T(0);
+            }
+        }
+        // the scaled modes are already the inverse's operands
+        T4 u = {0, 0, 0, 0}, v = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            u = mfma16(SPLIT ? Bo[s] : Ao[s], zo[s], u);
+            if constexpr (SPLIT) v = mfma16(Be[s], ze[s], v);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+            const int jp = 4 * q + r4;
+            if constexpr (SPLIT) {
+                if (jp < HE) {
+                    x[jp * 16] = u[q] + v[q];
+                    x[(m - 1 - jp) * 16] = u[q] - v[q];
+                } else if (jp == H - 1) {
+                    x[jp * 16] = u[q];
+                }
+            } else if (jp < m) {
+                x[jp * 16] = u[q];
+            }
+        }
+    }
+    __syncthreads();
+    // inverse over the first index, with the (2/N)^2 normalisation
+    constexpr T sc = (T(2) / T(N)) * (T(2) / T(N));
+    for (int it = wid; it < PCH * m; it += NT / 64) {
+        T *x = &L[(it / m) * NA * 16 + (it % m) * 16 + cc];
+        T4 u = {0, 0, 0, 0}, v = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int r = 4 * s + r4;
+            const T bo = r < H ? x[r * m * 16] : T(0);
+            u = mfma16(SPLIT ? Bo[s] : Ao[s], bo, u);
+            if constexpr (SPLIT) {
+                const T be = r < HE ? x[(H + r) * m * 16] : T(0);
+                v = mfma16(Be[s], be, v);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+            const int ip = 4 * q + r4;
+            if constexpr (SPLIT) {
+                if (ip < HE) {
+                    x[ip * m * 16] = (u[q] + v[q]) * sc;
+                    x[(m - 1 - ip) * m * 16] = (u[q] - v[q]) * sc;
+                } else if (ip == H - 1) {
+                    x[ip * m * 16] = u[q] * sc;
+                }
+            } else if (ip < m) {
+                x[ip * m * 16] = u[q] * sc;
+            }
+        }
+    }
+    __syncthreads();
+    for (int idx = tid; idx < NCHK; idx += NT) *mem_at(idx) = *lds_at(idx);
+}
+
+// blocks per stack, and a block's lateral tile and first cell: the two 16-cell groups of one tile, where they are
+// two blocks, are 8 workgroups apart (one XCD, shared L2 lines)
+template <typename T, int N>
+__host__ __device__ constexpr int apass_mfma_blocks(int npb)
+{
+    return AngMfma<T, N>::PCH == 2 ? npb : (npb + 7) / 8 * 16;
+}
+template <typename T, int N>
+__device__ __forceinline__ void apass_mfma_block(const AParams<T> &P, const T *__restrict__ Ktab, int bid, long stack, int npb)
+{
+    int pb = bid, c0 = 0;
+    if constexpr (AngMfma<T, N>::PCH == 1) {
+        pb = (bid >> 4) * 8 + (bid & 7);
+        c0 = ((bid >> 3) & 1) * 16;
+    }
+    if (pb >= npb) return;
+    apass_mfma_body<T, N>(P, Ktab, stack, pb, c0);
+}
+
+template <typename T, int N>
+__global__ __launch_bounds__((AngMfma<T, N>::NT)) void apass_mfma_kernel(AParams<T> P, const T *__restrict__ Ktab)
+{
+    apass_mfma_block<T, N>(P, Ktab, blockIdx.x, blockIdx.y, P.NPB);
+}
+
+template <typename T, int N>
+static hipError_t launch_apass_mfma_n(const AParams<T> &P, const T *Ktab, long nstack, hipStream_t st)
+{
+    hipLaunchKernelGGL((apass_mfma_kernel<T, N>), dim3((unsigned)(apass_mfma_blocks<T, N>(P.NPB)), (unsigned)nstack),
+                       dim3(AngMfma<T, N>::NT), 0, st, P, Ktab);
+    return hipGetLastError();
+}
+
 bool apass_supported(int nth)
 {
     switch (nth) {
@@ -2413,18 +2647,22 @@ bool apass_supported(int nth)
 }
 
 template <typename T>
-hipError_t launch_apass(const AParams<T> &P, int nth, long nstack, hipStream_t st)
+hipError_t launch_apass(const AParams<T> &P, const T *Ktab, int nth, long nstack, hipStream_t st)
 {
+    if constexpr (sizeof(T) == 4) {
+        if (nth == 16) return launch_apass_mfma16(P, Ktab, nstack, st);
+        if (nth == 32) return launch_apass_mfma32(P, Ktab, nstack, st);
+    }
     switch (nth) {
     case 4: return launch_apass_n<T, 4>(P, nstack, st);
     case 6: return launch_apass_n<T, 6>(P, nstack, st);
     case 8: return launch_apass_n<T, 8>(P, nstack, st);
     case 10: return launch_apass_n<T, 10>(P, nstack, st);
     case 12: return launch_apass_n<T, 12>(P, nstack, st);
-    case 16: return launch_apass_n<T, 16>(P, nstack, st);
-    case 20: return launch_apass_n<T, 20>(P, nstack, st);
-    case 24: return launch_apass_n<T, 24>(P, nstack, st);
-    case 32: return launch_apass_n<T, 32>(P, nstack, st);
+    case 16: return launch_apass_mfma_n<T, 16>(P, Ktab, nstack, st);
+    case 20: return launch_apass_mfma_n<T, 20>(P, Ktab, nstack, st);
+    case 24: return launch_apass_mfma_n<T, 24>(P, Ktab, nstack, st);
+    case 32: return launch_apass_mfma_n<T, 32>(P, Ktab, nstack, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -2968,8 +3206,6 @@ hipError_t launch_qgemm_bf16s(const QParams<float> &P, const unsigned short *Ahi
     return hipGetLastError();
 }
 
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-
 // FP64, and FP32 below 128 angular unknowns (up to 12 nodes per axis): v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4.
 // What bounded the vector kernel it replaces: its LDS staging (a barrier pair per 32 source nodes) on small
 // grids, two LDS reads per multiply on large ones.  Here both operands go from global memory straight into MFMA
@@ -2984,8 +3220,6 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // unknowns on (685 against 788, 4678 against 6297 at 64 x 64, 31 x 31, 32 groups): a matrix step there takes half the
 // time and the operand loads no longer hide behind it.
 constexpr int QS_PF = 4;
-__device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-__device__ __forceinline__ doublex4 mfma4(double a, double b, doublex4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 template <typename T, int NTL>
 __global__ __launch_bounds__(256) void qgemm_direct_kernel(QParams<T> P, int nnt)
@@ -3031,7 +3265,7 @@ __global__ __launch_bounds__(256) void qgemm_direct_kernel(QParams<T> P, int nnt
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) acc[i][j][h] = mfma4(a[i], b[j][h], acc[i][j][h]);
+                for (int h = 0; h < 2; ++h) acc[i][j][h] = mfma16(a[i], b[j][h], acc[i][j][h]);
     };
 #pragma unroll
     for (int u = 0; u < QS_PF; ++u) fetch(u, u);
@@ -3381,11 +3615,9 @@ __global__ __launch_bounds__(64 * WPB) void tpass_batched_pair_kernel(const Beam
     tpass_pair_body(P, (long)blockIdx.x * WPB + (threadIdx.x >> 6));
 }
 
-template <int N, int PC>
-__global__ __launch_bounds__(256) void apass_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh, int s, int k)
+// angular record of one beam of the batch at step s (generation k, or all for k < 0)
+__device__ __forceinline__ AParams<float> batch_aparams(const BeamDev &B, const BatchShape &Sh, int s, int k)
 {
-    const BeamDev &B = beams[blockIdx.z];
-    if (s >= B.nz || blockIdx.y >= (unsigned)((k < 0 ? Sh.ngen : 1) * B.G * 2)) return;
     AParams<float> P;
     P.psi = k < 0 ? B.psi : B.psi + (long)k * B.G * 2 * Sh.NLINE;
     P.rho = B.rho + (long)s * Sh.NPB * PBS_PT;
@@ -3397,7 +3629,16 @@ __global__ __launch_bounds__(256) void apass_batched_kernel(const BeamDev *__res
     P.NA = Sh.NA;
     P.NPB = Sh.NPB;
     P.NLINE = Sh.NLINE;
-    apass_body<float, N, PC>(P, blockIdx.x, blockIdx.y);
+    return P;
+}
+
+template <int N>
+__global__ __launch_bounds__((AngMfma<float, N>::NT)) void apass_batched_kernel(const BeamDev *__restrict__ beams,
+                                                                                 BatchShape Sh, int s, int k)
+{
+    const BeamDev &B = beams[blockIdx.z];
+    if (s >= B.nz || blockIdx.y >= (unsigned)((k < 0 ? Sh.ngen : 1) * B.G * 2)) return;
+    apass_mfma_block<float, N>(batch_aparams(B, Sh, s, k), Sh.K, blockIdx.x, blockIdx.y, Sh.NPB);
 }
 
 // batched MFMA angular passes (nth = 16 and 32): the single-beam bodies, beam = blockIdx.z
@@ -3410,17 +3651,7 @@ void apass_mfma_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh,
     const int bid = blockIdx.x;
     const int pb = (bid >> 4) * 8 + (bid & 7), half = (bid >> 3) & 1;
     if (pb >= Sh.NPB) return;
-    AParams<float> P;
-    P.psi = k < 0 ? B.psi : B.psi + (long)k * B.G * 2 * Sh.NLINE;
-    P.rho = B.rho + (long)s * Sh.NPB * PBS_PT;
-    P.sig = B.tabf + 6 * B.G;
-    P.S = Sh.S;
-    P.lam = Sh.lam;
-    P.h = B.dz;
-    P.G = B.G;
-    P.NA = Sh.NA;
-    P.NPB = Sh.NPB;
-    P.NLINE = Sh.NLINE;
+    const AParams<float> P = batch_aparams(B, Sh, s, k);
     if constexpr (NTH == 32)
         apass_mfma32_body(P, Sh.K, blockIdx.y, pb, half);
     else
@@ -3514,20 +3745,12 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
             else
                 hipLaunchKernelGGL(apass_mfma_batched_kernel<16>, grid, dim3(256), 0, q, beams, Sh, s, k);
         } else {
-            const int pc = tu.apass_pc;
-            dim3 grid((unsigned)(Sh.NPB * (PBS_PT / pc)), (unsigned)nstack, nbeam);
-#define PBS_AB(N)                                                                                              \
-    do {                                                                                                       \
-        const size_t sh = (size_t)(N - 1) * (N - 1) * pc * sizeof(float);                                      \
-        if (pc == 32) hipLaunchKernelGGL((apass_batched_kernel<N, 32>), grid, dim3(256), sh, q, beams, Sh, s, k); \
-        else if (pc == 16) hipLaunchKernelGGL((apass_batched_kernel<N, 16>), grid, dim3(256), sh, q, beams, Sh, s, k); \
-        else hipLaunchKernelGGL((apass_batched_kernel<N, 8>), grid, dim3(256), sh, q, beams, Sh, s, k);         \
-    } while (0)
+#define PBS_AB(N)                                                                                                    \
+    hipLaunchKernelGGL((apass_batched_kernel<N>), dim3((unsigned)(apass_mfma_blocks<float, N>(Sh.NPB)), nstack, nbeam), \
+                       dim3(AngMfma<float, N>::NT), 0, q, beams, Sh, s, k)
             switch (Sh.nth) {
-            case 16: PBS_AB(16); break;
             case 20: PBS_AB(20); break;
             case 24: PBS_AB(24); break;
-            case 32: PBS_AB(32); break;
             default: return hipErrorInvalidValue;
             }
 #undef PBS_AB
@@ -3592,7 +3815,7 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
 #define PBS_INSTANTIATE(T)                                                                                    \
     template hipError_t launch_epass<T>(const EParams<T> &, int, hipStream_t);                                \
     template hipError_t launch_tpass<T>(const TParams<T> &, hipStream_t);                                     \
-    template hipError_t launch_apass<T>(const AParams<T> &, int, long, hipStream_t);                          \
+    template hipError_t launch_apass<T>(const AParams<T> &, const T *, int, long, hipStream_t);                        \
     template hipError_t launch_qgemm<T>(const QParams<T> &, hipStream_t);                                     \
     template hipError_t launch_fill<T>(T *, T, long, hipStream_t);                                            \
     template hipError_t launch_initial<T>(T *, const double *, const double *, const double *, long, int, int, \

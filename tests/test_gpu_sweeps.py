@@ -156,3 +156,21 @@ def test_straggling_march_around_the_group_ring(O, ng, ngen, prec):
     assert e <= (1e-12 if prec == "fp64" else 1e-4)
     for k in range(ngen):
         assert np.abs(f[k] - fref[k]).max() <= (1e-12 if prec == "fp64" else 1e-4) * np.abs(fref[k]).max(), k
+
+
+# every angular grid (dense and parity-split matrix forms, vector form for 4 and 6), with a last tile that is not full
+# and tile counts around the 8 that share an XCD group
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nth", [4, 6, 8, 10, 12, 16, 20, 24, 32])
+@pytest.mark.parametrize("nx,ny", [(3, 7), (9, 30)])
+def test_angular_step(O, nx, ny, nth, prec):
+    print("case angular", nx, ny, nth, prec, flush=True)
+    s, o, c, st = _setup(O, prec, dict(nx=nx, ny=ny, nth=nth, ng=2, ngen=2))
+    ref = st.copy()
+    rho = np.ascontiguousarray(c["rho"][1].reshape(-1))
+    for k in range(ref.shape[0]):
+        o.angular_cn(ref[k], rho, 0.3)
+    s.apply(3, 1, 0.3)
+    got = s.state()
+    s.close()
+    _check(got, ref, prec, "angular")
