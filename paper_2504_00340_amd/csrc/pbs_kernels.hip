@@ -34,7 +34,29 @@ __device__ __forceinline__ T tab(const T *p, long i)
     return ((const __attribute__((address_space(4))) T *)p)[i];
 }
 
+// v of lane l (uniform)
+template <typename T>
+__device__ __forceinline__ T lane_of(T v, int l)
+{
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+    } else {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, l);
+        const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
+        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+    }
+}
+
 // ------------------------------------------------------------------------------- energy pass
+// The pipeline form of the smallest grids (defined below) and the blocks of 64 threads up to which they take it: about
+// three blocks per CU, what its LDS lets run at once.  With one line per thread it still wins at 784 blocks (32 x 32 cells,
+// 7 x 7 angles 36 -> 29 us) and loses at 1687 (20 x 24, 15 x 15, FP64 60 -> 82); with four at 605 (12 x 12, 31 x 31 104 -> 89
+// us) and loses at 928 (32 x 32, 15 x 15 150 -> 200).
+constexpr long EP_PIPE_BLOCKS = 800;
+template <typename T, int L> static long epass_pipe_blocks(const EParams<T> &P);
+template <typename T, int L> static hipError_t launch_epass_pipe(const EParams<T> &P, int mode, hipStream_t st);
+
 // One thread per line (FP64 contexts, and FP32 contexts whose source product takes the plain scan W):
 // block = one lateral tile pb and one octet of angular lines a = 8*oct + e (e = tid/32), 32 cells
 // pt = tid%32.  FP32 contexts with the split-BF16 product use epass8_body below.
@@ -217,6 +239,7 @@ hipError_t launch_epass(const EParams<T> &P, int mode, hipStream_t st)
 {
     if (P.Wh != nullptr) return hipErrorInvalidValue;   // split scans: launch_epass8
     if (P.NB > 4) return hipErrorInvalidValue;
+    if (P.inj_c == nullptr && epass_pipe_blocks<T, 1>(P) <= EP_PIPE_BLOCKS) return launch_epass_pipe<T, 1>(P, mode, st);
     const unsigned nb = (unsigned)((P.NLINE / P.NAPT) * P.NOCT);
     if (P.NB > 1) {
         if (P.Q) launch_epass_t<T, true, true>(P, mode, nb, st);
@@ -823,6 +846,9 @@ hipError_t launch_epass8(const EParams<float> &P, int mode, hipStream_t st)
     const unsigned nb = (unsigned)((nthreads + 255) / 256);
     if (P.NB > 4) return hipErrorInvalidValue;
     if (P.NB > 1 && P.inj_c != nullptr) return hipErrorInvalidValue;   // banded nuclear data: no surrogate records
+    if (P.inj_c == nullptr && P.Wl == nullptr && (P.Q == nullptr || P.Qb != nullptr) &&
+        epass_pipe_blocks<float, 4>(P) <= EP_PIPE_BLOCKS)
+        return launch_epass_pipe<float, 4>(P, mode, st);
     if (nthreads / 64 <= EP8_RING_WAVES && P.Wl == nullptr && (P.Q == nullptr || P.Qb != nullptr)) {
         const bool q = P.Q != nullptr;
         if (P.NB > 1) {
@@ -848,6 +874,372 @@ hipError_t launch_epass8(const EParams<float> &P, int mode, hipStream_t st)
         launch_epass8_t<false, true>(P, mode, nb, st);
     else
         launch_epass8_t<false, false>(P, mode, nb, st);
+    return hipGetLastError();
+}
+
+// ----------------------------------------------------------------- energy pass as a pipeline of waves
+// The smallest grids hold fewer line groups than the chip has SIMDs, and a wave's own instruction stream is what
+// bounds the sweep there (about 120 vector instructions a group for one line, 370 for four).  A block therefore
+// runs the sweep of 64 threads as four waves, each with a quarter of the work, two to four groups (a chunk) behind
+// the one before it, handing values on through LDS:
+//   0  loads the fluence and the closing source, solves the closing half-step
+//   1  loads the opening source, solves the opening half-step, stores the fluence
+//   2  scans the three states for the next generation's source
+//   3  sums the FP64 deposits
+// The arithmetic of a line is that of the passes above (for four lines per thread bit for bit).  One barrier per
+// chunk, which waits for LDS only: loads and stores stay in flight across it.  Three chunk buffers: one being
+// written by each of waves 0 and 1, one being read by 2 and 3.
+// Measured, us per launch, before -> after: 4 x 4 cells, 11 x 11 angles, 60 groups 27 -> 19 (FP64 31 -> 22); 16 x 16, 7 x 7, 48
+// 24 -> 18 (FP64 26 -> 20); 6 x 6, 15 x 15, 60 59 -> 37; 16 x 16, 15 x 15, 131 125 -> 74; 24 x 24, 15 x 15, 131 133 -> 105.
+template <typename T, int L>
+struct EPipe {
+    static constexpr int C = L == 1 ? 4 : 2;   // groups per chunk
+    static constexpr int PF = 2;               // chunks loaded ahead
+    typedef T V __attribute__((ext_vector_type(L)));
+    struct Group { V x1[64], x2[64], y1[64], y2[64], z1[64], z2[64], qc[64], qo[64]; };
+};
+
+__device__ __forceinline__ void epipe_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Three per-group tables of a chunk's C groups in the lanes of one vector load, read back by lane: scalar loads share
+// their counter with LDS, whose every wait would then wait for them.
+template <typename X, int C>
+struct EPipeTab {
+    const X *p;
+    int top;
+    X v;
+    __device__ __forceinline__ EPipeTab(const X *a, const X *b, const X *c, int G, int lane)
+        : p(lane < C ? a : lane < 2 * C ? b : c), top(G - 1 - lane % C), v(X(0))
+    {
+    }
+    __device__ __forceinline__ void fetch(int n) { v = p[max(top - n * C, 0)]; }
+};
+
+// 2 x 2 CN solve of one group for one line: coefficients of the cell's half-step a
+template <typename T>
+struct ECoef {
+    T d11, d12, d21, d22, c1, c2, m11, m12, m21, m22, inv, a;
+    __device__ __forceinline__ void set(T sm, T sp, T kp, T a_)
+    {
+#pragma clang fp contract(off)
+        a = a_;
+        d11 = -(sm + kp), d12 = sm, d21 = T(-3) * sp, d22 = -(fma(T(2), sm, sp) + kp);
+        c1 = sp, c2 = T(3) * sp;
+        m11 = fma(-a, d11, T(1)), m12 = -a * d12, m21 = -a * d21, m22 = fma(-a, d22, T(1));
+        inv = fast_rcp(fma(m11, m22, -(m12 * m21)));
+    }
+    __device__ __forceinline__ void solve(T x1, T x2, T f, T q, T &y1, T &y2) const
+    {
+#pragma clang fp contract(off)
+        const T r1 = fma(a, fma(c1, f, fma(d12, x2, d11 * x1)) + q, x1);
+        const T r2 = fma(a, fma(c2, f, fma(d21, x1, d22 * x2)), x2);
+        y1 = fma(r1, m22, -(m12 * r2)) * inv;
+        y2 = fma(m11, r2, -(m21 * r1)) * inv;
+    }
+};
+
+template <typename T, int L, int MODE, bool BANDS, bool HASQ>
+__global__ __launch_bounds__(256) void epass_pipe_kernel(EParams<T> P)
+{
+    using E = EPipe<T, L>;
+    using V = typename E::V;
+    constexpr int C = E::C, PF = E::PF;
+    constexpr bool CL = (MODE & MODE_CLOSE) != 0, OP = (MODE & MODE_OPEN) != 0;
+    typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+    __shared__ typename E::Group buf[3][C];
+    const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int G = P.G, NA = (int)(P.NAPT / PBS_PT);
+    const long S = P.NLINE, NPB = S / P.NAPT;
+    // this thread's lines: L = 1 the line itself, L = 4 a line group of an octet (as in the 4-line pass)
+    const long gid = (long)blockIdx.x * 64 + lane;
+    const int pt = (int)(gid & 31);
+    const long rows = L == 1 ? NPB * NA : NPB * P.NOCT * 2;
+    // L = 1: the last block's missing row repeats the last one (same wave, same values); L = 4: rows are even
+    const long r = min(gid >> 5, rows - 1);
+    const int per = L == 1 ? NA : P.NOCT * 2, grp = (int)(r % per);
+    const long pbk = r / per;
+    const int nval = min(L, NA - L * grp);   // lines of this thread that exist
+    const long pq = pbk * PBS_PT + pt;
+    const double rc = CL ? (double)P.rho_c[pq] : 0.0, ro = OP ? (double)P.rho_o[pq] : 0.0;
+    const double dac = 0.5 * (double)P.h * rc, dao = 0.5 * (double)P.h * ro;
+    const T ac = (T)dac, ao = (T)dao;
+    const int nch = (G + C - 1) / C, NI = (nch + 2 + PF - 1) / PF * PF;   // chunks; barriers of every wave
+    // line e of this thread (one past the last node reads the last one's and is dropped)
+    auto line_of = [&](int e) { return ((long)pbk * NA + min(L * grp + e, NA - 1)) * PBS_PT + pt; };
+    const int NAq = (NA + 3) & ~3;
+    const long QS = (long)G * S, QSb = (long)G * NPB * NAq * PBS_PT;
+    auto top = [&](int n, int u) { return G - 1 - (n * C + u); };   // group u of chunk n (< 0 past the last)
+
+    // one half-step: wave 0 from the fluence, wave 1 from wave 0's result
+    auto half_step = [&](auto first) {
+        constexpr bool closing = decltype(first)::value, ACT = closing ? CL : OP;
+        const T ah = closing ? ac : ao;
+        V rx1[PF][C], rx2[PF][C];
+        std::conditional_t<L == 1, V, u16x4> rq[PF][C];
+        auto fetch = [&](int n, int sl) {
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                const long g = max(top(n, u), 0);
+                if constexpr (closing) {
+#pragma unroll
+                    for (int e = 0; e < L; ++e) {
+                        const T *p = P.psi + 2 * g * S + line_of(e);
+                        rx1[sl][u][e] = p[0];
+                        rx2[sl][u][e] = p[S];
+                    }
+                }
+                if constexpr (HASQ && ACT) {
+                    if constexpr (L == 1)
+                        rq[sl][u] = P.Q[(closing ? 0L : QS) + g * S + line_of(0)];
+                    else
+                        rq[sl][u] = *reinterpret_cast<const u16x4 *>(
+                            P.Qb + (closing ? 0L : QSb) + ((g * NPB + pbk) * NAq + min(L * grp, NAq - L)) * PBS_PT + pt * L);
+                }
+            }
+        };
+        V fi = V(T(0)), fo = V(T(0));   // psi1 - psi2 of the group above: the state before this half-step, after it
+        EPipeTab<T, C> tb(P.Sm, P.Sp, P.kap, G, lane);
+        auto chunk = [&](int n, int sl, auto whole) {
+            constexpr bool FULL = decltype(whole)::value;   // no group past the last one
+            typename E::Group *B = buf[n % 3];
+            T cm[C], cp[C], ck[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u)
+                cm[u] = lane_of(tb.v, u), cp[u] = lane_of(tb.v, C + u), ck[u] = lane_of(tb.v, 2 * C + u);
+            tb.fetch(n + 1);
+            V q[C], a1[C], a2[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                if constexpr (closing) {
+#pragma unroll
+                    for (int e = 0; e < L; ++e) {
+                        a1[u][e] = e < nval ? rx1[sl][u][e] : T(0);
+                        a2[u][e] = e < nval ? rx2[sl][u][e] : T(0);
+                    }
+                } else {
+                    a1[u] = B[u].y1[lane];
+                    a2[u] = B[u].y2[lane];
+                }
+                q[u] = V(T(0));
+                if constexpr (HASQ && ACT) {
+#pragma unroll
+                    for (int e = 0; e < L; ++e) {
+                        if constexpr (L == 1) q[u][e] = rq[sl][u][e];
+                        else q[u][e] = e < nval ? (T)bf16_to_f32(rq[sl][u][e]) : T(0);
+                    }
+                }
+            }
+            fetch(n + PF, sl);
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                const int g = top(n, u);
+                if (!FULL && g < 0) break;
+                V b1 = a1[u], b2 = a2[u];
+                if constexpr (ACT) {
+                    ECoef<T> K;
+                    K.set(cm[u], cp[u], ck[u], ah);
+#pragma unroll
+                    for (int e = 0; e < L; ++e) {
+                        T s1, s2;
+                        K.solve(a1[u][e], a2[u][e], fi[e] + fo[e], q[u][e], s1, s2);
+                        b1[e] = s1;
+                        b2[e] = s2;
+                    }
+                }
+                fi = a1[u] - a2[u];
+                fo = b1 - b2;
+                if constexpr (closing) {
+                    B[u].x1[lane] = a1[u];
+                    B[u].x2[lane] = a2[u];
+                    B[u].y1[lane] = b1;
+                    B[u].y2[lane] = b2;
+                    if constexpr (HASQ && ACT) B[u].qc[lane] = q[u];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < L; ++e)
+                        if (e < nval) {
+                            T *p = P.psi + 2L * g * S + line_of(e);
+                            p[0] = b1[e];
+                            p[S] = b2[e];
+                        }
+                    B[u].z1[lane] = b1;
+                    B[u].z2[lane] = b2;
+                    if constexpr (HASQ && ACT) B[u].qo[lane] = q[u];
+                }
+            }
+        };
+        tb.fetch(0);
+#pragma unroll
+        for (int k = 0; k < PF; ++k) fetch(k, k);
+        if constexpr (!closing) epipe_barrier();   // one chunk behind wave 0
+        for (int n0 = 0; n0 < NI; n0 += PF) {
+#pragma unroll
+            for (int k = 0; k < PF; ++k) {
+                if (n0 + k < G / C) chunk(n0 + k, k, std::true_type());
+                else if (n0 + k < nch) chunk(n0 + k, k, std::false_type());
+                if (closing || n0 + k < NI - 1) epipe_barrier();
+            }
+        }
+    };
+    if (role == 0) {
+        half_step(std::true_type());
+    } else if (role == 1) {
+        half_step(std::false_type());
+    } else if (role == 2) {
+        const bool hasW = L == 1 ? P.W != nullptr : P.Wh != nullptr;
+        V U0 = V(T(0)), U1 = V(T(0)), U2 = V(T(0));
+        V U0b[BANDS ? 4 : 1], U1b[BANDS ? 4 : 1], U2b[BANDS ? 4 : 1], ec = V(T(0)), eo = V(T(0));
+#pragma unroll
+        for (int b = 0; b < (BANDS ? 4 : 1); ++b) U0b[b] = U1b[b] = U2b[b] = V(T(0));
+        const long SB = (long)G * NPB * P.NOCT * (PBS_PT * 8);
+        EPipeTab<T, C> tb(P.wc, P.wdec, P.invdE, G, lane);
+        auto chunk = [&](int n, auto whole) {
+#pragma clang fp contract(off)
+            constexpr bool FULL = decltype(whole)::value;
+            const typename E::Group *B = buf[n % 3];
+            T cw[C], cd[C], ci[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u)
+                cw[u] = lane_of(tb.v, u), cd[u] = lane_of(tb.v, C + u), ci[u] = lane_of(tb.v, 2 * C + u);
+            tb.fetch(n + 1);
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                const int g = top(n, u);
+                if (!FULL && g < 0) break;
+                const V x = B[u].x1[lane], y = B[u].y1[lane], z = B[u].z1[lane];
+                unsigned short hc[L], ho[L];
+#pragma unroll
+                for (int e = 0; e < L; ++e) {
+                    if constexpr (BANDS) {
+                        const int bg = tab(P.band, g);
+                        U0[e] = U1[e] = U2[e] = T(0);
+#pragma unroll
+                        for (int b = 0; b < 4; ++b)
+                            if (b < P.NB) {
+                                const T d = tab(P.wdecb, (long)b * G + g), wb = b == bg ? cw[u] : T(0);
+                                if (CL) U0[e] += (U0b[b][e] = fma(wb, x[e], d * U0b[b][e]));
+                                U1[e] += (U1b[b][e] = fma(wb, y[e], d * U1b[b][e]));
+                                if (OP) U2[e] += (U2b[b][e] = fma(wb, z[e], d * U2b[b][e]));
+                            }
+                    } else {
+                        if (CL) U0[e] = fma(cw[u], x[e], cd[u] * U0[e]);
+                        U1[e] = fma(cw[u], y[e], cd[u] * U1[e]);
+                        if (OP) U2[e] = fma(cd[u], U2[e], cw[u] * z[e]);
+                    }
+                    const T uc = CL ? U0[e] + U1[e] : T(0), uo = OP ? U1[e] + U2[e] : T(0);
+                    if constexpr (L == 1) {
+                        if (CL) P.W[(long)g * S + line_of(0)] = uc * ci[u];
+                        if (OP) P.W[QS + (long)g * S + line_of(0)] = uo * ci[u];
+                    } else {
+                        // rounded with error feedback along the groups, as in the 4-line pass
+                        const float tc = fma(uc, ci[u], ec[e]), to = fma(uo, ci[u], eo[e]);
+                        const __bf16 bc = (__bf16)tc, bo = (__bf16)to;
+                        hc[e] = __builtin_bit_cast(unsigned short, bc);
+                        ho[e] = __builtin_bit_cast(unsigned short, bo);
+                        ec[e] = tc - (float)bc;
+                        eo[e] = to - (float)bo;
+                    }
+                }
+                if constexpr (L == 4) {
+                    const long ob = (((long)g * NPB + pbk) * P.NOCT + grp / 2) * (PBS_PT * 8) + pt * 8 + L * (grp % 2);
+                    if (CL) *reinterpret_cast<u16x4 *>(P.Wh + ob) = u16x4{hc[0], hc[1], hc[2], hc[3]};
+                    if (OP) *reinterpret_cast<u16x4 *>(P.Wh + SB + ob) = u16x4{ho[0], ho[1], ho[2], ho[3]};
+                }
+            }
+        };
+        tb.fetch(0);
+        epipe_barrier();
+        epipe_barrier();   // two chunks behind wave 0
+        for (int n = 0; n < NI - 2; ++n) {
+            if (hasW && n < G / C) chunk(n, std::true_type());
+            else if (hasW && n < nch) chunk(n, std::false_type());
+            epipe_barrier();
+        }
+    } else {
+        double ph0 = 0, ph1 = 0, ph2 = 0, injc = 0, injo = 0;
+        EPipeTab<double, C> tb(P.dA, P.dB, P.dInj, G, lane);
+        auto sum = [&](const V &v) {
+            double s = 0;
+#pragma unroll
+            for (int e = 0; e < L; ++e) s += (double)v[e];
+            return s;
+        };
+        auto chunk = [&](int n, auto whole) {
+#pragma clang fp contract(off)
+            constexpr bool FULL = decltype(whole)::value;
+            const typename E::Group *B = buf[n % 3];
+            double cA[C], cB[C], cw[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u)
+                cA[u] = lane_of(tb.v, u), cB[u] = lane_of(tb.v, C + u), cw[u] = lane_of(tb.v, 2 * C + u);
+            tb.fetch(n + 1);
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                const int g = top(n, u);
+                if (!FULL && g < 0) break;
+                const double s0a = sum(B[u].x1[lane]), s0b = sum(B[u].x2[lane]), s1a = sum(B[u].y1[lane]),
+                             s1b = sum(B[u].y2[lane]), s2a = sum(B[u].z1[lane]), s2b = sum(B[u].z2[lane]);
+                if (CL) ph0 += fma(cA[u], s0a, cB[u] * s0b);
+                ph1 += fma(cA[u], s1a, cB[u] * s1b);
+                if (OP) ph2 += fma(cA[u], s2a, cB[u] * s2b);
+                if (g == 0) {
+                    if (CL) ph0 = fma(P.dBot, s0a - s0b, ph0);
+                    ph1 = fma(P.dBot, s1a - s1b, ph1);
+                    if (OP) ph2 = fma(P.dBot, s2a - s2b, ph2);
+                }
+                if constexpr (HASQ) {
+                    if (CL) injc = fma(cw[u], sum(B[u].qc[lane]), injc);
+                    if (OP) injo = fma(cw[u], sum(B[u].qo[lane]), injo);
+                }
+            }
+        };
+        tb.fetch(0);
+        epipe_barrier();
+        epipe_barrier();
+        for (int n = 0; n < NI - 2; ++n) {
+            if (n < G / C) chunk(n, std::true_type());
+            else if (n < nch) chunk(n, std::false_type());
+            epipe_barrier();
+        }
+        const long slot = L == 1 ? line_of(0) : ((long)pbk * NA + grp) * PBS_PT + pt;
+        if (CL) P.dep_c[slot] = dac * (ph0 + ph1 - injc) * P.scale;
+        if (OP) P.dep_o[slot] = dao * (ph1 + ph2 - injo) * P.scale;
+    }
+}
+
+// blocks of the pipeline form of a grid (64 threads each)
+template <typename T, int L>
+static long epass_pipe_blocks(const EParams<T> &P)
+{
+    const long rows = L == 1 ? P.NLINE / PBS_PT : P.NLINE / P.NAPT * P.NOCT * 2;
+    return (rows * PBS_PT + 63) / 64;
+}
+template <typename T, int L, bool BANDS, bool HASQ>
+static void launch_epass_pipe_t(const EParams<T> &P, int mode, hipStream_t st)
+{
+    const dim3 nb((unsigned)(epass_pipe_blocks<T, L>(P)));
+    if (mode == MODE_PAIR)
+        hipLaunchKernelGGL((epass_pipe_kernel<T, L, MODE_PAIR, BANDS, HASQ>), nb, dim3(256), 0, st, P);
+    else if (mode == MODE_OPEN)
+        hipLaunchKernelGGL((epass_pipe_kernel<T, L, MODE_OPEN, BANDS, HASQ>), nb, dim3(256), 0, st, P);
+    else
+        hipLaunchKernelGGL((epass_pipe_kernel<T, L, MODE_CLOSE, BANDS, HASQ>), nb, dim3(256), 0, st, P);
+}
+template <typename T, int L>
+static hipError_t launch_epass_pipe(const EParams<T> &P, int mode, hipStream_t st)
+{
+    if (P.NB > 1) {
+        if (P.Q) launch_epass_pipe_t<T, L, true, true>(P, mode, st);
+        else launch_epass_pipe_t<T, L, true, false>(P, mode, st);
+    } else {
+        if (P.Q) launch_epass_pipe_t<T, L, false, true>(P, mode, st);
+        else launch_epass_pipe_t<T, L, false, false>(P, mode, st);
+    }
     return hipGetLastError();
 }
 
@@ -1555,18 +1947,6 @@ __device__ __forceinline__ T dpp_zt(T x)
         const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
         const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xF, 0xF, true);
         const unsigned hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, true);
-        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-    }
-}
-template <typename T>
-__device__ __forceinline__ T lane_of(T v, int l)
-{
-    if constexpr (sizeof(T) == 4) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
-    } else {
-        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-        const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, l);
-        const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
         return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
     }
 }

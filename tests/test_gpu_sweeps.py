@@ -67,8 +67,24 @@ def test_energy_step_around_the_group_ring(O, nth, prec, ng):
         _check(got, ref, prec, "ring")
 
 
+# one lateral tile: an odd number of (tile, line) rows, the last block's second half repeats the last one
+@pytest.mark.parametrize("ng,ngen", [(2, 2), (9, 3)])
+@pytest.mark.parametrize("nth,prec", [(8, "fp32"), (12, "fp64"), (16, "fp64"), (16, "fp32")])
+def test_energy_pipeline_of_one_tile(O, nth, prec, ng, ngen):
+    print("case energy pipeline", nth, prec, ng, ngen, flush=True)
+    s, o, c, st = _setup(O, prec, dict(nx=4, ny=5, nth=nth, ng=ng, ngen=ngen), phys=dict(I.PHYS, **I.NUC_BANDS))
+    ref = st.copy()
+    rho = np.ascontiguousarray(c["rho"][1].reshape(-1))
+    o.energy_all(ref, rho, 0.02)
+    s.apply(1, 1, 0.02)
+    got = s.state()
+    s.close()
+    n = 1 if prec == "fp32" and nth >= 16 else ngen   # the BF16 source has its own bound
+    _check(got[:n], ref[:n], prec, "pipeline")
+
+
 def test_batched_ring_is_the_single_beam_pass():
-    """Few beams take the ring in both paths; the plain pass of a wide batch must give the same bits."""
+    """The single beam takes the pipeline of waves, few batched beams the ring and many the plain pass: the same bits."""
     from paper_2504_00340_amd.pbsplit import Batch, Solver
 
     def beams(n):
