@@ -57,6 +57,30 @@ constexpr long EP_PIPE_BLOCKS = 800;
 template <typename T, int L> static long epass_pipe_blocks(const EParams<T> &P);
 template <typename T, int L> static hipError_t launch_epass_pipe(const EParams<T> &P, int mode, hipStream_t st);
 
+// 2 x 2 CN solve of one group for one line: coefficients of the cell's half-step a.  The fused multiply-adds are
+// spelled out, so that every pass that solves a line this way has the same bits.
+template <typename T>
+struct ECoef {
+    T d11, d12, d21, d22, c1, c2, m11, m12, m21, m22, inv, a;
+    __device__ __forceinline__ void set(T sm, T sp, T kp, T a_)
+    {
+#pragma clang fp contract(off)
+        a = a_;
+        d11 = -(sm + kp), d12 = sm, d21 = T(-3) * sp, d22 = -(fma(T(2), sm, sp) + kp);
+        c1 = sp, c2 = T(3) * sp;
+        m11 = fma(-a, d11, T(1)), m12 = -a * d12, m21 = -a * d21, m22 = fma(-a, d22, T(1));
+        inv = fast_rcp(fma(m11, m22, -(m12 * m21)));
+    }
+    __device__ __forceinline__ void solve(T x1, T x2, T f, T q, T &y1, T &y2) const
+    {
+#pragma clang fp contract(off)
+        const T r1 = fma(a, fma(c1, f, fma(d12, x2, d11 * x1)) + q, x1);
+        const T r2 = fma(a, fma(c2, f, fma(d21, x1, d22 * x2)), x2);
+        y1 = fma(r1, m22, -(m12 * r2)) * inv;
+        y2 = fma(m11, r2, -(m21 * r1)) * inv;
+    }
+};
+
 // One thread per line (FP64 contexts, and FP32 contexts whose source product takes the plain scan W):
 // block = one lateral tile pb and one octet of angular lines a = 8*oct + e (e = tid/32), 32 cells
 // pt = tid%32.  FP32 contexts with the split-BF16 product use epass8_body below.
@@ -110,51 +134,42 @@ __device__ __forceinline__ void epass_body(const EParams<T> &P, int bx)
     };
 #pragma unroll
     for (int u = 0; u < EP_RING; ++u) fetch(P.G - 1 - u, rx1[u], rx2[u], rqc[u], rqo[u]);
+    // multiply-adds spelled out as in the pipeline of waves below: recording or not leaves the same bits
     auto group = [&](const int g, const int u) {
+#pragma clang fp contract(off)
         T *p1 = P.psi + (2L * g) * S + line;
         T *p2 = p1 + S;
         const T x1 = rx1[u], x2 = rx2[u], qc = rqc[u], qo = rqo[u];
         fetch(g - EP_RING, rx1[u], rx2[u], rqc[u], rqo[u]);
         const T sm = tab(P.Sm, g), sp = tab(P.Sp, g), kp = tab(P.kap, g);
         // rho-free operator: psi1 row [-(S-+k), S-], psi2 row [-3S+, -(S+ + 2S- + k)], coupling S+[1,3]
-        const T d11 = -(sm + kp), d12 = sm, d21 = T(-3) * sp, d22 = -(sp + T(2) * sm + kp);
-        const T c1 = sp, c2 = T(3) * sp;
         T y1 = x1, y2 = x2;
+        ECoef<T> K;
         if (CL) {
-            const T f = fin + fcl;
-            const T r1 = x1 + ac * (d11 * x1 + d12 * x2 + c1 * f + qc);
-            const T r2 = x2 + ac * (d21 * x1 + d22 * x2 + c2 * f);
-            const T m11 = T(1) - ac * d11, m12 = -ac * d12, m21 = -ac * d21, m22 = T(1) - ac * d22;
-            const T inv = fast_rcp(m11 * m22 - m12 * m21);
-            y1 = (r1 * m22 - m12 * r2) * inv;
-            y2 = (m11 * r2 - m21 * r1) * inv;
+            K.set(sm, sp, kp, ac);
+            K.solve(x1, x2, fin + fcl, qc, y1, y2);
         }
         T z1 = y1, z2 = y2;
         if (OP) {
-            const T f = (CL ? fcl : fin) + fop;
-            const T r1 = y1 + ao * (d11 * y1 + d12 * y2 + c1 * f + qo);
-            const T r2 = y2 + ao * (d21 * y1 + d22 * y2 + c2 * f);
-            const T m11 = T(1) - ao * d11, m12 = -ao * d12, m21 = -ao * d21, m22 = T(1) - ao * d22;
-            const T inv = fast_rcp(m11 * m22 - m12 * m21);
-            z1 = (r1 * m22 - m12 * r2) * inv;
-            z2 = (m11 * r2 - m21 * r1) * inv;
+            K.set(sm, sp, kp, ao);
+            K.solve(y1, y2, (CL ? fcl : fin) + fop, qo, z1, z2);
         }
         *p1 = z1;
         *p2 = z2;
         // deposit functional (FP64): stopping + removal of every state, bottom-face outflow
         const double A = tab(P.dA, g), B = tab(P.dB, g);
-        if (CL) ph0 += A * (double)x1 + B * (double)x2;
-        ph1 += A * (double)y1 + B * (double)y2;
-        if (OP) ph2 += A * (double)z1 + B * (double)z2;
+        if (CL) ph0 += fma(A, (double)x1, B * (double)x2);
+        ph1 += fma(A, (double)y1, B * (double)y2);
+        if (OP) ph2 += fma(A, (double)z1, B * (double)z2);
         if (g == 0) {
-            if (CL) ph0 += P.dBot * ((double)x1 - (double)x2);
-            ph1 += P.dBot * ((double)y1 - (double)y2);
-            if (OP) ph2 += P.dBot * ((double)z1 - (double)z2);
+            if (CL) ph0 = fma(P.dBot, (double)x1 - (double)x2, ph0);
+            ph1 = fma(P.dBot, (double)y1 - (double)y2, ph1);
+            if (OP) ph2 = fma(P.dBot, (double)z1 - (double)z2, ph2);
         }
         if constexpr (HASQ) {
             const double wi = tab(P.dInj, g);
-            if (CL) injc += wi * (double)qc;
-            if (OP) injo += wi * (double)qo;
+            if (CL) injc = fma(wi, (double)qc, injc);
+            if (OP) injo = fma(wi, (double)qo, injo);
         }
         if (hasW || feat) {
             // energy scans of the three states; the next generation needs the sums 0+1 and 1+2
@@ -168,24 +183,24 @@ __device__ __forceinline__ void epass_body(const EParams<T> &P, int bx)
                 for (int b = 0; b < 4; ++b)
                     if (b < P.NB) {
                         const T d = tab(P.wdecb, (long)b * P.G + g), wb = b == bg ? w : T(0);
-                        if (CL) U0 += (U0b[b] = wb * x1 + d * U0b[b]);
-                        U1 += (U1b[b] = wb * y1 + d * U1b[b]);
-                        if (OP) U2 += (U2b[b] = wb * z1 + d * U2b[b]);
+                        if (CL) U0 += (U0b[b] = fma(wb, x1, d * U0b[b]));
+                        U1 += (U1b[b] = fma(wb, y1, d * U1b[b]));
+                        if (OP) U2 += (U2b[b] = fma(wb, z1, d * U2b[b]));
                     }
             } else {
-                if (CL) U0 = w * x1 + dec * U0;
-                U1 = w * y1 + dec * U1;
-                if (OP) U2 = w * z1 + dec * U2;
+                if (CL) U0 = fma(w, x1, dec * U0);
+                U1 = fma(w, y1, dec * U1);
+                if (OP) U2 = fma(dec, U2, w * z1);
             }
             if (feat) {
                 // energy the re-emission puts into the next generation (the dInj functional of its
                 // source summed over destination angles, which the angular law conserves), moments
                 const T wi = (T)tab(P.dInj, g);
-                if (CL) fic += wi * ((U0 + U1) * idE);
+                if (CL) fic = fma(wi, (U0 + U1) * idE, fic);
                 if (OP) {
-                    fio += wi * ((U1 + U2) * idE);
-                    fme += (T)tab(P.wmom, g) * z1 + (T)tab(P.wmom, 2L * P.G + g) * z2;
-                    fmn += (T)tab(P.wmom, (long)P.G + g) * z1;
+                    fio = fma(wi, (U1 + U2) * idE, fio);
+                    fme += fma((T)tab(P.wmom, g), z1, (T)tab(P.wmom, 2L * P.G + g) * z2);
+                    fmn = fma((T)tab(P.wmom, (long)P.G + g), z1, fmn);
                 }
             }
             if (hasW) {
@@ -918,29 +933,6 @@ struct EPipeTab {
     {
     }
     __device__ __forceinline__ void fetch(int n) { v = p[max(top - n * C, 0)]; }
-};
-
-// 2 x 2 CN solve of one group for one line: coefficients of the cell's half-step a
-template <typename T>
-struct ECoef {
-    T d11, d12, d21, d22, c1, c2, m11, m12, m21, m22, inv, a;
-    __device__ __forceinline__ void set(T sm, T sp, T kp, T a_)
-    {
-#pragma clang fp contract(off)
-        a = a_;
-        d11 = -(sm + kp), d12 = sm, d21 = T(-3) * sp, d22 = -(fma(T(2), sm, sp) + kp);
-        c1 = sp, c2 = T(3) * sp;
-        m11 = fma(-a, d11, T(1)), m12 = -a * d12, m21 = -a * d21, m22 = fma(-a, d22, T(1));
-        inv = fast_rcp(fma(m11, m22, -(m12 * m21)));
-    }
-    __device__ __forceinline__ void solve(T x1, T x2, T f, T q, T &y1, T &y2) const
-    {
-#pragma clang fp contract(off)
-        const T r1 = fma(a, fma(c1, f, fma(d12, x2, d11 * x1)) + q, x1);
-        const T r2 = fma(a, fma(c2, f, fma(d21, x1, d22 * x2)), x2);
-        y1 = fma(r1, m22, -(m12 * r2)) * inv;
-        y2 = fma(m11, r2, -(m21 * r1)) * inv;
-    }
 };
 
 template <typename T, int L, int MODE, bool BANDS, bool HASQ>
