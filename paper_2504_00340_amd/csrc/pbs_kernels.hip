@@ -2646,152 +2646,48 @@ __device__ __forceinline__ void apass_mfma32_body(const AParams<float> &P, const
     }
 }
 
-// MFMA version for nth = 16 (15 interior nodes), FP32: each 15-point sine transform is one dense
-// 16 x 16 product (the matrix zero-padded), a chain of four v_mfma_f32_16x16x4_f32 whose 16 columns
-// are 16 lateral cells of one angular line; the 15 x 15 x 16 block (14.4 KB) stays in LDS.  The sine
-// matrix is symmetric, so the inverse uses the same operand table with the factor 2/N.  As in the
-// 32-node pass the operand rows are permuted, so that result element q of lane group g holds index
-// 4 q + g: a store's lane groups then land in adjacent rows, and the modes of the second index feed
-// the inverse product straight from registers.
-//   Ktab[s*64 + lane] = S[perm(lane % 16)][4 s + lane / 16], S[r][k] = sin(pi (r+1)(k+1) / 16), zero at
-//   15, perm(4 g + q) = 4 q + g.
-__device__ __forceinline__ void apass_mfma16_body(const AParams<float> &P, const float *__restrict__ Ktab, long stack,
-                                                  int pb, int half)
+// Blocks of the 16-cell forms per stack, and a block's lateral tile and first cell.  From 8 tiles on the two halves of one tile
+// are 8 workgroups apart (one XCD, shared L2 lines), in whole groups of 8 tiles; fewer tiles are packed, as most of
+// such a group would be empty blocks (2 tiles, 15 x 15 angles, 60 groups: 33 -> 21 us).
+__host__ __device__ constexpr int apass_half_blocks(int npb) { return npb < 8 ? 2 * npb : (npb + 7) / 8 * 16; }
+__device__ __forceinline__ void apass_half_tile(int bid, int npb, int &pb, int &half)
 {
-    constexpr int m = 15, NA = 225, PC = 16, NT = 256;
-    __shared__ float L[NA * PC];   // L[a*16 + c], a = i*15 + j
-    const int c0 = half * PC;
-    const int g = (int)((stack / 2) % P.G);
-    float *blk = P.psi + stack * P.NLINE + (long)pb * NA * PBS_PT + c0;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int r4 = lane >> 4, cc = lane & 15;
-    for (int idx = tid; idx < NA * 4; idx += NT) {
-        const int a = idx >> 2, q = idx & 3;
-        *reinterpret_cast<float4 *>(&L[a * PC + q * 4]) = *reinterpret_cast<const float4 *>(blk + (long)a * PBS_PT + q * 4);
-    }
-    float A[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) A[s] = Ktab[s * 64 + lane];
-    // result element q of lane group r4 holds index 4 q + r4 (permuted operand rows)
-    float lamR[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int r = 4 * q + r4;
-        lamR[q] = r < m ? P.lam[r] : 0.f;
-    }
-    const float al = 0.25f * P.h * P.sig[g] * P.rho[(long)pb * PBS_PT + c0 + cc];
-    constexpr float sc = 2.f / 16.f;
-    __syncthreads();
-    // forward over the first angular index; line = column j
-    for (int j = wid; j < m; j += NT / 64) {
-        floatx4 y = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int ip = 4 * s + r4;
-            y = mfma16(A[s], ip < m ? L[(ip * m + j) * PC + cc] : 0.f, y);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int r = 4 * q + r4;
-            if (r < m) L[(r * m + j) * PC + cc] = y[q];
-        }
-    }
-    __syncthreads();
-    // over the second index: forward, CN factor, inverse; line = mode k of the first index
-    for (int k = wid; k < m; k += NT / 64) {
-        floatx4 z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int jp = 4 * s + r4;
-            z = mfma16(A[s], jp < m ? L[(k * m + jp) * PC + cc] : 0.f, z);
-        }
-        const float lk = P.lam[k];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float t = al * (lk + lamR[q]);
-            z[q] = z[q] * (1.f + t) * __builtin_amdgcn_rcpf(1.f - t);
-        }
-        // the scaled modes are already the inverse's B operands (element s of lane group r4 is mode 4 s + r4,
-        // the operand of step s; mode 15 is zero: its operand row is)
-        floatx4 u = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) u = mfma16(A[s], z[s], u);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int jp = 4 * q + r4;
-            if (jp < m) L[(k * m + jp) * PC + cc] = u[q] * sc;
-        }
-    }
-    __syncthreads();
-    // inverse over the first index
-    for (int j = wid; j < m; j += NT / 64) {
-        floatx4 u = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int r = 4 * s + r4;
-            u = mfma16(A[s], r < m ? L[(r * m + j) * PC + cc] : 0.f, u);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int ip = 4 * q + r4;
-            if (ip < m) L[(ip * m + j) * PC + cc] = u[q] * sc;
-        }
-    }
-    __syncthreads();
-    for (int idx = tid; idx < NA * 4; idx += NT) {
-        const int a = idx >> 2, q = idx & 3;
-        *reinterpret_cast<float4 *>(blk + (long)a * PBS_PT + q * 4) = *reinterpret_cast<const float4 *>(&L[a * PC + q * 4]);
-    }
-}
-
-__global__ __launch_bounds__(256) void apass_mfma16_kernel(AParams<float> P, const float *__restrict__ Ktab, int npb)
-{
-    // the two 16-column halves of one lateral tile are 8 workgroups apart -> same XCD, same L2 lines
-    const int bid = blockIdx.x;
-    const int pb = (bid >> 4) * 8 + (bid & 7), half = (bid >> 3) & 1;
-    if (pb >= npb) return;
-    apass_mfma16_body(P, Ktab, blockIdx.y, pb, half);
-}
-
-hipError_t launch_apass_mfma16(const AParams<float> &P, const float *Ktab, long nstack, hipStream_t st)
-{
-    const int nb = (P.NPB + 7) / 8 * 16;
-    hipLaunchKernelGGL(apass_mfma16_kernel, dim3(nb, (unsigned)nstack), dim3(256), 0, st, P, Ktab, P.NPB);
-    return hipGetLastError();
+    pb = npb < 8 ? bid >> 1 : (bid >> 4) * 8 + (bid & 7);
+    half = npb < 8 ? bid & 1 : (bid >> 3) & 1;
 }
 
 // two blocks per CU need <= 64 VGPRs (8 waves per SIMD)
 __global__ __launch_bounds__(APASS32_NT) __attribute__((amdgpu_waves_per_eu(8))) void apass_mfma32_kernel(
     AParams<float> P, const float *__restrict__ Ktab, int npb)
 {
-    // the two 16-column halves of one lateral tile are 8 workgroups apart -> same XCD, same L2 lines
-    const int bid = blockIdx.x;
-    const int pb = (bid >> 4) * 8 + (bid & 7), half = (bid >> 3) & 1;
+    int pb, half;
+    apass_half_tile(blockIdx.x, npb, pb, half);
     if (pb >= npb) return;
     apass_mfma32_body(P, Ktab, blockIdx.y, pb, half);
 }
 
 hipError_t launch_apass_mfma32(const AParams<float> &P, const float *Ktab, long nstack, hipStream_t st)
 {
-    const int nb = (P.NPB + 7) / 8 * 16;
-    hipLaunchKernelGGL(apass_mfma32_kernel, dim3(nb, (unsigned)nstack), dim3(APASS32_NT), 0, st, P, Ktab, P.NPB);
+    hipLaunchKernelGGL(apass_mfma32_kernel, dim3(apass_half_blocks(P.NPB), (unsigned)nstack), dim3(APASS32_NT), 0, st, P, Ktab, P.NPB);
     return hipGetLastError();
 }
 
-// The same two forms for N = 20 and 24 (split by mode parity), and in FP64 for N = 16 (one dense product per line), 20,
-// 24 and 32.  What bounded the vector transform they replace was its set-up around the arithmetic, not the
-// arithmetic: half a wave's lanes per line, the sine table through scalar loads in every line, a block barrier per
-// phase with 12 waves per CU.  A block holds PCH groups of 16 cells of one lateral tile; its 8 waves take whole
-// (group, line) items.  FP64 results come out in operand order by themselves (row 4 q + lane / 16), so its operand
-// rows are not permuted.
+// The other matrix forms: N = 16 (one dense 16 x 16 product per line, zero-padded, a chain of four), 20 and 24 (split by
+// mode parity as above), and N = 32 in FP64.  What bounded the vector transform they replace was its set-up around the
+// arithmetic, not the arithmetic: half a wave's lanes per line, the sine table through scalar loads in every line, a
+// block barrier per phase with 12 waves per CU.  A block holds 16 cells of one lateral tile; its waves take whole lines
+// and work in place.  As in the 32-node pass the FP32 operand rows are permuted, so that result element q of lane
+// group g holds index 4 q + g: a store's lane groups land in adjacent rows, and the modes of the second index feed the
+// inverse product straight from registers.  FP64 results come out in that order by themselves (row 4 q + lane / 16).
+//   Ktab: dense, [s*64 + lane] = S[perm(lane % 16)][4 s + lane / 16], S[r][k] = sin(pi (r+1)(k+1) / N) (symmetric: the
+//   inverse uses it too); split as above.
 // Measured, us per launch of two generations, before -> after: FP32 40 x 40 cells, 60 groups, N = 20 686 -> 343 and N =
-// 24 1144 -> 432; 45 x 70, N = 20, 75, three generations 2487 -> 1060; FP64 64 x 64, N = 16, 64 1311 -> 1010; 40 x 40,
-// 60, N = 20 970 -> 775 and N = 24 1161 -> 1000; 32 x 32, 32, N = 32 828 -> 700.  Both groups of a tile in one block:
-// 1.5-18 % slower for N = 20 and 24; 4 or 16 waves: 5-25 % slower.  Below 16 nodes the vector transform stays: its
+// 24 1144 -> 432; 45 x 70, N = 20, 75, three generations 2487 -> 1060; 64 x 64, N = 16, 96 657 -> 640 (4.4 TB/s; the four
+// loads of a thread in flight before their LDS stores); FP64 64 x 64, N = 16, 64 1311 -> 881; 40 x 40, 60, N = 20 970 -> 775
+// and N = 24 1161 -> 1000; 32 x 32, 32, N = 32 828 -> 700.  Tried and dropped: both 16-cell groups of a tile in one block (1-18 %
+// slower), 4 or 16 waves instead of 8 for the split forms (5-25 %), 8 instead of 4 for N = 16 in FP32 (7 %; in FP64 8 are
+// 3 % faster), blocks that stay and load their next tile while they transform the present one (N = 16: 5-15 % slower, the
+// registers of the tile cost more waves than the overlap gains).  Below 16 nodes the vector transform stays: its
 // lines are short enough that its blocks keep 32 waves per CU, and the matrix form took 1.3-1.7 times as long at N = 8 and
 // 10 and 1.25 times at N = 12.
 template <typename T, int N>
@@ -2801,8 +2697,7 @@ struct AngMfma {
     static constexpr int H = SPLIT ? N / 2 : m;       // odd (or all) modes and operand nodes
     static constexpr int HE = SPLIT ? N / 2 - 1 : 0;  // even modes
     static constexpr int KS = (H + 3) / 4;            // 4-node steps
-    static constexpr int PCH = SPLIT ? 1 : 2;         // groups of 16 cells per block
-    static constexpr int NT = 512;
+    static constexpr int NT = !SPLIT && sizeof(T) == 4 ? 256 : 512;
     static constexpr int CH = 16 / (int)sizeof(T);    // values per 16-byte access
     typedef T T4 __attribute__((ext_vector_type(4)));
     typedef T TC __attribute__((ext_vector_type(CH)));
@@ -2814,19 +2709,16 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
     using C = AngMfma<T, N>;
     using T4 = typename C::T4;
     using TC = typename C::TC;
-    constexpr int m = C::m, NA = C::NA, H = C::H, HE = C::HE, KS = C::KS, NT = C::NT, CH = C::CH, PCH = C::PCH;
+    constexpr int m = C::m, NA = C::NA, H = C::H, HE = C::HE, KS = C::KS, NT = C::NT, CH = C::CH;
     constexpr bool SPLIT = C::SPLIT;
-    __shared__ T L[PCH * NA * 16];   // [group][a][cell]
+    __shared__ T L[NA * 16];   // [a][cell]
     const int g = (int)((stack / 2) % P.G);
     T *blk = P.psi + stack * P.NLINE + (long)pb * NA * PBS_PT + c0;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int r4 = lane >> 4, cc = lane & 15;
     // tile to LDS and back, 16 bytes per lane, several loads in flight
-    constexpr int CPR = PCH * 16 / CH, NCHK = NA * CPR, UL = 4;
-    auto lds_at = [&](int idx) {
-        const int a = idx / CPR, c = (idx % CPR) * CH;
-        return reinterpret_cast<TC *>(&L[((c >> 4) * NA + a) * 16 + (c & 15)]);
-    };
+    constexpr int CPR = 16 / CH, NCHK = NA * CPR, UL = 4;
+    auto lds_at = [&](int idx) { return reinterpret_cast<TC *>(&L[idx * CH]); };
     auto mem_at = [&](int idx) { return reinterpret_cast<TC *>(blk + (long)(idx / CPR) * PBS_PT + (idx % CPR) * CH); };
     for (int i0 = tid; i0 < NCHK; i0 += UL * NT) {
         TC v[UL];
@@ -2856,9 +2748,7 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
         lamO[q] = r < H ? P.lam[SPLIT ? 2 * r : r] : T(0);
         lamE[q] = SPLIT && r < HE ? P.lam[2 * r + 1] : T(0);
     }
-    T al[PCH];
-#pragma unroll
-    for (int h = 0; h < PCH; ++h) al[h] = T(0.25) * P.h * P.sig[g] * P.rho[(long)pb * PBS_PT + c0 + 16 * h + cc];
+    const T al = T(0.25) * P.h * P.sig[g] * P.rho[(long)pb * PBS_PT + c0 + cc];
     // a line's operand at step s: node ip, and its mirror image folded in by parity
     auto fold = [&](const T *x, int stride, int s, T &o, T &e) {
         const int ip = 4 * s + r4;
@@ -2873,8 +2763,8 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
     };
     __syncthreads();
     // forward over the first angular index, line = column j: odd mode r to row r, even mode r to row H + r
-    for (int it = wid; it < PCH * m; it += NT / 64) {
-        T *x = &L[(it / m) * NA * 16 + (it % m) * 16 + cc];
+    for (int j = wid; j < m; j += NT / 64) {
+        T *x = &L[j * 16 + cc];
         T4 yo = {0, 0, 0, 0}, ye = {0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
@@ -2892,9 +2782,8 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
     }
     __syncthreads();
     // over the second index: forward, CN factor, inverse; line = row k (odd or even mode of the first index)
-    for (int it = wid; it < PCH * m; it += NT / 64) {
-        const int k = it % m;
-        T *x = &L[(it / m) * NA * 16 + k * m * 16 + cc];
+    for (int k = wid; k < m; k += NT / 64) {
+        T *x = &L[k * m * 16 + cc];
         T4 zo = {0, 0, 0, 0}, ze = {0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
@@ -2904,15 +2793,13 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
             if constexpr (SPLIT) ze = mfma16(Ae[s], e, ze);
         }
         const T lk = P.lam[!SPLIT ? k : k < H ? 2 * k : 2 * (k - H) + 1];
-        T alh = al[0];
-        if constexpr (PCH > 1) alh = it / m ? al[PCH - 1] : al[0];
 #pragma unroll
         for (int q = 0; q < KS; ++q) {
             const int r = 4 * q + r4;
-            const T to = alh * (lk + lamO[q]);
+            const T to = al * (lk + lamO[q]);
             zo[q] = r < H ? zo[q] * (T(1) + to) * fast_rcp(T(1) - to) : T(0);
             if constexpr (SPLIT) {
-                const T te = alh * (lk + lamE[q]);
+                const T te = al * (lk + lamE[q]);
                 ze[q] = r < HE ? ze[q] * (T(1) + te) * fast_rcp(T(1) - te) : T(0);
             }
         }
@@ -2943,8 +2830,8 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
     __syncthreads();
     // inverse over the first index, with the (2/N)^2 normalisation
     constexpr T sc = (T(2) / T(N)) * (T(2) / T(N));
-    for (int it = wid; it < PCH * m; it += NT / 64) {
-        T *x = &L[(it / m) * NA * 16 + (it % m) * 16 + cc];
+    for (int j = wid; j < m; j += NT / 64) {
+        T *x = &L[j * 16 + cc];
         T4 u = {0, 0, 0, 0}, v = {0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
@@ -2977,23 +2864,13 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
     for (int idx = tid; idx < NCHK; idx += NT) *mem_at(idx) = *lds_at(idx);
 }
 
-// blocks per stack, and a block's lateral tile and first cell: the two 16-cell groups of one tile, where they are
-// two blocks, are 8 workgroups apart (one XCD, shared L2 lines)
-template <typename T, int N>
-__host__ __device__ constexpr int apass_mfma_blocks(int npb)
-{
-    return AngMfma<T, N>::PCH == 2 ? npb : (npb + 7) / 8 * 16;
-}
 template <typename T, int N>
 __device__ __forceinline__ void apass_mfma_block(const AParams<T> &P, const T *__restrict__ Ktab, int bid, long stack, int npb)
 {
-    int pb = bid, c0 = 0;
-    if constexpr (AngMfma<T, N>::PCH == 1) {
-        pb = (bid >> 4) * 8 + (bid & 7);
-        c0 = ((bid >> 3) & 1) * 16;
-    }
+    int pb, half;
+    apass_half_tile(bid, npb, pb, half);
     if (pb >= npb) return;
-    apass_mfma_body<T, N>(P, Ktab, stack, pb, c0);
+    apass_mfma_body<T, N>(P, Ktab, stack, pb, 16 * half);
 }
 
 template <typename T, int N>
@@ -3005,7 +2882,7 @@ __global__ __launch_bounds__((AngMfma<T, N>::NT)) void apass_mfma_kernel(AParams
 template <typename T, int N>
 static hipError_t launch_apass_mfma_n(const AParams<T> &P, const T *Ktab, long nstack, hipStream_t st)
 {
-    hipLaunchKernelGGL((apass_mfma_kernel<T, N>), dim3((unsigned)(apass_mfma_blocks<T, N>(P.NPB)), (unsigned)nstack),
+    hipLaunchKernelGGL((apass_mfma_kernel<T, N>), dim3((unsigned)(apass_half_blocks(P.NPB)), (unsigned)nstack),
                        dim3(AngMfma<T, N>::NT), 0, st, P, Ktab);
     return hipGetLastError();
 }
@@ -3022,7 +2899,6 @@ template <typename T>
 hipError_t launch_apass(const AParams<T> &P, const T *Ktab, int nth, long nstack, hipStream_t st)
 {
     if constexpr (sizeof(T) == 4) {
-        if (nth == 16) return launch_apass_mfma16(P, Ktab, nstack, st);
         if (nth == 32) return launch_apass_mfma32(P, Ktab, nstack, st);
     }
     switch (nth) {
@@ -3034,7 +2910,9 @@ hipError_t launch_apass(const AParams<T> &P, const T *Ktab, int nth, long nstack
     case 16: return launch_apass_mfma_n<T, 16>(P, Ktab, nstack, st);
     case 20: return launch_apass_mfma_n<T, 20>(P, Ktab, nstack, st);
     case 24: return launch_apass_mfma_n<T, 24>(P, Ktab, nstack, st);
-    case 32: return launch_apass_mfma_n<T, 32>(P, Ktab, nstack, st);
+    case 32:
+        if constexpr (sizeof(T) == 8) return launch_apass_mfma_n<T, 32>(P, Ktab, nstack, st);
+        [[fallthrough]];
     default: return hipErrorInvalidValue;
     }
 }
@@ -4013,21 +3891,16 @@ __global__ __launch_bounds__((AngMfma<float, N>::NT)) void apass_batched_kernel(
     apass_mfma_block<float, N>(batch_aparams(B, Sh, s, k), Sh.K, blockIdx.x, blockIdx.y, Sh.NPB);
 }
 
-// batched MFMA angular passes (nth = 16 and 32): the single-beam bodies, beam = blockIdx.z
-template <int NTH>
-__global__ __launch_bounds__(NTH == 32 ? APASS32_NT : 256) __attribute__((amdgpu_waves_per_eu(8)))
-void apass_mfma_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh, int s, int k)
+// the 32-node FP32 pass, beam = blockIdx.z
+__global__ __launch_bounds__(APASS32_NT) __attribute__((amdgpu_waves_per_eu(8)))
+void apass_mfma32_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh, int s, int k)
 {
     const BeamDev &B = beams[blockIdx.z];
     if (s >= B.nz || blockIdx.y >= (unsigned)((k < 0 ? Sh.ngen : 1) * B.G * 2)) return;
-    const int bid = blockIdx.x;
-    const int pb = (bid >> 4) * 8 + (bid & 7), half = (bid >> 3) & 1;
+    int pb, half;
+    apass_half_tile(blockIdx.x, Sh.NPB, pb, half);
     if (pb >= Sh.NPB) return;
-    const AParams<float> P = batch_aparams(B, Sh, s, k);
-    if constexpr (NTH == 32)
-        apass_mfma32_body(P, Sh.K, blockIdx.y, pb, half);
-    else
-        apass_mfma16_body(P, Sh.K, blockIdx.y, pb, half);
+    apass_mfma32_body(batch_aparams(B, Sh, s, k), Sh.K, blockIdx.y, pb, half);
 }
 
 __global__ __launch_bounds__(256) void dose_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh, int s)
@@ -4110,23 +3983,19 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
 #undef PBS_TD
         };
         tpass();
-        if (Sh.nth == 16 || Sh.nth == 32) {
-            dim3 grid((unsigned)((Sh.NPB + 7) / 8 * 16), (unsigned)nstack, nbeam);
-            if (Sh.nth == 32)
-                hipLaunchKernelGGL(apass_mfma_batched_kernel<32>, grid, dim3(APASS32_NT), 0, q, beams, Sh, s, k);
-            else
-                hipLaunchKernelGGL(apass_mfma_batched_kernel<16>, grid, dim3(256), 0, q, beams, Sh, s, k);
-        } else {
-#define PBS_AB(N)                                                                                                    \
-    hipLaunchKernelGGL((apass_batched_kernel<N>), dim3((unsigned)(apass_mfma_blocks<float, N>(Sh.NPB)), nstack, nbeam), \
-                       dim3(AngMfma<float, N>::NT), 0, q, beams, Sh, s, k)
-            switch (Sh.nth) {
-            case 20: PBS_AB(20); break;
-            case 24: PBS_AB(24); break;
-            default: return hipErrorInvalidValue;
-            }
-#undef PBS_AB
+        const dim3 grid((unsigned)apass_half_blocks(Sh.NPB), (unsigned)nstack, nbeam);
+#define PBS_AB(N) \
+    hipLaunchKernelGGL((apass_batched_kernel<N>), grid, dim3(AngMfma<float, N>::NT), 0, q, beams, Sh, s, k)
+        switch (Sh.nth) {
+        case 16: PBS_AB(16); break;
+        case 20: PBS_AB(20); break;
+        case 24: PBS_AB(24); break;
+        case 32:
+            hipLaunchKernelGGL(apass_mfma32_batched_kernel, grid, dim3(APASS32_NT), 0, q, beams, Sh, s, k);
+            break;
+        default: return hipErrorInvalidValue;
         }
+#undef PBS_AB
         tpass();
         return hipGetLastError();
     };
