@@ -12,15 +12,18 @@
 #include "pbs_ctx.h"
 #include "pbs_net_internal.h"
 
-// The depth march runs on two streams (a generation's T A T beside the energy chain) when one
-// generation holds fewer phase-space cells than this: such kernels leave most of the GPU idle (a 32 x 32
-// beam with 15 x 15 angles and 128 groups: +11 % beams/s), while at 64 x 64 cells, 31 x 31 angles, 128
-// groups and 4 generations every kernel already saturates HBM and the concurrent ones mostly slow each other
-// (1 % per step gained, every kernel 1.4-2.6x longer), so there the sub-steps stay in order on one stream
-// and each kernel's own rate stays measurable.
+// The depth march runs on two streams (a generation's T A T beside the energy chain) when it has several generations
+// and one of them holds fewer phase-space cells than PBS_OVERLAP_CELLS: such kernels leave most of the GPU idle (32 x 32
+// cells, 15 x 15 angles, 131 groups: 926 -> 822 us a step), while at 64 x 64 cells, 31 x 31 angles, 128 groups and 4
+// generations every kernel already saturates HBM and the concurrent ones mostly slow each other (1 % per step gained,
+// every kernel 1.4-2.6x longer), so there the sub-steps stay in order on one stream.  One generation has nothing to
+// overlap with (64 x 64, 15 x 15, 96: 1160 against 1177 us).  The events between the streams cost the host about 35 us per
+// generation and step: below PBS_OVERLAP_MIN cells of a grid with few angles the step itself is shorter than that (4 x
+// 4, 11 x 11, 60: 64 against 78 us; 16 x 16, 7 x 7, 48: 71 against 78).
 #ifndef PBS_OVERLAP_CELLS
 #define PBS_OVERLAP_CELLS 100000000L
 #endif
+#define PBS_OVERLAP_MIN 1000000L
 #include "pbsplit.h"
 
 using namespace pbs;
@@ -924,8 +927,10 @@ pbs_status one_step(pbs_ctx *c)
     const int s = c->step;
     const double dz = c->g.dz;
     // a context without the side stream (bound to the static scratch) always marches on one stream
+    const long cells = (long)c->NP * c->NA * c->G();
     const bool ovl = c->side && (c->sched == PBS_SCHED_TWO_STREAMS ||
-                                 (c->sched == PBS_SCHED_AUTO && (long)c->NP * c->NA * c->G() < PBS_OVERLAP_CELLS));
+                                 (c->sched == PBS_SCHED_AUTO && c->kact > 1 && cells < PBS_OVERLAP_CELLS &&
+                                  (c->NA >= 128 || cells >= PBS_OVERLAP_MIN)));
     const int tat = ovl ? s : -1;
     pbs_status r = (s == 0) ? energy_chain<T>(c, MODE_OPEN, -1, 0, 0.5 * dz, tat)
                             : energy_chain<T>(c, MODE_PAIR, s - 1, s, 0.5 * dz, tat);
