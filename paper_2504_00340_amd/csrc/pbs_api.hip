@@ -19,7 +19,7 @@
 // every kernel 1.4-2.6x longer), so there the sub-steps stay in order on one stream.  One generation has nothing to
 // overlap with (64 x 64, 15 x 15, 96: 1160 against 1177 us).  The events between the streams cost the host about 35 us per
 // generation and step: below PBS_OVERLAP_MIN cells of a grid with few angles the step itself is shorter than that (4 x
-// 4, 11 x 11, 60: 64 against 78 us; 16 x 16, 7 x 7, 48: 71 against 78).
+// 4, 11 x 11, 60: 64 against 78 us; 16 x 16, 7 x 7, 48: 71 against 78), and where T A T is one launch.
 #ifndef PBS_OVERLAP_CELLS
 #define PBS_OVERLAP_CELLS 100000000L
 #endif
@@ -131,7 +131,7 @@ void transfer_table_bf16(const std::vector<double> &P2T, int NA, int Mp, int Kpb
 void apass_mfma_table(int nth, bool fp64, double *t)
 {
     for (int i = 0; i < 1024; ++i) t[i] = 0.0;
-    if (nth < 8) return;
+    if (nth < 16) return;   // no MFMA form
     const int H = nth / 2;
     auto sodd = [&](int r, int i) { return r < H && i < H ? std::sin(M_PI * (2 * r + 1) * (i + 1) / (double)nth) : 0.0; };
     auto seven = [&](int r, int i) {
