@@ -585,10 +585,9 @@ pbs_status upload_tables(pbs_ctx *c)
     // zero-padded, source-major copy for the MFMA product: P2p[b][k][a] = P2T[b][a][k]
     const size_t NA2 = (size_t)c->NA * c->NA, KM = (size_t)c->Kp * c->Mp;
     for (int b = 0; b < c->NB; ++b)
-        for (int k = 0; k < c->Kp; ++k)
-            for (int a = 0; a < c->Mp; ++a)
-                t[c->t_P2p + b * KM + (size_t)k * c->Mp + a] =
-                    (k < c->NA && a < c->NA) ? (T)c->P2T[b * NA2 + (size_t)a * c->NA + k] : T(0);
+        for (int a = 0; a < c->NA; ++a)
+            for (int k = 0; k < c->NA; ++k)
+                t[c->t_P2p + b * KM + (size_t)k * c->Mp + a] = (T)c->P2T[b * NA2 + (size_t)a * c->NA + k];
     // MFMA operand constants of the angular pass
     std::vector<double> kt(1024);
     apass_mfma_table(c->g.nth, sizeof(T) == 8, kt.data());
@@ -724,6 +723,8 @@ template <typename T>
 pbs_status transport(pbs_ctx *c, double h, int k = -1, hipStream_t st = nullptr);
 template <typename T>
 pbs_status angular(pbs_ctx *c, int layer, double h, int k = -1, hipStream_t st = nullptr);
+template <typename T>
+pbs_status transport_angular(pbs_ctx *c, int layer, double h, int k = -1, hipStream_t st = nullptr);
 
 // Energy half-step(s) for all generations in order.  mode: close the layer lay_c (state 0 -> 1),
 // open the layer lay_o (state 1 -> 2), or both in one sweep.  Deposits go to the FP64 dose.
@@ -768,9 +769,7 @@ pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, in
             HIPCHK(c, hipEventRecord(c->ev_e[k], c->stream));
             HIPCHK(c, hipStreamWaitEvent(c->side, c->ev_e[k], 0));
             pbs_status r;
-            if ((r = transport<T>(c, h, k, c->side)) != PBS_OK) return r;
-            if ((r = angular<T>(c, tat_layer, 2 * h, k, c->side)) != PBS_OK) return r;
-            if ((r = transport<T>(c, h, k, c->side)) != PBS_OK) return r;
+            if ((r = transport_angular<T>(c, tat_layer, 2 * h, k, c->side)) != PBS_OK) return r;
             HIPCHK(c, hipEventRecord(c->ev_tat[k], c->side));
             c->tat_pend[k] = true;
         }
@@ -827,8 +826,9 @@ pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, in
     return PBS_OK;
 }
 
+// of generation k, all active ones for k < 0
 template <typename T>
-pbs_status transport(pbs_ctx *c, double h, int k, hipStream_t st)
+TParams<T> tparams(pbs_ctx *c, double h, int k)
 {
     TParams<T> P;
     P.psi = c->psi<T>(k < 0 ? 0 : k);
@@ -841,20 +841,15 @@ pbs_status transport(pbs_ctx *c, double h, int k, hipStream_t st)
     P.NA = c->NA;
     P.NLINE = c->NLINE;
     P.nplanes = (long)(k < 0 ? c->kact : 1) * c->G() * 2 * c->NA;
-    if (!st) st = c->stream;
-    ProfScope ps(c, PBS_K_TPASS, st);
-    HIPCHK(c, launch_tpass<T>(P, st));
-    return PBS_OK;
+    return P;
 }
 
 template <typename T>
-pbs_status angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st)
+AParams<T> aparams(pbs_ctx *c, int layer, double h, int k)
 {
     AParams<T> P;
     T *tb = c->tabT<T>();
     P.psi = c->psi<T>(k < 0 ? 0 : k);
-    const long nstack = (long)(k < 0 ? c->kact : 1) * c->G() * 2;
-    if (!st) st = c->stream;
     P.rho = c->rhoT<T>(layer);
     P.sig = tb + c->t_sig;
     P.S = tb + c->t_S;
@@ -864,9 +859,49 @@ pbs_status angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st)
     P.NA = c->NA;
     P.NPB = c->NPB;
     P.NLINE = c->NLINE;
-    ProfScope ps(c, PBS_K_APASS, st);
-    HIPCHK(c, launch_apass<T>(P, tb + c->t_K32, c->g.nth, nstack, st));
+    return P;
+}
+
+static long slabs(const pbs_ctx *c, int k) { return (long)(k < 0 ? c->kact : 1) * c->G() * 2; }
+
+template <typename T>
+pbs_status transport(pbs_ctx *c, double h, int k, hipStream_t st)
+{
+    if (!st) st = c->stream;
+    ProfScope ps(c, PBS_K_TPASS, st);
+    HIPCHK(c, launch_tpass<T>(tparams<T>(c, h, k), st));
     return PBS_OK;
+}
+
+template <typename T>
+pbs_status angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st)
+{
+    if (!st) st = c->stream;
+    ProfScope ps(c, PBS_K_APASS, st);
+    HIPCHK(c, launch_apass<T>(aparams<T>(c, layer, h, k), c->tabT<T>() + c->t_K32, c->g.nth, slabs(c, k), st));
+    return PBS_OK;
+}
+
+// every active generation's T(h/2) A(h) T(h/2) in one launch (the kinds of pass are timed one by one)
+template <typename T>
+bool tat_fused(const pbs_ctx *c)
+{
+    return !c->prof && tat_fits<T>(c->g.nth, c->g.ny, c->NLINE, slabs(c, -1));
+}
+
+// T(h/2) A(h) T(h/2)
+template <typename T>
+pbs_status transport_angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st)
+{
+    if (!st) st = c->stream;
+    if (k < 0 && tat_fused<T>(c)) {
+        HIPCHK(c, launch_tat<T>(tparams<T>(c, 0.5 * h, k), aparams<T>(c, layer, h, k), c->g.nth, slabs(c, k), st));
+        return PBS_OK;
+    }
+    pbs_status r;
+    if ((r = transport<T>(c, 0.5 * h, k, st)) != PBS_OK) return r;
+    if ((r = angular<T>(c, layer, h, k, st)) != PBS_OK) return r;
+    return transport<T>(c, 0.5 * h, k, st);
 }
 
 // the main stream waits for every generation's pending T A T
@@ -896,9 +931,7 @@ pbs_status extrapolated_step(pbs_ctx *c)
     auto strang = [&](double h, int row, bool pair_inside) -> pbs_status {
         pbs_status q;
         if ((q = energy_chain<T>(c, MODE_OPEN, -1, s, 0.5 * h, -1, -1, row)) != PBS_OK) return q;
-        if ((q = transport<T>(c, 0.5 * h)) != PBS_OK) return q;
-        if ((q = angular<T>(c, s, h)) != PBS_OK) return q;
-        if ((q = transport<T>(c, 0.5 * h)) != PBS_OK) return q;
+        if ((q = transport_angular<T>(c, s, h)) != PBS_OK) return q;
         if (pair_inside) return energy_chain<T>(c, MODE_PAIR, s, s, 0.5 * h, -1, row, row);
         return energy_chain<T>(c, MODE_CLOSE, s, -1, 0.5 * h, -1, row, -1);
     };
@@ -908,9 +941,7 @@ pbs_status extrapolated_step(pbs_ctx *c)
     HIPCHK(c, hipMemcpyAsync(psi, x0, n * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
     // B: two steps of dz/2 into row nz + 1 (the closing half of the first fused with the opening of the second)
     if ((r = strang(0.5 * dz, nz + 1, true)) != PBS_OK) return r;
-    if ((r = transport<T>(c, 0.25 * dz)) != PBS_OK) return r;
-    if ((r = angular<T>(c, s, 0.5 * dz)) != PBS_OK) return r;
-    if ((r = transport<T>(c, 0.25 * dz)) != PBS_OK) return r;
+    if ((r = transport_angular<T>(c, s, 0.5 * dz)) != PBS_OK) return r;
     if ((r = energy_chain<T>(c, MODE_CLOSE, s, -1, 0.25 * dz, -1, nz + 1, -1)) != PBS_OK) return r;
     HIPCHK(c, launch_combine<T>(psi, xA, T(4.0 / 3.0), T(-1.0 / 3.0), n, c->stream));
     HIPCHK(c, launch_fill<double>(c->edep(s), 0.0, c->NP, c->stream));
@@ -930,16 +961,12 @@ pbs_status one_step(pbs_ctx *c)
     const long cells = (long)c->NP * c->NA * c->G();
     const bool ovl = c->side && (c->sched == PBS_SCHED_TWO_STREAMS ||
                                  (c->sched == PBS_SCHED_AUTO && c->kact > 1 && cells < PBS_OVERLAP_CELLS &&
-                                  (c->NA >= 128 || cells >= PBS_OVERLAP_MIN)));
+                                  (c->NA >= 128 || cells >= PBS_OVERLAP_MIN) && !tat_fused<T>(c)));
     const int tat = ovl ? s : -1;
     pbs_status r = (s == 0) ? energy_chain<T>(c, MODE_OPEN, -1, 0, 0.5 * dz, tat)
                             : energy_chain<T>(c, MODE_PAIR, s - 1, s, 0.5 * dz, tat);
     if (r != PBS_OK) return r;
-    if (!ovl) {
-        if ((r = transport<T>(c, 0.5 * dz)) != PBS_OK) return r;
-        if ((r = angular<T>(c, s, dz)) != PBS_OK) return r;
-        if ((r = transport<T>(c, 0.5 * dz)) != PBS_OK) return r;
-    }
+    if (!ovl && (r = transport_angular<T>(c, s, dz)) != PBS_OK) return r;
     c->step = s + 1;
     return PBS_OK;
 }

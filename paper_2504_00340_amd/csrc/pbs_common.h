@@ -167,6 +167,9 @@ __host__ __device__ inline int epass8_slots(int NOCT) { return NOCT * (8 / PBS_E
 template <typename T> hipError_t launch_tpass(const TParams<T> &P, hipStream_t st);
 // Ktab: operand table of the MFMA forms (apass_mfma_table)
 template <typename T> hipError_t launch_apass(const AParams<T> &P, const T *Ktab, int nth, long nstack, hipStream_t st);
+// transport, angular step, transport of nstack slabs of nline values in one launch, where tat_fits
+template <typename T> bool tat_fits(int nth, int ny, long nline, long nstack);
+template <typename T> hipError_t launch_tat(const TParams<T> &P, const AParams<T> &A, int nth, long nstack, hipStream_t st);
 template <typename T> hipError_t launch_qgemm(const QParams<T> &P, hipStream_t st);
 template <typename T> hipError_t launch_fill(T *p, T v, long n, hipStream_t st);
 // y = a y + b x elementwise

@@ -2001,8 +2001,10 @@ static inline bool tpass_packed_fits(const TParams<T> &P)
 }
 
 // One plane per W lanes (W = 16, 32, 64; ny <= W); wave number from the caller, the same in all lanes.
-template <typename T, int W, int AUX>
-__device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wave)
+// make(first slab) -> {load(byte offset), store(value, byte offset)} of two slabs; an offset from 2^31 on is no cell's:
+// the load gives 0, the store is dropped.
+template <typename T, int W, typename MAKE>
+__device__ __forceinline__ void tpass_pack_planes(const TParams<T> &P, unsigned wave, MAKE make)
 {
     constexpr unsigned NPW = 64 / W, TS = sizeof(T), SH = TS == 4 ? 2 : 3;
     const unsigned pl0 = wave * NPW, nplanes = (unsigned)P.nplanes, NA = P.NA, m = P.m;
@@ -2025,8 +2027,7 @@ __device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wa
         if ((lane >> 4) & 1) m16 = pow_lane(c1, (lane & 15) + 1);
     if constexpr (W >= 64)
         if (lane >= 32) m32 = pow_lane(c1, (lane & 31) + 1);
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(P.psi + slab0 * P.NLINE), (short)0, (int)(2 * P.NLINE * TS), 0x00020000);
+    const auto mem = make(slab0);
     const unsigned K = PBS_PT * TS * (NA - 1);
     const unsigned base = live ? a * (PBS_PT * TS) + (next ? (unsigned)(P.NLINE * TS) : 0u) : 0x80000000u;
     const int step = live ? (mx ? -ny : ny) : 0;
@@ -2056,7 +2057,7 @@ __device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wa
     for (int i = 0; i < PF; ++i) {
         rb[i] = T(0);
         if (i < nx) {
-            rb[i] = buf_ld<T, AUX>(rs, addr(pld));
+            rb[i] = mem.load(addr(pld));
             pld += step;
         }
     }
@@ -2070,7 +2071,7 @@ __device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wa
         const T R = p0 - ax * (dxb + (dxp - dxm)) - ay * (dyb + (dyp - dym));
         T y = (R + ax * ym1) * idiag;
         scan_lanes<W>(y, c1, c2, c4, c8, m16, m32);
-        buf_st<AUX>(y, rs, addr(pst));
+        mem.store(y, addr(pst));
         pst += step;
         dxb = dxf;
         dxm = dxp;
@@ -2080,7 +2081,7 @@ __device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wa
     for (; r0 + 2 * PF <= nx; r0 += PF) {
 #pragma unroll
         for (int i = 0; i < PF; ++i) {
-            rb[PF + i] = buf_ld<T, AUX>(rs, addr(pld));
+            rb[PF + i] = mem.load(addr(pld));
             pld += step;
         }
 #pragma unroll
@@ -2094,7 +2095,7 @@ __device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wa
         for (int i = 0; i < PF; ++i) {
             rb[PF + i] = T(0);
             if (r0 + PF + i < nx) {
-                rb[PF + i] = buf_ld<T, AUX>(rs, addr(pld));
+                rb[PF + i] = mem.load(addr(pld));
                 pld += step;
             }
         }
@@ -2102,6 +2103,24 @@ __device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wa
         for (int i = 0; i < 2 * PF; ++i)
             if (r0 + i < nx) row(rb[i], i + 1 < 2 * PF ? rb[i + 1 < 2 * PF ? i + 1 : 0] : T(0));
     }
+}
+
+template <typename T, int AUX>
+struct SlabBuf {
+    __amdgpu_buffer_rsrc_t rs;
+    __device__ __forceinline__ SlabBuf(T *slab, long bytes)
+        : rs(__builtin_amdgcn_make_buffer_rsrc((void *)slab, (short)0, (int)bytes, 0x00020000))
+    {
+    }
+    __device__ __forceinline__ T load(unsigned o) const { return buf_ld<T, AUX>(rs, o); }
+    __device__ __forceinline__ void store(T v, unsigned o) const { buf_st<AUX>(v, rs, o); }
+};
+template <typename T, int W, int AUX>
+__device__ __forceinline__ void tpass_pack_body(const TParams<T> &P, unsigned wave)
+{
+    tpass_pack_planes<T, W>(P, wave, [&](unsigned slab0) {
+        return SlabBuf<T, AUX>(P.psi + slab0 * P.NLINE, 2 * P.NLINE * (long)sizeof(T));
+    });
 }
 
 // 64 < ny <= 96 (TWO: two planes in three operations, as tpass_wide2_body) or ny <= 128 (one plane in two).
@@ -2383,6 +2402,60 @@ __device__ __forceinline__ void dst1(const T (&x)[N - 1], T (&y)[N - 1], const T
     }
 }
 
+// The angular step of PC cells of ntile tiles (one: TILES = 1) in LDS, L0 = [tile][NA][PC], rho their densities;
+// all nt threads of the block, which sees the results after the barrier that ends it.
+template <typename T, int N, int PC, int TILES>
+__device__ __forceinline__ void apass_cells(const AParams<T> &P, T *L0, const T *rho, int g, int ntile, int nt)
+{
+    constexpr int m = N - 1, NA = m * m;
+    constexpr T inv2N = T(2) / T(N);
+    // forward transform over the first angular index for every (j, column)
+    for (int it = threadIdx.x; it < ntile * m * PC; it += nt) {
+        T *L = TILES == 1 ? L0 : L0 + it / (m * PC) * (NA * PC);
+        const int j = (TILES == 1 ? it : it % (m * PC)) / PC, c = it % PC;
+        T x[m], y[m];
+#pragma unroll
+        for (int i = 0; i < m; ++i) x[i] = L[(i * m + j) * PC + c];
+        dst1<T, N>(x, y, P.S);
+#pragma unroll
+        for (int k = 0; k < m; ++k) L[(k * m + j) * PC + c] = y[k];
+    }
+    __syncthreads();
+    // over the second index: forward, CN factor (1 + a lam)/(1 - a lam), inverse
+    const T coef = T(0.25) * P.h * P.sig[g];   // (h/2) * sigma_tr/2, times rho
+    for (int it = threadIdx.x; it < ntile * m * PC; it += nt) {
+        T *L = TILES == 1 ? L0 : L0 + it / (m * PC) * (NA * PC);
+        const int k = (TILES == 1 ? it : it % (m * PC)) / PC, c = it % PC;
+        const T al = coef * rho[TILES == 1 ? c : it / (m * PC) * PC + c];
+        const T lk = P.lam[k];
+        T x[m], y[m];
+#pragma unroll
+        for (int j = 0; j < m; ++j) x[j] = L[(k * m + j) * PC + c];
+        dst1<T, N>(x, y, P.S);
+#pragma unroll
+        for (int n = 0; n < m; ++n) {
+            const T lm = al * (lk + P.lam[n]);
+            y[n] = y[n] * (T(1) + lm) * fast_rcp(T(1) - lm);
+        }
+        dst1<T, N>(y, x, P.S);
+#pragma unroll
+        for (int j = 0; j < m; ++j) L[(k * m + j) * PC + c] = x[j] * inv2N;
+    }
+    __syncthreads();
+    // inverse over the first index
+    for (int it = threadIdx.x; it < ntile * m * PC; it += nt) {
+        T *L = TILES == 1 ? L0 : L0 + it / (m * PC) * (NA * PC);
+        const int j = (TILES == 1 ? it : it % (m * PC)) / PC, c = it % PC;
+        T x[m], y[m];
+#pragma unroll
+        for (int k = 0; k < m; ++k) x[k] = L[(k * m + j) * PC + c];
+        dst1<T, N>(x, y, P.S);
+#pragma unroll
+        for (int i = 0; i < m; ++i) L[(i * m + j) * PC + c] = y[i] * inv2N;
+    }
+    __syncthreads();
+}
+
 template <typename T, int N, int PC>
 __device__ __forceinline__ void apass_body(const AParams<T> &P, int bx, long by)
 {
@@ -2411,49 +2484,7 @@ __device__ __forceinline__ void apass_body(const AParams<T> &P, int bx, long by)
         }
     }
     __syncthreads();
-    constexpr T inv2N = T(2) / T(N);
-    // forward transform over the first angular index for every (j, column)
-    for (int it = tid; it < m * PC; it += 256) {
-        const int j = it / PC, c = it % PC;
-        T x[m], y[m];
-#pragma unroll
-        for (int i = 0; i < m; ++i) x[i] = L[(i * m + j) * PC + c];
-        dst1<T, N>(x, y, P.S);
-#pragma unroll
-        for (int k = 0; k < m; ++k) L[(k * m + j) * PC + c] = y[k];
-    }
-    __syncthreads();
-    // over the second index: forward, CN factor (1 + a lam)/(1 - a lam), inverse
-    const T coef = T(0.25) * P.h * P.sig[g];   // (h/2) * sigma_tr/2, times rho
-    for (int it = tid; it < m * PC; it += 256) {
-        const int k = it / PC, c = it % PC;
-        const T al = coef * P.rho[(long)pb * PBS_PT + c0 + c];
-        const T lk = P.lam[k];
-        T x[m], y[m];
-#pragma unroll
-        for (int j = 0; j < m; ++j) x[j] = L[(k * m + j) * PC + c];
-        dst1<T, N>(x, y, P.S);
-#pragma unroll
-        for (int n = 0; n < m; ++n) {
-            const T lm = al * (lk + P.lam[n]);
-            y[n] = y[n] * (T(1) + lm) * fast_rcp(T(1) - lm);
-        }
-        dst1<T, N>(y, x, P.S);
-#pragma unroll
-        for (int j = 0; j < m; ++j) L[(k * m + j) * PC + c] = x[j] * inv2N;
-    }
-    __syncthreads();
-    // inverse over the first index
-    for (int it = tid; it < m * PC; it += 256) {
-        const int j = it / PC, c = it % PC;
-        T x[m], y[m];
-#pragma unroll
-        for (int k = 0; k < m; ++k) x[k] = L[(k * m + j) * PC + c];
-        dst1<T, N>(x, y, P.S);
-#pragma unroll
-        for (int i = 0; i < m; ++i) L[(i * m + j) * PC + c] = y[i] * inv2N;
-    }
-    __syncthreads();
+    apass_cells<T, N, PC, 1>(P, L, P.rho + (long)pb * PBS_PT + c0, g, 1, 256);
     for (int idx = tid; idx < NA * PC; idx += 256) {
         const int a = idx / PC, c = idx % PC;
         blk[(long)a * PBS_PT + c] = L[idx];
@@ -2481,6 +2512,91 @@ static hipError_t launch_apass_n(const AParams<T> &P, long nstack, hipStream_t s
     case 8: hipLaunchKernelGGL((apass_kernel<T, N, 8>), grid, dim3(256), sh, st, P); break;
     case 4: hipLaunchKernelGGL((apass_kernel<T, N, 4>), grid, dim3(256), sh, st, P); break;
     default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// ------------------------------------------- transport, angular step, transport of a small slab in one launch
+// The three passes between two energy sweeps read and write the fluence once each, and on the smallest grids each
+// of them is a launch of a few microseconds that waits for its loads.  One block holds a whole (group, coefficient)
+// slab of a generation in LDS: the transport sweeps of its planes read it from memory, the angular step of its
+// cells works in place, the second transport writes it back.  The arithmetic is that of the passes by themselves.
+// 1024 threads, for the loads in flight: 512 cost 2 us more.  Whole steps, us, three launches -> one:
+// 4 x 4 cells, 11 x 11 angles, 60 groups, 2 generations 64 -> 59 (FP64 84 -> 76); 16 x 16, 7 x 7, 48 71 -> 61
+// (FP64 86 -> 73); 32 x 32, 5 x 5, 60 97 -> 80; 16 x 16, 11 x 11, 48 90 (two streams) -> 86.
+constexpr int TAT_NT = 1024;
+constexpr long TAT_SLAB = 131072;   // bytes of a slab held in LDS (of 160 KB)
+template <typename T>
+struct SlabLds {
+    char *p;
+    unsigned zero, dump;   // beyond the slab: a zero to load, a place to store to, for lanes without a cell
+    __device__ __forceinline__ T load(unsigned o) const { return *reinterpret_cast<const T *>(p + min(o, zero)); }
+    __device__ __forceinline__ void store(T v, unsigned o) const { *reinterpret_cast<T *>(p + min(o, dump)) = v; }
+};
+template <typename T, typename FROM, typename TO>
+struct SlabMove {
+    FROM from;
+    TO to;
+    __device__ __forceinline__ T load(unsigned o) const { return from.load(o); }
+    __device__ __forceinline__ void store(T v, unsigned o) const { to.store(v, o); }
+};
+
+template <typename T, int N, int W>
+__global__ __launch_bounds__(TAT_NT) void tat_kernel(TParams<T> P, AParams<T> A)
+{
+    constexpr int NA = (N - 1) * (N - 1);
+    extern __shared__ char smem_raw[];
+    const long stack = blockIdx.x;   // (k*G + g)*2 + l
+    const unsigned bytes = (unsigned)(P.NLINE * (long)sizeof(T));
+    const SlabLds<T> lds{smem_raw, bytes, bytes + 8};
+    const SlabBuf<T, 0> buf(P.psi + stack * P.NLINE, bytes);
+    T *L = reinterpret_cast<T *>(smem_raw);
+    // cells that pad the last tile, and the zero
+    const int np = P.nx * P.ny, npad = A.NPB * PBS_PT - np;
+    for (int i = threadIdx.x; i < npad * NA; i += TAT_NT)
+        L[((long)(A.NPB - 1) * NA + i / npad) * PBS_PT + PBS_PT - npad + i % npad] = T(0);
+    if (threadIdx.x == 0) *reinterpret_cast<T *>(smem_raw + bytes) = T(0);
+    P.nplanes = NA;
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (unsigned w = wave; w < (NA * W + 63) / 64; w += TAT_NT / 64)
+        tpass_pack_planes<T, W>(P, w, [&](unsigned) { return SlabMove<T, SlabBuf<T, 0>, SlabLds<T>>{buf, lds}; });
+    __syncthreads();
+    apass_cells<T, N, PBS_PT, 0>(A, L, A.rho, (int)((stack / 2) % A.G), A.NPB, TAT_NT);
+    for (unsigned w = wave; w < (NA * W + 63) / 64; w += TAT_NT / 64)
+        tpass_pack_planes<T, W>(P, w, [&](unsigned) { return SlabMove<T, SlabLds<T>, SlabBuf<T, 0>>{lds, buf}; });
+}
+
+// All slabs have to fit the chip at once (256 CUs, two blocks a CU where LDS holds two slabs): a second round costs
+// what the launches save (16 x 16, 9 x 9, 100, 3 generations of 81 KB: 183 us a step against 177).  Fewer than 96 leave
+// too many CUs idle (5 x 7, 11 x 11, 40, one generation: 80 slabs, 32 against 31 us; 60: 36.7 against 37.7).
+template <typename T>
+bool tat_fits(int nth, int ny, long nline, long nstack)
+{
+    const long bytes = nline * (long)sizeof(T);
+    if (nth != 6 && nth != 8 && nth != 10 && nth != 12) return false;
+    if (ny > (sizeof(T) == 8 && nth >= 10 ? 16 : 32)) return false;   // registers of 1024 threads
+    return bytes <= TAT_SLAB && nstack >= 96 && nstack <= (bytes < 81000 ? 512 : 256);
+}
+template <typename T, int N>
+static void launch_tat_n(const TParams<T> &P, const AParams<T> &A, long nstack, hipStream_t st)
+{
+    const size_t sh = P.NLINE * sizeof(T) + 16;
+    if (P.ny <= 16) {
+        hipLaunchKernelGGL((tat_kernel<T, N, 16>), dim3((unsigned)nstack), dim3(TAT_NT), sh, st, P, A);
+    } else {
+        if constexpr (sizeof(T) == 4 || N < 10)
+            hipLaunchKernelGGL((tat_kernel<T, N, 32>), dim3((unsigned)nstack), dim3(TAT_NT), sh, st, P, A);
+    }
+}
+template <typename T>
+hipError_t launch_tat(const TParams<T> &P, const AParams<T> &A, int nth, long nstack, hipStream_t st)
+{
+    if (!tat_fits<T>(nth, P.ny, P.NLINE, nstack) || P.NA != (nth - 1) * (nth - 1)) return hipErrorInvalidValue;
+    switch (nth) {
+    case 6: launch_tat_n<T, 6>(P, A, nstack, st); break;
+    case 8: launch_tat_n<T, 8>(P, A, nstack, st); break;
+    case 10: launch_tat_n<T, 10>(P, A, nstack, st); break;
+    default: launch_tat_n<T, 12>(P, A, nstack, st); break;
     }
     return hipGetLastError();
 }
@@ -4057,6 +4173,8 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
     template hipError_t launch_epass<T>(const EParams<T> &, int, hipStream_t);                                \
     template hipError_t launch_tpass<T>(const TParams<T> &, hipStream_t);                                     \
     template hipError_t launch_apass<T>(const AParams<T> &, const T *, int, long, hipStream_t);                        \
+    template bool tat_fits<T>(int, int, long, long);                                                           \
+    template hipError_t launch_tat<T>(const TParams<T> &, const AParams<T> &, int, long, hipStream_t);                 \
     template hipError_t launch_qgemm<T>(const QParams<T> &, hipStream_t);                                     \
     template hipError_t launch_fill<T>(T *, T, long, hipStream_t);                                            \
     template hipError_t launch_initial<T>(T *, const double *, const double *, const double *, long, int, int, \

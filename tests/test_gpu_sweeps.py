@@ -190,3 +190,28 @@ def test_angular_step(O, nx, ny, nth, prec):
     got = s.state()
     s.close()
     _check(got, ref, prec, "angular")
+
+
+# T A T of a small slab in one launch (one stream) against its three passes (two streams), whose bits it has: every
+# angular count it takes, one and two planes per 32 lanes, partly filled and several tiles, the fewest slabs and the most
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,nth,ng,ngen", [(1, 1, 6, 48, 1), (3, 5, 8, 24, 2), (4, 4, 12, 50, 2), (2, 16, 10, 128, 2),
+                                               (5, 16, 12, 64, 1), (3, 17, 8, 64, 4), (2, 32, 6, 50, 2), (9, 31, 6, 60, 2),
+                                               (2, 30, 10, 48, 1), (1, 32, 12, 64, 2)])
+def test_small_slabs_in_one_launch(nx, ny, nth, ng, ngen, prec):
+    from paper_2504_00340_amd import pbsplit as P
+
+    print("case one launch", nx, ny, nth, ng, ngen, prec, flush=True)
+    c = I.small(nz=4, seed=3, nx=nx, ny=ny, nth=nth, ng=ng, ngen=ngen)
+    out = []
+    for mode in (P.PBS_SCHED_ONE_STREAM, P.PBS_SCHED_TWO_STREAMS):
+        s = P.Solver(c["grid"], c["phys"], precision=prec)
+        s.set_schedule(mode)
+        s.set_phantom(c["rho"])
+        s.set_beam(c["beam"])
+        s.set_state(I.random_state(s.state_shape, 3))
+        s.step(3)
+        out.append((s.state(), s.dose()))
+        s.close()
+    assert np.isfinite(out[0][0]).all()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
