@@ -724,7 +724,7 @@ pbs_status transport(pbs_ctx *c, double h, int k = -1, hipStream_t st = nullptr)
 template <typename T>
 pbs_status angular(pbs_ctx *c, int layer, double h, int k = -1, hipStream_t st = nullptr);
 template <typename T>
-pbs_status transport_angular(pbs_ctx *c, int layer, double h, int k = -1, hipStream_t st = nullptr);
+pbs_status transport_angular(pbs_ctx *c, int layer, double h, int k = -1, hipStream_t st = nullptr, const DoseJobs &J = {});
 
 // Energy half-step(s) for all generations in order.  mode: close the layer lay_c (state 0 -> 1),
 // open the layer lay_o (state 1 -> 2), or both in one sweep.  Deposits go to the FP64 dose.
@@ -733,9 +733,10 @@ pbs_status transport_angular(pbs_ctx *c, int layer, double h, int k = -1, hipStr
 // as its energy pass is done: it touches only that generation's fluence, while the main stream goes on
 // with k's source product and the later generations' energy passes.  A generation's next energy pass
 // waits for its pending T A T; the march joins the side stream back at its end (join_side).
+// later: the dose reductions are handed over there, for the launch of T A T, instead of being launched.
 template <typename T>
 pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, int tat_layer = -1, int row_c = -1,
-                        int row_o = -1)
+                        int row_o = -1, DoseJobs *later = nullptr)
 {
     // deposits go to the dose rows of the layers unless other rows are named (the extrapolated march)
     if (row_c < 0) row_c = lay_c;
@@ -806,6 +807,7 @@ pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, in
     }
     ProfScope ps(c, PBS_K_DOSE);
     DoseJobs J;
+    J.nslot = nslot;
     if (mode & MODE_CLOSE) J.add(c->edep(row_c), c->dep(0, 0), K1);
     if (mode & MODE_OPEN) J.add(c->edep(row_o), c->dep(1, 0), K1);
     if (c->feat_on) {
@@ -822,7 +824,8 @@ pbs_status energy_chain(pbs_ctx *c, int mode, int lay_c, int lay_o, double h, in
             if (K1 > 1) J.add(c->frec(3, lay_o), c->dep(1, 0), 1);
         }
     }
-    HIPCHK(c, launch_dose_reduce(J, c->NA, nslot, c->NLINE, c->NP, c->stream));
+    if (later) *later = J;
+    else HIPCHK(c, launch_dose_reduce(J, c->NA, c->NLINE, c->NP, c->stream));
     return PBS_OK;
 }
 
@@ -889,13 +892,13 @@ bool tat_fused(const pbs_ctx *c)
     return !c->prof && tat_fits<T>(c->g.nth, c->g.ny, c->NLINE, slabs(c, -1));
 }
 
-// T(h/2) A(h) T(h/2)
+// T(h/2) A(h) T(h/2), and the dose reductions J if it is fused
 template <typename T>
-pbs_status transport_angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st)
+pbs_status transport_angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st, const DoseJobs &J)
 {
     if (!st) st = c->stream;
     if (k < 0 && tat_fused<T>(c)) {
-        HIPCHK(c, launch_tat<T>(tparams<T>(c, 0.5 * h, k), aparams<T>(c, layer, h, k), c->g.nth, slabs(c, k), st));
+        HIPCHK(c, launch_tat<T>(tparams<T>(c, 0.5 * h, k), aparams<T>(c, layer, h, k), c->g.nth, slabs(c, k), J, st));
         return PBS_OK;
     }
     pbs_status r;
@@ -963,10 +966,12 @@ pbs_status one_step(pbs_ctx *c)
                                  (c->sched == PBS_SCHED_AUTO && c->kact > 1 && cells < PBS_OVERLAP_CELLS &&
                                   (c->NA >= 128 || cells >= PBS_OVERLAP_MIN) && !tat_fused<T>(c)));
     const int tat = ovl ? s : -1;
-    pbs_status r = (s == 0) ? energy_chain<T>(c, MODE_OPEN, -1, 0, 0.5 * dz, tat)
-                            : energy_chain<T>(c, MODE_PAIR, s - 1, s, 0.5 * dz, tat);
+    DoseJobs J;
+    DoseJobs *later = !ovl && tat_fused<T>(c) ? &J : nullptr;
+    pbs_status r = (s == 0) ? energy_chain<T>(c, MODE_OPEN, -1, 0, 0.5 * dz, tat, -1, -1, later)
+                            : energy_chain<T>(c, MODE_PAIR, s - 1, s, 0.5 * dz, tat, -1, -1, later);
     if (r != PBS_OK) return r;
-    if (!ovl && (r = transport_angular<T>(c, s, dz)) != PBS_OK) return r;
+    if (!ovl && (r = transport_angular<T>(c, s, dz, -1, nullptr, J)) != PBS_OK) return r;
     c->step = s + 1;
     return PBS_OK;
 }

@@ -167,22 +167,23 @@ __host__ __device__ inline int epass8_slots(int NOCT) { return NOCT * (8 / PBS_E
 template <typename T> hipError_t launch_tpass(const TParams<T> &P, hipStream_t st);
 // Ktab: operand table of the MFMA forms (apass_mfma_table)
 template <typename T> hipError_t launch_apass(const AParams<T> &P, const T *Ktab, int nth, long nstack, hipStream_t st);
-// transport, angular step, transport of nstack slabs of nline values in one launch, where tat_fits
-template <typename T> bool tat_fits(int nth, int ny, long nline, long nstack);
-template <typename T> hipError_t launch_tat(const TParams<T> &P, const AParams<T> &A, int nth, long nstack, hipStream_t st);
-template <typename T> hipError_t launch_qgemm(const QParams<T> &P, hipStream_t st);
-template <typename T> hipError_t launch_fill(T *p, T v, long n, hipStream_t st);
-// y = a y + b x elementwise
-template <typename T> hipError_t launch_combine(T *y, const T *x, T a, T b, long n, hipStream_t st);
-// row[j][pq] += sum over ngen[j] generations and the first nslot angular slots of dep[j], j < n, in one launch
+// row[j][pq] += sum over ngen[j] generations and the first nslot angular slots of dep[j], j < n
 struct DoseJobs {
-    int n = 0;
+    int n = 0, nslot = 0;
     double *row[8];
     const double *dep[8];
     int ngen[8];
     void add(double *r, const double *d, int k) { row[n] = r, dep[n] = d, ngen[n] = k, ++n; }
 };
-hipError_t launch_dose_reduce(const DoseJobs &J, int NA, int nslot, long NLINE, int NP, hipStream_t st);
+hipError_t launch_dose_reduce(const DoseJobs &J, int NA, long NLINE, int NP, hipStream_t st);
+// transport, angular step, transport of nstack slabs of nline values in one launch, where tat_fits, with the dose
+// reductions J (rows that differ) beside them
+template <typename T> bool tat_fits(int nth, int ny, long nline, long nstack);
+template <typename T> hipError_t launch_tat(const TParams<T> &P, const AParams<T> &A, int nth, long nstack, const DoseJobs &J, hipStream_t st);
+template <typename T> hipError_t launch_qgemm(const QParams<T> &P, hipStream_t st);
+template <typename T> hipError_t launch_fill(T *p, T v, long n, hipStream_t st);
+// y = a y + b x elementwise
+template <typename T> hipError_t launch_combine(T *y, const T *x, T a, T b, long n, hipStream_t st);
 hipError_t launch_dose_finalize(double *out, const double *edep, const double *rho, double vol, long n,
                                 hipStream_t st);
 template <typename T>

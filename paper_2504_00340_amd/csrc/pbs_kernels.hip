@@ -2375,6 +2375,7 @@ hipError_t launch_tpass(const TParams<T> &P, hipStream_t st)
 // ----------------------------------------------------------------------------- angular pass
 // y_M = sum_n sin(pi M n / N) x_n over the interior nodes n, M = 1..N-1, with the even/odd split
 // sin(pi M (N-n)/N) = (-1)^(M+1) sin(pi M n/N).  S[(M-1)*(N-1) + (n-1)] holds the sines.
+// They are scalar loads by tab(): left to the compiler, a kernel that stores before them reads them per lane and spills.
 template <typename T, int N>
 __device__ __forceinline__ void dst1(const T (&x)[N - 1], T (&y)[N - 1], const T *__restrict__ S)
 {
@@ -2390,14 +2391,14 @@ __device__ __forceinline__ void dst1(const T (&x)[N - 1], T (&y)[N - 1], const T
     for (int M = 1; M < N; M += 2) {   // odd modes: symmetric part + centre node
         T acc = T(0);
 #pragma unroll
-        for (int n = 1; n <= H; ++n) acc += S[(M - 1) * (N - 1) + (n - 1)] * sp[n - 1];
+        for (int n = 1; n <= H; ++n) acc += tab(S, (M - 1) * (N - 1) + (n - 1)) * sp[n - 1];
         y[M - 1] = acc;
     }
 #pragma unroll
     for (int M = 2; M < N; M += 2) {   // even modes: antisymmetric part
         T acc = T(0);
 #pragma unroll
-        for (int n = 1; n < H; ++n) acc += S[(M - 1) * (N - 1) + (n - 1)] * dm[n - 1];
+        for (int n = 1; n < H; ++n) acc += tab(S, (M - 1) * (N - 1) + (n - 1)) * dm[n - 1];
         y[M - 1] = acc;
     }
 }
@@ -2541,10 +2542,20 @@ struct SlabMove {
     __device__ __forceinline__ void store(T v, unsigned o) const { to.store(v, o); }
 };
 
+__device__ __forceinline__ void dose_reduce_body(double *edep, const double *dep, int ngen, int NA, int nslot,
+                                                 long NLINE, int NP, int pb);
+
+// blocks 0 .. nstack - 1: one slab each; those after them: the step's dose reductions, a job and lateral tile each
 template <typename T, int N, int W>
-__global__ __launch_bounds__(TAT_NT) void tat_kernel(TParams<T> P, AParams<T> A)
+__global__ __launch_bounds__(TAT_NT) void tat_kernel(TParams<T> P, AParams<T> A, int nstack, DoseJobs J)
 {
     constexpr int NA = (N - 1) * (N - 1);
+    if ((int)blockIdx.x >= nstack) {
+        const int q = blockIdx.x - nstack, j = q / A.NPB;
+        if (threadIdx.x < 256)
+            dose_reduce_body(J.row[j], J.dep[j], J.ngen[j], NA, J.nslot, P.NLINE, P.nx * P.ny, q % A.NPB);
+        return;
+    }
     extern __shared__ char smem_raw[];
     const long stack = blockIdx.x;   // (k*G + g)*2 + l
     const unsigned bytes = (unsigned)(P.NLINE * (long)sizeof(T));
@@ -2575,28 +2586,29 @@ bool tat_fits(int nth, int ny, long nline, long nstack)
     const long bytes = nline * (long)sizeof(T);
     if (nth != 6 && nth != 8 && nth != 10 && nth != 12) return false;
     if (ny > (sizeof(T) == 8 && nth >= 10 ? 16 : 32)) return false;   // registers of 1024 threads
-    return bytes <= TAT_SLAB && nstack >= 96 && nstack <= (bytes < 81000 ? 512 : 256);
+    return bytes <= TAT_SLAB && nstack >= 96 && nstack <= (bytes < 80000 ? 512 : 256);
 }
 template <typename T, int N>
-static void launch_tat_n(const TParams<T> &P, const AParams<T> &A, long nstack, hipStream_t st)
+static void launch_tat_n(const TParams<T> &P, const AParams<T> &A, long nstack, const DoseJobs &J, hipStream_t st)
 {
+    const dim3 grid((unsigned)(nstack + (long)J.n * A.NPB));
     const size_t sh = P.NLINE * sizeof(T) + 16;
     if (P.ny <= 16) {
-        hipLaunchKernelGGL((tat_kernel<T, N, 16>), dim3((unsigned)nstack), dim3(TAT_NT), sh, st, P, A);
+        hipLaunchKernelGGL((tat_kernel<T, N, 16>), grid, dim3(TAT_NT), sh, st, P, A, (int)nstack, J);
     } else {
         if constexpr (sizeof(T) == 4 || N < 10)
-            hipLaunchKernelGGL((tat_kernel<T, N, 32>), dim3((unsigned)nstack), dim3(TAT_NT), sh, st, P, A);
+            hipLaunchKernelGGL((tat_kernel<T, N, 32>), grid, dim3(TAT_NT), sh, st, P, A, (int)nstack, J);
     }
 }
 template <typename T>
-hipError_t launch_tat(const TParams<T> &P, const AParams<T> &A, int nth, long nstack, hipStream_t st)
+hipError_t launch_tat(const TParams<T> &P, const AParams<T> &A, int nth, long nstack, const DoseJobs &J, hipStream_t st)
 {
     if (!tat_fits<T>(nth, P.ny, P.NLINE, nstack) || P.NA != (nth - 1) * (nth - 1)) return hipErrorInvalidValue;
     switch (nth) {
-    case 6: launch_tat_n<T, 6>(P, A, nstack, st); break;
-    case 8: launch_tat_n<T, 8>(P, A, nstack, st); break;
-    case 10: launch_tat_n<T, 10>(P, A, nstack, st); break;
-    default: launch_tat_n<T, 12>(P, A, nstack, st); break;
+    case 6: launch_tat_n<T, 6>(P, A, nstack, J, st); break;
+    case 8: launch_tat_n<T, 8>(P, A, nstack, J, st); break;
+    case 10: launch_tat_n<T, 10>(P, A, nstack, J, st); break;
+    default: launch_tat_n<T, 12>(P, A, nstack, J, st); break;
     }
     return hipGetLastError();
 }
@@ -3759,13 +3771,13 @@ __device__ __forceinline__ void dose_reduce_body(double *edep, const double *dep
 }
 
 // blockIdx.y picks the reduction: rows that differ, so that the blocks of one launch never meet
-__global__ __launch_bounds__(256) void dose_reduce_kernel(DoseJobs J, int NA, int nslot, long NLINE, int NP)
+__global__ __launch_bounds__(256) void dose_reduce_kernel(DoseJobs J, int NA, long NLINE, int NP)
 {
     const int j = blockIdx.y;
-    dose_reduce_body(J.row[j], J.dep[j], J.ngen[j], NA, nslot, NLINE, NP, blockIdx.x);
+    dose_reduce_body(J.row[j], J.dep[j], J.ngen[j], NA, J.nslot, NLINE, NP, blockIdx.x);
 }
 
-hipError_t launch_dose_reduce(const DoseJobs &J, int NA, int nslot, long NLINE, int NP, hipStream_t st)
+hipError_t launch_dose_reduce(const DoseJobs &J, int NA, long NLINE, int NP, hipStream_t st)
 {
     if (J.n <= 0) return hipSuccess;
     for (int i = 0; i < J.n; ++i)
@@ -3776,11 +3788,11 @@ hipError_t launch_dose_reduce(const DoseJobs &J, int NA, int nslot, long NLINE, 
                 A.n = j;
                 B.n = J.n - j;
                 for (int q = 0; q < B.n; ++q) B.row[q] = J.row[j + q], B.dep[q] = J.dep[j + q], B.ngen[q] = J.ngen[j + q];
-                const hipError_t e = launch_dose_reduce(A, NA, nslot, NLINE, NP, st);
-                return e != hipSuccess ? e : launch_dose_reduce(B, NA, nslot, NLINE, NP, st);
+                const hipError_t e = launch_dose_reduce(A, NA, NLINE, NP, st);
+                return e != hipSuccess ? e : launch_dose_reduce(B, NA, NLINE, NP, st);
             }
     const int npb = (NP + PBS_PT - 1) / PBS_PT;
-    hipLaunchKernelGGL(dose_reduce_kernel, dim3(npb, J.n), dim3(256), 0, st, J, NA, nslot, NLINE, NP);
+    hipLaunchKernelGGL(dose_reduce_kernel, dim3(npb, J.n), dim3(256), 0, st, J, NA, NLINE, NP);
     return hipGetLastError();
 }
 
@@ -4174,7 +4186,7 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
     template hipError_t launch_tpass<T>(const TParams<T> &, hipStream_t);                                     \
     template hipError_t launch_apass<T>(const AParams<T> &, const T *, int, long, hipStream_t);                        \
     template bool tat_fits<T>(int, int, long, long);                                                           \
-    template hipError_t launch_tat<T>(const TParams<T> &, const AParams<T> &, int, long, hipStream_t);                 \
+    template hipError_t launch_tat<T>(const TParams<T> &, const AParams<T> &, int, long, const DoseJobs &, hipStream_t); \
     template hipError_t launch_qgemm<T>(const QParams<T> &, hipStream_t);                                     \
     template hipError_t launch_fill<T>(T *, T, long, hipStream_t);                                            \
     template hipError_t launch_initial<T>(T *, const double *, const double *, const double *, long, int, int, \
