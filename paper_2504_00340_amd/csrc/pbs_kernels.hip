@@ -2876,6 +2876,7 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
         lamO[q] = r < H ? P.lam[SPLIT ? 2 * r : r] : T(0);
         lamE[q] = SPLIT && r < HE ? P.lam[2 * r + 1] : T(0);
     }
+    constexpr T sc = T(2) / T(N);   // after each inverse: values below the normal range round as in the other passes
     const T al = T(0.25) * P.h * P.sig[g] * P.rho[(long)pb * PBS_PT + c0 + cc];
     // a line's operand at step s: node ip, and its mirror image folded in by parity
     auto fold = [&](const T *x, int stride, int s, T &o, T &e) {
@@ -2945,19 +2946,18 @@ __device__ __forceinline__ void apass_mfma_body(const AParams<T> &P, const T *__
             const int jp = 4 * q + r4;
             if constexpr (SPLIT) {
                 if (jp < HE) {
-                    x[jp * 16] = u[q] + v[q];
-                    x[(m - 1 - jp) * 16] = u[q] - v[q];
+                    x[jp * 16] = (u[q] + v[q]) * sc;
+                    x[(m - 1 - jp) * 16] = (u[q] - v[q]) * sc;
                 } else if (jp == H - 1) {
-                    x[jp * 16] = u[q];
+                    x[jp * 16] = u[q] * sc;
                 }
             } else if (jp < m) {
-                x[jp * 16] = u[q];
+                x[jp * 16] = u[q] * sc;
             }
         }
     }
     __syncthreads();
-    // inverse over the first index, with the (2/N)^2 normalisation
-    constexpr T sc = (T(2) / T(N)) * (T(2) / T(N));
+    // inverse over the first index
     for (int j = wid; j < m; j += NT / 64) {
         T *x = &L[j * 16 + cc];
         T4 u = {0, 0, 0, 0}, v = {0, 0, 0, 0};
