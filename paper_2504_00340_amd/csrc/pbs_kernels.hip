@@ -2403,17 +2403,17 @@ __device__ __forceinline__ void dst1(const T (&x)[N - 1], T (&y)[N - 1], const T
     }
 }
 
-// The angular step of PC cells of ntile tiles (one: TILES = 1) in LDS, L0 = [tile][NA][PC], rho their densities;
+// The angular step of ntile lateral tiles (ONE: one) in LDS, L0 = [tile][NA][PC], rho their densities;
 // all nt threads of the block, which sees the results after the barrier that ends it.
-template <typename T, int N, int PC, int TILES>
+template <typename T, int N, bool ONE>
 __device__ __forceinline__ void apass_cells(const AParams<T> &P, T *L0, const T *rho, int g, int ntile, int nt)
 {
-    constexpr int m = N - 1, NA = m * m;
+    constexpr int m = N - 1, NA = m * m, PC = PBS_PT;
     constexpr T inv2N = T(2) / T(N);
     // forward transform over the first angular index for every (j, column)
     for (int it = threadIdx.x; it < ntile * m * PC; it += nt) {
-        T *L = TILES == 1 ? L0 : L0 + it / (m * PC) * (NA * PC);
-        const int j = (TILES == 1 ? it : it % (m * PC)) / PC, c = it % PC;
+        T *L = ONE ? L0 : L0 + it / (m * PC) * (NA * PC);
+        const int j = (ONE ? it : it % (m * PC)) / PC, c = it % PC;
         T x[m], y[m];
 #pragma unroll
         for (int i = 0; i < m; ++i) x[i] = L[(i * m + j) * PC + c];
@@ -2425,9 +2425,9 @@ __device__ __forceinline__ void apass_cells(const AParams<T> &P, T *L0, const T 
     // over the second index: forward, CN factor (1 + a lam)/(1 - a lam), inverse
     const T coef = T(0.25) * P.h * P.sig[g];   // (h/2) * sigma_tr/2, times rho
     for (int it = threadIdx.x; it < ntile * m * PC; it += nt) {
-        T *L = TILES == 1 ? L0 : L0 + it / (m * PC) * (NA * PC);
-        const int k = (TILES == 1 ? it : it % (m * PC)) / PC, c = it % PC;
-        const T al = coef * rho[TILES == 1 ? c : it / (m * PC) * PC + c];
+        T *L = ONE ? L0 : L0 + it / (m * PC) * (NA * PC);
+        const int k = (ONE ? it : it % (m * PC)) / PC, c = it % PC;
+        const T al = coef * rho[ONE ? c : it / (m * PC) * PC + c];
         const T lk = P.lam[k];
         T x[m], y[m];
 #pragma unroll
@@ -2445,8 +2445,8 @@ __device__ __forceinline__ void apass_cells(const AParams<T> &P, T *L0, const T 
     __syncthreads();
     // inverse over the first index
     for (int it = threadIdx.x; it < ntile * m * PC; it += nt) {
-        T *L = TILES == 1 ? L0 : L0 + it / (m * PC) * (NA * PC);
-        const int j = (TILES == 1 ? it : it % (m * PC)) / PC, c = it % PC;
+        T *L = ONE ? L0 : L0 + it / (m * PC) * (NA * PC);
+        const int j = (ONE ? it : it % (m * PC)) / PC, c = it % PC;
         T x[m], y[m];
 #pragma unroll
         for (int k = 0; k < m; ++k) x[k] = L[(k * m + j) * PC + c];
@@ -2457,63 +2457,39 @@ __device__ __forceinline__ void apass_cells(const AParams<T> &P, T *L0, const T 
     __syncthreads();
 }
 
-template <typename T, int N, int PC>
-__device__ __forceinline__ void apass_body(const AParams<T> &P, int bx, long by)
+// one lateral tile of one slab per block
+template <typename T, int N>
+__global__ __launch_bounds__(256) void apass_kernel(AParams<T> P)
 {
-    constexpr int m = N - 1;
-    constexpr int NA = m * m;
-    extern __shared__ char smem_raw[];
-    T *L = reinterpret_cast<T *>(smem_raw);   // [NA][PC]
+    constexpr int NA = (N - 1) * (N - 1), NV = NA * PBS_PT;
+    __shared__ T L[NV];              // [NA][PBS_PT]
     const int tid = threadIdx.x;
-    const long stack = by;           // (k*G + g)*2 + l
-    const int g = (int)((stack / 2) % P.G);
-    const int pb = bx / (PBS_PT / PC);
-    const int c0 = (bx % (PBS_PT / PC)) * PC;
-    T *blk = P.psi + stack * P.NLINE + (long)pb * NA * PBS_PT + c0;
+    const long stack = blockIdx.y;   // (k*G + g)*2 + l
+    const int g = (int)((stack / 2) % P.G), pb = blockIdx.x;
+    T *blk = P.psi + stack * P.NLINE + (long)pb * NV;
     // 8 loads in flight per thread before their LDS stores (a load-store loop waits for each in turn)
-    for (int i0 = tid; i0 < NA * PC; i0 += 8 * 256) {
+    for (int i0 = tid; i0 < NV; i0 += 8 * 256) {
         T v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int idx = i0 + u * 256;
-            if (idx < NA * PC) v[u] = blk[(long)(idx / PC) * PBS_PT + idx % PC];
+            if (idx < NV) v[u] = blk[idx];
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int idx = i0 + u * 256;
-            if (idx < NA * PC) L[idx] = v[u];
+            if (idx < NV) L[idx] = v[u];
         }
     }
     __syncthreads();
-    apass_cells<T, N, PC, 1>(P, L, P.rho + (long)pb * PBS_PT + c0, g, 1, 256);
-    for (int idx = tid; idx < NA * PC; idx += 256) {
-        const int a = idx / PC, c = idx % PC;
-        blk[(long)a * PBS_PT + c] = L[idx];
-    }
-}
-
-template <typename T, int N, int PC>
-__global__ __launch_bounds__(256) void apass_kernel(AParams<T> P)
-{
-    apass_body<T, N, PC>(P, blockIdx.x, blockIdx.y);
+    apass_cells<T, N, true>(P, L, P.rho + (long)pb * PBS_PT, g, 1, 256);
+    for (int idx = tid; idx < NV; idx += 256) blk[idx] = L[idx];
 }
 
 template <typename T, int N>
 static hipError_t launch_apass_n(const AParams<T> &P, long nstack, hipStream_t st)
 {
-    constexpr int NA = (N - 1) * (N - 1);
-    const size_t lim = 64 * 1024;
-    int pc = 32;
-    while (pc > 1 && (size_t)NA * pc * sizeof(T) > lim) pc /= 2;
-    dim3 grid((unsigned)(P.NPB * (PBS_PT / pc)), (unsigned)nstack);
-    const size_t sh = (size_t)NA * pc * sizeof(T);
-    switch (pc) {
-    case 32: hipLaunchKernelGGL((apass_kernel<T, N, 32>), grid, dim3(256), sh, st, P); break;
-    case 16: hipLaunchKernelGGL((apass_kernel<T, N, 16>), grid, dim3(256), sh, st, P); break;
-    case 8: hipLaunchKernelGGL((apass_kernel<T, N, 8>), grid, dim3(256), sh, st, P); break;
-    case 4: hipLaunchKernelGGL((apass_kernel<T, N, 4>), grid, dim3(256), sh, st, P); break;
-    default: return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL((apass_kernel<T, N>), dim3(P.NPB, (unsigned)nstack), dim3(256), 0, st, P);
     return hipGetLastError();
 }
 
@@ -2572,7 +2548,7 @@ __global__ __launch_bounds__(TAT_NT) void tat_kernel(TParams<T> P, AParams<T> A,
     for (unsigned w = wave; w < (NA * W + 63) / 64; w += TAT_NT / 64)
         tpass_pack_planes<T, W>(P, w, [&](unsigned) { return SlabMove<T, SlabBuf<T, 0>, SlabLds<T>>{buf, lds}; });
     __syncthreads();
-    apass_cells<T, N, PBS_PT, 0>(A, L, A.rho, (int)((stack / 2) % A.G), A.NPB, TAT_NT);
+    apass_cells<T, N, false>(A, L, A.rho, (int)((stack / 2) % A.G), A.NPB, TAT_NT);
     for (unsigned w = wave; w < (NA * W + 63) / 64; w += TAT_NT / 64)
         tpass_pack_planes<T, W>(P, w, [&](unsigned) { return SlabMove<T, SlabLds<T>, SlabBuf<T, 0>>{lds, buf}; });
 }
