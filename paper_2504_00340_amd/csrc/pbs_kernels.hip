@@ -2528,8 +2528,7 @@ __global__ __launch_bounds__(TAT_NT) void tat_kernel(TParams<T> P, AParams<T> A,
     constexpr int NA = (N - 1) * (N - 1);
     if ((int)blockIdx.x >= nstack) {
         const int q = blockIdx.x - nstack, j = q / A.NPB;
-        if (threadIdx.x < 256)
-            dose_reduce_body(J.row[j], J.dep[j], J.ngen[j], NA, J.nslot, P.NLINE, P.nx * P.ny, q % A.NPB);
+        dose_reduce_body(J.row[j], J.dep[j], J.ngen[j], NA, J.nslot, P.NLINE, P.nx * P.ny, q % A.NPB);
         return;
     }
     extern __shared__ char smem_raw[];
@@ -3732,15 +3731,18 @@ __device__ __forceinline__ void dose_reduce_body(double *edep, const double *dep
     __shared__ double part[4][32];
     const int tid = threadIdx.x, pt = tid & 31, h = (tid >> 5) & 1, w = tid >> 6;
     const long base = (long)pb * NA * PBS_PT + pt;
+    const bool adds = w < 4;   // further waves of a larger block only meet the barriers
     double s = 0.0;
-    for (int k = 0; k < ngen; ++k) {
-        const double *d = dep + (long)k * NLINE + base;
+    if (adds) {
+        for (int k = 0; k < ngen; ++k) {
+            const double *d = dep + (long)k * NLINE + base;
 #pragma unroll 8
-        for (int a = 2 * w + h; a < nslot; a += 8) s += d[(long)a * PBS_PT];
+            for (int a = 2 * w + h; a < nslot; a += 8) s += d[(long)a * PBS_PT];
+        }
     }
     s += __shfl_xor(s, 32);
     __syncthreads();   // a second reduction of the same block: the first one's partials have been read
-    if (h == 0) part[w][pt] = s;
+    if (adds && h == 0) part[w][pt] = s;
     __syncthreads();
     const int pq = pb * PBS_PT + pt;
     if (tid < 32 && pq < NP) edep[pq] += ((part[0][pt] + part[1][pt]) + part[2][pt]) + part[3][pt];
