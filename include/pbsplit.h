@@ -266,8 +266,9 @@ enum { PBS_SCHED_AUTO = 0, PBS_SCHED_ONE_STREAM = 1, PBS_SCHED_TWO_STREAMS = 2 }
 pbs_status pbs_set_schedule(pbs_ctx *ctx, int mode);
 
 /* Diagnostics: kernel timing.  pbs_profile(ctx, 1) starts recording a HIP event pair on the
- * bound stream around every kernel launch, grouped by kind; pbs_profile(ctx, 0) stops and
- * clears.  pbs_profile_read synchronises the stream and returns, for kind = 0..n-1 (at most
+ * bound stream around every launch of a pass, grouped by kind; pbs_profile(ctx, 0) stops and
+ * clears.  The schedule and the results stay those of the march without timing; where that takes T A T of
+ * all generations (and the dose reductions) as one launch, they are launched by themselves while timed.  pbs_profile_read synchronises the stream and returns, for kind = 0..n-1 (at most
  * PBS_NKIND), the summed duration in ms and the number of launches since recording began. */
 enum { PBS_K_EPASS = 0, PBS_K_TPASS = 1, PBS_K_APASS = 2, PBS_K_QGEMM = 3, PBS_K_DOSE = 4, PBS_NKIND = 5 };
 pbs_status pbs_profile(pbs_ctx *ctx, int enable);

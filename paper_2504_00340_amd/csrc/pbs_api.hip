@@ -885,11 +885,18 @@ pbs_status angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st)
     return PBS_OK;
 }
 
-// every active generation's T(h/2) A(h) T(h/2) in one launch (the kinds of pass are timed one by one)
+// every active generation's T(h/2) A(h) T(h/2) takes one launch
+template <typename T>
+bool tat_single(const pbs_ctx *c)
+{
+    return tat_fits<T>(c->g.nth, c->g.ny, c->NLINE, slabs(c, -1));
+}
+
+// ... and is launched so: while the kinds of pass are timed one by one it runs as its passes, in the same schedule
 template <typename T>
 bool tat_fused(const pbs_ctx *c)
 {
-    return !c->prof && tat_fits<T>(c->g.nth, c->g.ny, c->NLINE, slabs(c, -1));
+    return !c->prof && tat_single<T>(c);
 }
 
 // T(h/2) A(h) T(h/2), and the dose reductions J if it is fused
@@ -964,7 +971,7 @@ pbs_status one_step(pbs_ctx *c)
     const long cells = (long)c->NP * c->NA * c->G();
     const bool ovl = c->side && (c->sched == PBS_SCHED_TWO_STREAMS ||
                                  (c->sched == PBS_SCHED_AUTO && c->kact > 1 && cells < PBS_OVERLAP_CELLS &&
-                                  (c->NA >= 128 || cells >= PBS_OVERLAP_MIN) && !tat_fused<T>(c)));
+                                  (c->NA >= 128 || cells >= PBS_OVERLAP_MIN) && !tat_single<T>(c)));
     const int tat = ovl ? s : -1;
     DoseJobs J;
     DoseJobs *later = !ovl && tat_fused<T>(c) ? &J : nullptr;

@@ -1,0 +1,28 @@
+"""The schedule that a march takes by itself, seen from the launches that the kernel timing counts: on one stream a
+step's transport is two launches for all generations, on two streams two for each."""
+import pytest
+
+from paper_2504_00340_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _streams(nx, ny, nth, ng, ngen, prec):
+    from paper_2504_00340_amd import pbsplit as P
+
+    print("case schedule", nx, ny, nth, ng, ngen, prec, flush=True)
+    c = I.small(nz=3, seed=3, nx=nx, ny=ny, nth=nth, ng=ng, ngen=ngen)
+    s = P.Solver(c["grid"], c["phys"], precision=prec)
+    s.set_phantom(c["rho"])
+    s.set_beam(c["beam"])
+    s.profile(True)
+    s.step(2)
+    n = s.profile_read()["tpass"][1]
+    s.close()
+    assert n in (4, 4 * ngen)
+    return 1 if n == 4 else 2
+
+
+def test_timing_keeps_the_stream_of_the_march():
+    # small slabs whose T A T is one launch stay on one stream, also while their passes are timed one by one
+    assert _streams(32, 32, 6, 60, 2, "fp32") == 1
