@@ -258,8 +258,8 @@ pbs_status pbs_set_splitting(pbs_ctx *ctx, int order);
  * run on a second stream beside the energy passes and source products of the later generations
  * (section 3.3's Strang sequence is kept per generation; the next step's energy pass of k waits for
  * them).  mode PBS_SCHED_AUTO (the default) uses the second stream for several generations of fewer than
- * 1e8 phase-space cells each (at least 1e6 or 128 angular unknowns, and only where T A T of all generations
- * is more than one launch), PBS_SCHED_ONE_STREAM never, PBS_SCHED_TWO_STREAMS always.  The stream is
+ * 1e8 phase-space cells each (below 1e6 and 128 angular unknowns where the groups make the step long enough,
+ * and only where T A T of all generations is more than one launch), PBS_SCHED_ONE_STREAM never, PBS_SCHED_TWO_STREAMS always.  The stream is
  * created by pbs_bind and joined back into the bound stream at the end of every pbs_step_depth /
  * pbs_run_beam call.  Returns PBS_EINVAL for another mode. */
 enum { PBS_SCHED_AUTO = 0, PBS_SCHED_ONE_STREAM = 1, PBS_SCHED_TWO_STREAMS = 2 };

@@ -16,10 +16,10 @@
 // and one of them holds fewer phase-space cells than PBS_OVERLAP_CELLS: such kernels leave most of the GPU idle (32 x 32
 // cells, 15 x 15 angles, 131 groups: 926 -> 822 us a step), while at 64 x 64 cells, 31 x 31 angles, 128 groups and 4
 // generations every kernel already saturates HBM and the concurrent ones mostly slow each other (1 % per step gained,
-// every kernel 1.4-2.6x longer), so there the sub-steps stay in order on one stream.  One generation has nothing to
-// overlap with (64 x 64, 15 x 15, 96: 1160 against 1177 us).  The events between the streams cost the host about 35 us per
-// generation and step: below PBS_OVERLAP_MIN cells of a grid with few angles the step itself is shorter than that (4 x
-// 4, 11 x 11, 60: 64 against 78 us; 16 x 16, 7 x 7, 48: 71 against 78), and where T A T is one launch.
+// every kernel 1.4-2.6x longer), so there the sub-steps stay in order on one stream and each kernel's own rate stays
+// measurable.  One generation has nothing to overlap with (64 x 64, 15 x 15, 96: 1160 against 1177 us).
+// The events between the streams cost the host about 36 us per generation and step, so a small grid (fewer than
+// PBS_OVERLAP_MIN cells and 128 angles) takes them only where its step is longer than that: overlap_pays.
 #ifndef PBS_OVERLAP_CELLS
 #define PBS_OVERLAP_CELLS 100000000L
 #endif
@@ -961,6 +961,21 @@ pbs_status extrapolated_step(pbs_ctx *c)
     return PBS_OK;
 }
 
+// A small grid's step of one generation on one stream, in us: launches, the source product's chain over the angles,
+// the energy sweeps' chain over the groups, and what grows with the cells.  Fitted to 118 marches of up to 1e6
+// cells, 9 to 121 angles, 16 to 160 groups, 2 to 8 generations, FP32 and FP64: the choice by it is at most 8 % slower
+// than the better one, 0.2 % on average.  us a step on one | two streams: 4 x 4 cells, 3 x 3 angles, 130 groups 70 | 80;
+// 4 x 4, 7 x 7, 130 82 | 84; 10 x 40, 5 x 5, 60 75 | 79 and 90 94 | 91; 10 x 10, 7 x 7, 130 108 | 102; 4 x 4, 11 x 11, 130 104 | 98; 10
+// x 40, 7 x 7, 24 60 | 72 and 48 85 | 83; 48 and three generations 117 | 107; FP64 8 x 20, 9 x 9, 30 80 | 83 and 60 109 | 103.
+template <typename T>
+bool overlap_pays(const pbs_ctx *c, long cells)
+{
+    const double mc = 1e-6 * (double)cells;
+    const double us = sizeof(T) == 8 ? 12 + 0.12 * c->NA + 0.27 * c->G() + 8 * mc
+                                       : 13 + 0.03 * c->NA + 0.2 * c->G() + 20 * mc;
+    return us > 42;
+}
+
 template <typename T>
 pbs_status one_step(pbs_ctx *c)
 {
@@ -971,7 +986,8 @@ pbs_status one_step(pbs_ctx *c)
     const long cells = (long)c->NP * c->NA * c->G();
     const bool ovl = c->side && (c->sched == PBS_SCHED_TWO_STREAMS ||
                                  (c->sched == PBS_SCHED_AUTO && c->kact > 1 && cells < PBS_OVERLAP_CELLS &&
-                                  (c->NA >= 128 || cells >= PBS_OVERLAP_MIN) && !tat_single<T>(c)));
+                                  (c->NA >= 128 || cells >= PBS_OVERLAP_MIN || overlap_pays<T>(c, cells)) &&
+                                  !tat_single<T>(c)));
     const int tat = ovl ? s : -1;
     DoseJobs J;
     DoseJobs *later = !ovl && tat_fused<T>(c) ? &J : nullptr;

@@ -26,3 +26,13 @@ def _streams(nx, ny, nth, ng, ngen, prec):
 def test_timing_keeps_the_stream_of_the_march():
     # small slabs whose T A T is one launch stay on one stream, also while their passes are timed one by one
     assert _streams(32, 32, 6, 60, 2, "fp32") == 1
+
+
+# short steps stay on one stream, long ones overlap, around the length that the second stream's events cost; from 1e6
+# cells or 128 angles on always two, one generation always one
+@pytest.mark.parametrize("nx,ny,nth,ng,ngen,prec,streams", [
+    (10, 10, 8, 130, 2, "fp32", 2), (10, 40, 8, 24, 2, "fp32", 1), (10, 40, 6, 90, 2, "fp32", 2), (10, 40, 6, 60, 2, "fp32", 1),
+    (4, 4, 4, 130, 2, "fp32", 1), (4, 4, 12, 130, 2, "fp32", 2), (10, 40, 8, 48, 3, "fp32", 2), (8, 20, 10, 60, 2, "fp64", 2),
+    (8, 20, 10, 30, 2, "fp64", 1), (4, 4, 16, 16, 2, "fp32", 2), (40, 40, 12, 16, 2, "fp32", 2), (10, 40, 8, 130, 1, "fp32", 1)])
+def test_second_stream_by_the_length_of_the_step(nx, ny, nth, ng, ngen, prec, streams):
+    assert _streams(nx, ny, nth, ng, ngen, prec) == streams
