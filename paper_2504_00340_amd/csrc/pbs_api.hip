@@ -889,7 +889,8 @@ pbs_status angular(pbs_ctx *c, int layer, double h, int k, hipStream_t st)
 template <typename T>
 bool tat_single(const pbs_ctx *c)
 {
-    return tat_fits<T>(c->g.nth, c->g.ny, c->NLINE, slabs(c, -1));
+    const bool overlap = c->side && c->sched == PBS_SCHED_AUTO && c->order == 2;
+    return tat_fits<T>(c->g.nth, c->g.ny, c->NLINE, slabs(c, -1), c->kact, overlap);
 }
 
 // ... and is launched so: while the kinds of pass are timed one by one it runs as its passes, in the same schedule

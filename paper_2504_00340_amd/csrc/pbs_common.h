@@ -176,9 +176,9 @@ struct DoseJobs {
     void add(double *r, const double *d, int k) { row[n] = r, dep[n] = d, ngen[n] = k, ++n; }
 };
 hipError_t launch_dose_reduce(const DoseJobs &J, int NA, long NLINE, int NP, hipStream_t st);
-// transport, angular step, transport of nstack slabs of nline values in one launch, where tat_fits, with the dose
-// reductions J (rows that differ) beside them
-template <typename T> bool tat_fits(int nth, int ny, long nline, long nstack);
+// transport, angular step, transport of nstack slabs (of ngen generations) of nline values in one launch, where
+// tat_fits (overlap: the march may take two streams instead), with the dose reductions J (rows that differ) beside them
+template <typename T> bool tat_fits(int nth, int ny, long nline, long nstack, int ngen, bool overlap);
 template <typename T> hipError_t launch_tat(const TParams<T> &P, const AParams<T> &A, int nth, long nstack, const DoseJobs &J, hipStream_t st);
 template <typename T> hipError_t launch_qgemm(const QParams<T> &P, hipStream_t st);
 template <typename T> hipError_t launch_fill(T *p, T v, long n, hipStream_t st);

@@ -2552,16 +2552,34 @@ __global__ __launch_bounds__(TAT_NT) void tat_kernel(TParams<T> P, AParams<T> A,
         tpass_pack_planes<T, W>(P, w, [&](unsigned) { return SlabMove<T, SlabLds<T>, SlabBuf<T, 0>>{lds, buf}; });
 }
 
-// All slabs have to fit the chip at once (256 CUs, two blocks a CU where LDS holds two slabs): a second round costs
-// what the launches save (16 x 16, 9 x 9, 100, 3 generations of 81 KB: 183 us a step against 177).  Fewer than 96 leave
-// too many CUs idle (5 x 7, 11 x 11, 40, one generation: 80 slabs, 32 against 31 us; 60: 36.7 against 37.7).
+// What the kernel can take: the angular grids it is built for, registers of 1024 threads, a slab in LDS.
 template <typename T>
-bool tat_fits(int nth, int ny, long nline, long nstack)
+static bool tat_takes(int nth, int ny, long nline)
 {
-    const long bytes = nline * (long)sizeof(T);
     if (nth != 6 && nth != 8 && nth != 10 && nth != 12) return false;
-    if (ny > (sizeof(T) == 8 && nth >= 10 ? 16 : 32)) return false;   // registers of 1024 threads
-    return bytes <= TAT_SLAB && nstack >= 96 && nstack <= (bytes < 80000 ? 512 : 256);
+    return ny <= (sizeof(T) == 8 && nth >= 10 ? 16 : 32) && nline * (long)sizeof(T) <= TAT_SLAB;
+}
+
+// Where it pays.  A CU holds one block (77-127 registers of 1024 threads), so 256 slabs are one round; fewer than 96
+// leave too many CUs idle (5 x 7, 11 x 11, 40, one generation: 80 slabs, 32 against 31 us; 60: 36.7 against 37.7).  A
+// second round still beats the passes on one stream by 5 to 15 % (16 x 16, 7 x 7, 120, two generations 93 against 108
+// us; 12 x 16, 7 x 7, 60, four, FP64 149 against 163), except for wide grids of large slabs (8 x 20, 11 x 11, 160, one
+// generation of 77 KB 93 against 87).  With two generations the passes on two streams, if they may take them (overlap), are
+// the better ones where the slabs take long: us a step here | there, 16 x 20, 7 x 7, 100 (63 KB) 104 | 98; 12 x 20, 7 x 7, 100 (50 KB) 95 | 98; 10 x
+// 16, 11 x 11, 128 (77 KB) 129 | 123; 8 x 16, 11 x 11, 100 (62 KB) 101 | 108; FP64 16 x 20, 5 x 5, 100 (64 KB) 108 | 104; 8 x
+// 20, 7 x 7, 100 (63 KB) 109 | 112; 4 x 4, 11 x 11, 100 (31 KB) 105 | 100.  24 x 32, 5 x 5, 128 (77 KB) 120 | 130.
+template <typename T>
+bool tat_fits(int nth, int ny, long nline, long nstack, int ngen, bool overlap)
+{
+    if (!tat_takes<T>(nth, ny, nline) || nstack < 96 || nstack > 512) return false;
+    if (nstack <= 256) return true;
+    constexpr bool F64 = sizeof(T) == 8;
+    long lim = 80000;   // bytes of a slab in two rounds
+    if (F64 || nth > 6) {
+        if (ngen == 1 && ny > 16) lim = 64000;
+        if (ngen == 2 && overlap) lim = F64 && nth == 12 ? 0 : !F64 && ny > 16 ? 51000 : 64000;
+    }
+    return nline * (long)sizeof(T) < lim;
 }
 template <typename T, int N>
 static void launch_tat_n(const TParams<T> &P, const AParams<T> &A, long nstack, const DoseJobs &J, hipStream_t st)
@@ -2578,7 +2596,7 @@ static void launch_tat_n(const TParams<T> &P, const AParams<T> &A, long nstack, 
 template <typename T>
 hipError_t launch_tat(const TParams<T> &P, const AParams<T> &A, int nth, long nstack, const DoseJobs &J, hipStream_t st)
 {
-    if (!tat_fits<T>(nth, P.ny, P.NLINE, nstack) || P.NA != (nth - 1) * (nth - 1)) return hipErrorInvalidValue;
+    if (!tat_takes<T>(nth, P.ny, P.NLINE) || P.NA != (nth - 1) * (nth - 1)) return hipErrorInvalidValue;
     switch (nth) {
     case 6: launch_tat_n<T, 6>(P, A, nstack, J, st); break;
     case 8: launch_tat_n<T, 8>(P, A, nstack, J, st); break;
@@ -4163,7 +4181,7 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
     template hipError_t launch_epass<T>(const EParams<T> &, int, hipStream_t);                                \
     template hipError_t launch_tpass<T>(const TParams<T> &, hipStream_t);                                     \
     template hipError_t launch_apass<T>(const AParams<T> &, const T *, int, long, hipStream_t);                        \
-    template bool tat_fits<T>(int, int, long, long);                                                           \
+    template bool tat_fits<T>(int, int, long, long, int, bool);                                                     \
     template hipError_t launch_tat<T>(const TParams<T> &, const AParams<T> &, int, long, const DoseJobs &, hipStream_t); \
     template hipError_t launch_qgemm<T>(const QParams<T> &, hipStream_t);                                     \
     template hipError_t launch_fill<T>(T *, T, long, hipStream_t);                                            \

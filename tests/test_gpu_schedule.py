@@ -36,3 +36,12 @@ def test_timing_keeps_the_stream_of_the_march():
     (8, 20, 10, 30, 2, "fp64", 1), (4, 4, 16, 16, 2, "fp32", 2), (40, 40, 12, 16, 2, "fp32", 2), (10, 40, 8, 130, 1, "fp32", 1)])
 def test_second_stream_by_the_length_of_the_step(nx, ny, nth, ng, ngen, prec, streams):
     assert _streams(nx, ny, nth, ng, ngen, prec) == streams
+
+
+# more slabs than CUs: T A T stays one launch on one stream except where the passes on two streams are faster
+@pytest.mark.parametrize("nx,ny,nth,ng,ngen,prec,streams", [
+    (16, 16, 8, 128, 2, "fp32", 1), (16, 20, 8, 100, 2, "fp32", 2), (16, 20, 8, 100, 3, "fp32", 2), (16, 20, 8, 60, 4, "fp32", 1),
+    (24, 32, 6, 128, 2, "fp32", 1), (10, 16, 12, 129, 2, "fp32", 2), (10, 16, 12, 128, 2, "fp32", 2), (8, 16, 12, 128, 2, "fp32", 1),
+    (4, 4, 12, 128, 2, "fp64", 2), (4, 4, 12, 64, 2, "fp64", 1), (4, 4, 12, 64, 4, "fp64", 1), (8, 20, 8, 128, 2, "fp64", 1)])
+def test_second_round_of_small_slabs(nx, ny, nth, ng, ngen, prec, streams):
+    assert _streams(nx, ny, nth, ng, ngen, prec) == streams
