@@ -532,10 +532,22 @@ void layout(pbs_ctx *c)
     c->t_theta = e; e += c->m;
     c->t_S = e; e += (size_t)c->m * c->m;
     c->t_lam = e; e += c->m;
-    e = (e + 63) / 64 * 64;   // vector loads of the padded tables need 256-byte alignment
-    c->t_P2p = e; e += (size_t)c->NB * c->Kp * c->Mp;
-    e = (e + 63) / 64 * 64;
-    c->t_K32 = e; e += 1024;
+    c->t_P2p = (e + 63) / 64 * 64;   // vector loads of the padded tables need 256-byte alignment
+    if (c->NA >= 128) {
+        e = c->t_P2p + (size_t)c->NB * c->Kp * c->Mp;
+        e = (e + 63) / 64 * 64;
+        c->t_K32 = e; e += 1024;
+    } else {
+        // fewer than 16 nodes: no operand table of the angular pass, whose room the matrices' rows (source nodes) are
+        // spaced out into, as far as it goes and to whole tiles at most: contexts that fit the static scratch with
+        // unpadded rows still do.  The product's waves read whole tiles of rows up to two rows past the last node.
+        e = (e + (size_t)c->NB * c->NA * c->NA + 63) / 64 * 64 + 1024;
+        const size_t tile = (c->NA + 31) / 32 * 32, room = e - c->t_P2p - tile;
+        const size_t sp = room / ((size_t)(c->NB - 1) * c->NA + c->NA + 2);
+        c->Kp = c->NA;
+        c->Mp = (int)(sp >= tile ? tile : std::max((size_t)c->NA, sp / 4 * 4));
+        c->t_K32 = c->t_P2p;   // not read
+    }
     c->t_wdecb = e; e += (size_t)c->NB * G;
     c->t_blk = e; e += c->strag ? (size_t)12 * G : 0;
     c->t_count = e;
@@ -582,16 +594,18 @@ pbs_status upload_tables(pbs_ctx *c)
     put(c->t_lam, c->lam);
     put(c->t_wdecb, c->wdecb);
     if (c->strag) put(c->t_blk, c->blk);
-    // zero-padded, source-major copy for the MFMA product: P2p[b][k][a] = P2T[b][a][k]
+    // source-major copy for the MFMA product, zero in its padding: P2p[b][k][a] = P2T[b][a][k]
     const size_t NA2 = (size_t)c->NA * c->NA, KM = (size_t)c->Kp * c->Mp;
     for (int b = 0; b < c->NB; ++b)
         for (int a = 0; a < c->NA; ++a)
             for (int k = 0; k < c->NA; ++k)
                 t[c->t_P2p + b * KM + (size_t)k * c->Mp + a] = (T)c->P2T[b * NA2 + (size_t)a * c->NA + k];
     // MFMA operand constants of the angular pass
-    std::vector<double> kt(1024);
-    apass_mfma_table(c->g.nth, sizeof(T) == 8, kt.data());
-    put(c->t_K32, kt);
+    if (c->g.nth >= 16) {
+        std::vector<double> kt(1024);
+        apass_mfma_table(c->g.nth, sizeof(T) == 8, kt.data());
+        put(c->t_K32, kt);
+    }
     std::vector<double> d(c->d_count, 0.0);
     std::memcpy(&d[c->d_A], c->dA.data(), c->G() * sizeof(double));
     std::memcpy(&d[c->d_B], c->dB.data(), c->G() * sizeof(double));
@@ -1295,10 +1309,7 @@ pbs_status pbs_create(const pbs_grid *grid, const pbs_physics *phys, int precisi
     c->dth = 2.0 * g.th_half / g.nth;
     c->NOCT = (c->NA + 7) / 8;
     c->kact = g.ngen;
-    // padding of the source product's matrix: whole MFMA steps and tiles
-    c->Kp = (c->NA + 3) / 4 * 4;
-    c->Mp = (c->NA + 31) / 32 * 32;
-    if (c->NA >= 128) {
+    if (c->NA >= 128) {   // the source product's matrix is padded to whole MFMA steps and tiles (below: layout)
         c->Kp = (c->NA + 15) / 16 * 16;
         c->Mp = (c->NA + 127) / 128 * 128;
         if (precision == PBS_FP32 && !ph.straggling) {

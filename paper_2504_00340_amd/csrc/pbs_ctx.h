@@ -66,7 +66,7 @@ struct pbs_ctx {
     size_t t_Sm, t_Sp, t_kap, t_wc, t_wdec, t_invdE, t_sig, t_theta, t_S, t_lam, t_P2p, t_K32, t_wdecb, t_blk,
         t_count;
     size_t o_band = 0, o_sfac = 0;   // band indices [G] (int); straggling factors [2][G][8][NPpad] (T)
-    int Kp = 0, Mp = 0;           // padded source product (MFMA path, FP32 with NA >= 128)
+    int Kp = 0, Mp = 0;           // rows and row spacing of the source product's matrix
     int Kpb = 0;                  // k padding of the split-BF16 operand tables
     int NOCT = 0;                 // source-node octets of the split-BF16 W layout
     size_t Wb_half = 0;           // elements of one of the hi / lo arrays

@@ -3580,7 +3580,7 @@ hipError_t launch_qgemm_bf16s(const QParams<float> &P, const unsigned short *Ahi
 // FP64, and FP32 below 128 angular unknowns (up to 12 nodes per axis): v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4.
 // What bounded the vector kernel it replaces: its LDS staging (a barrier pair per 32 source nodes) on small
 // grids, two LDS reads per multiply on large ones.  Here both operands go from global memory straight into MFMA
-// registers: P2 (zero-padded [Kp][Mp], resident in L2) and the scan, whose row of 32 cells
+// registers: P2 (rows Mp apart, resident in L2) and the scan, whose row of 32 cells
 // a lane reads as one pair, cell 2 c + h being column c of column tile h.  Block = up to 4 waves of 32 destination
 // rows each (blockIdx.y: the next 128 rows) over NTL lateral tiles of one (half, group); loads run QS_PF 4-node steps ahead.  NTL = 1 where the
 // grid has few tiles (latency), else as many as the registers hold, for each P2 load to feed more products.
@@ -3589,7 +3589,9 @@ hipError_t launch_qgemm_bf16s(const QParams<float> &P, const unsigned short *Ahi
 // In FP64 it also beats a 128 x 128 block tile staged in LDS at every size (64 x 64 cells, 15 x 15 angles, 64 groups 1472 ->
 // 1200, 44 TFLOP/s; 32 x 32, 31 x 31, 32 2688 -> 2390); in FP32 that kernel (qgemm_mfma_f32_kernel) wins from 128
 // unknowns on (685 against 788, 4678 against 6297 at 64 x 64, 31 x 31, 32 groups): a matrix step there takes half the
-// time and the operand loads no longer hide behind it.
+// time and the operand loads no longer hide behind it.  The last node has a step of its own, loaded first, with a zero
+// scan beside it, so that the matrix needs no rows of zeros below 128 unknowns (us with them and without: 4 x 4 cells,
+// 11 x 11, 60 9.4 | 9.5; 64 x 64, 7 x 7, 100 89 | 90; FP64 32 x 32, 11 x 11, 60 94 | 98; 64 x 64, 15 x 15, 64 1315 | 1253).
 constexpr int QS_PF = 4;
 
 template <typename T, int NTL>
@@ -3607,30 +3609,28 @@ __global__ __launch_bounds__(256) void qgemm_direct_kernel(QParams<T> P, int nnt
     const T *B[NTL];
 #pragma unroll
     for (int j = 0; j < NTL; ++j) B[j] = P.W + off + (long)min(nt * NTL + j, P.NPB - 1) * NAPT + 2 * c;
-    const int KS = P.Kp / 4;
+    const int KF = P.NA / 4;   // whole steps; one node is left (NA is odd squared)
     T4 acc[2][NTL][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < NTL; ++j) acc[i][j][0] = acc[i][j][1] = T4{0, 0, 0, 0};
-    T ra[QS_PF][2];
-    T2 rb[QS_PF][NTL];
-    // step k of 4 source nodes into ring slot u; a padded node (zero column of P2) reads the last node's scan
-    auto fetch = [&](int k, int u) {
-        const int kc = min(k, KS - 1);
-        const T *a = A + (long)kc * 4 * P.Mp;
-        ra[u][0] = a[0];
-        ra[u][1] = a[16];
-        const long row = (long)min(4 * kc + kq, P.NA - 1) * PBS_PT;
+    T ra[QS_PF][2], la[2];
+    T2 rb[QS_PF][NTL], lb[NTL];
+    // operands of step k: P2's rows of 4 source nodes (whole tiles of it: rows past the last node are dropped at the end,
+    // columns past it meet a zero scan) and the scan of one of them per lane group
+    auto load = [&](int k, int node, T (&a)[2], T2 (&b)[NTL]) {
+        const T *p = A + (long)k * 4 * P.Mp;
+        a[0] = p[0];
+        a[1] = p[16];
 #pragma unroll
-        for (int j = 0; j < NTL; ++j) rb[u][j] = *reinterpret_cast<const T2 *>(B[j] + row);
+        for (int j = 0; j < NTL; ++j) b[j] = *reinterpret_cast<const T2 *>(B[j] + (long)node * PBS_PT);
     };
-    auto step = [&](int k, int u) {
-        T a[2] = {ra[u][0], ra[u][1]};
-        T2 b[NTL];
-#pragma unroll
-        for (int j = 0; j < NTL; ++j) b[j] = rb[u][j];
-        fetch(k + QS_PF, u);
+    auto fetch = [&](int k, int u) {
+        const int kc = min(k, KF - 1);
+        load(kc, 4 * kc + kq, ra[u], rb[u]);
+    };
+    auto mac = [&](const T (&a)[2], const T2 (&b)[NTL]) {
 #pragma unroll
         for (int j = 0; j < NTL; ++j)
 #pragma unroll
@@ -3638,16 +3638,29 @@ __global__ __launch_bounds__(256) void qgemm_direct_kernel(QParams<T> P, int nnt
 #pragma unroll
                 for (int h = 0; h < 2; ++h) acc[i][j][h] = mfma16(a[i], b[j][h], acc[i][j][h]);
     };
+    auto step = [&](int k, int u) {
+        const T a[2] = {ra[u][0], ra[u][1]};
+        T2 b[NTL];
+#pragma unroll
+        for (int j = 0; j < NTL; ++j) b[j] = rb[u][j];
+        fetch(k + QS_PF, u);
+        mac(a, b);
+    };
 #pragma unroll
     for (int u = 0; u < QS_PF; ++u) fetch(u, u);
+    load(KF, P.NA - 1, la, lb);
     int k0 = 0;
-    for (; k0 + QS_PF <= KS; k0 += QS_PF) {
+    for (; k0 + QS_PF <= KF; k0 += QS_PF) {
 #pragma unroll
         for (int u = 0; u < QS_PF; ++u) step(k0 + u, u);
     }
 #pragma unroll
     for (int u = 0; u < QS_PF - 1; ++u)
-        if (k0 + u < KS) step(k0 + u, u);
+        if (k0 + u < KF) step(k0 + u, u);
+    // the last node, beside three that do not exist
+#pragma unroll
+    for (int j = 0; j < NTL; ++j) lb[j] = kq == 0 ? lb[j] : T2{0, 0};
+    mac(la, lb);
 #pragma unroll
     for (int j = 0; j < NTL; ++j) {
         const int pb = nt * NTL + j;
@@ -3673,8 +3686,8 @@ template <typename T>
 static hipError_t launch_qgemm_direct(const QParams<T> &P, hipStream_t st)
 {
     constexpr int WIDE = sizeof(T) == 4 ? 4 : 2;
-    const dim3 block(P.Mp >= 128 ? 256 : 64 * (P.Mp / 32));
-    const unsigned nmt = (unsigned)((P.Mp + 127) / 128);
+    const dim3 block(P.NA > 96 ? 256 : 64 * ((P.NA + 31) / 32));
+    const unsigned nmt = (unsigned)((P.NA + 127) / 128);
     const long items = (long)P.ns * P.G * P.NPB;
     if (items > QS_WIDE_ITEMS) {
         const int nnt = (P.NPB + WIDE - 1) / WIDE;

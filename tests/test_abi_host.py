@@ -226,3 +226,19 @@ def test_voxel_phantom_resampling_matches_the_batched_plan():
     assert B.lib().pbs_set_phantom_voxels(ctx, v.ctypes.data_as(C.POINTER(C.c_double)), 4, 5, 6, 0.1, 0.1, 0.1,
                                           0.0, 0.0) == B.PBS_ESTATE
     B.lib().pbs_destroy(ctx)
+
+
+# contexts of fewer than 128 angular unknowns just within the static scratch, as large as the unpadded product matrices
+# allow (bytes: the tables' exact sizes are part of what fits)
+@pytest.mark.parametrize("nx,ny,nth,ng,nz,ngen,prec,bands", [
+    (16, 4, 8, 145, 18454, 2, B.PBS_FP64, True), (16, 4, 10, 96, 17019, 2, B.PBS_FP64, True),
+    (16, 4, 12, 89, 10867, 2, B.PBS_FP64, True), (16, 4, 12, 133, 215, 2, B.PBS_FP64, True),
+    (16, 4, 12, 124, 15763, 3, B.PBS_FP32, False), (16, 4, 12, 138, 18083, 2, B.PBS_FP32, True)])
+def test_contexts_near_the_static_scratch_still_fit(nx, ny, nth, ng, nz, ngen, prec, bands):
+    g = I.grid(nx, ny, nth, ng, nz, ngen, 4.0, 4.0, 0.15, 0.0, 160.0, 1.0)
+    rc, ctx = _create(g, dict(I.PHYS, **I.NUC_BANDS) if bands else None, prec)
+    assert rc == B.PBS_OK
+    nb = C.c_size_t()
+    assert B.lib().pbs_workspace_bytes(ctx, C.byref(nb)) == B.PBS_OK
+    B.lib().pbs_destroy(ctx)
+    assert nb.value <= B.PBS_STATIC_SCRATCH_BYTES
