@@ -215,3 +215,26 @@ def test_small_slabs_in_one_launch(nx, ny, nth, ng, ngen, prec):
         s.close()
     assert np.isfinite(out[0][0]).all()
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+# slabs of 1 GiB and more: the sweep by pointers.  A beam in the middle of a very long grid against the same beam
+# on a short one of the same cells (nothing reaches either one's ends), so that no host copy of the fluence is needed.
+@pytest.mark.parametrize("ny,long_nx", [(33, 8500), (20, 14000), (64, 8801)])
+def test_transport_of_slabs_beyond_a_buffer_resource(ny, long_nx):
+    from paper_2504_00340_amd import pbsplit as P
+
+    print("case large slab", ny, long_nx, flush=True)
+    doses = []
+    for nx in (long_nx, 200 + long_nx % 2):
+        g = I.grid(nx, ny, 32, 2, 2, 1, 0.05 * nx, 1.5, 0.1, 0.0, 40.0, 0.4)
+        s = P.Solver(g, dict(I.PHYS), "fp32")
+        s.set_phantom(I.water(g))
+        s.set_beam(I.beam(30.0, y0=0.1, sigma_x=0.3, sigma_y=0.25))
+        s.run()
+        d = s.dose()
+        s.close()
+        lo = nx // 2 - 60
+        doses.append(d[:, lo:lo + 120].copy())
+    e = np.abs(doses[0] - doses[1]).max() / np.abs(doses[1]).max()
+    print("difference", e, flush=True)
+    assert np.isfinite(doses[0]).all() and e <= TOL["fp32"]
