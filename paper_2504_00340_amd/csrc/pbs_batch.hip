@@ -290,7 +290,7 @@ pbs_status autotune(pbs_batch *b, int nw, int maxG)
         *field = bestv;
     };
     pick(&t.gemm_kind, gk, 3);
-    pick(&t.tpass_wpb, wpb, 3);
+    if (batch_tpass_tunes(shape(b), maxG)) pick(&t.tpass_wpb, wpb, 3);
     BHIP(b, hipGetLastError());
     b->tune.gemm_kind = t.gemm_kind;
     b->tune.tpass_wpb = t.tpass_wpb;

@@ -137,7 +137,7 @@ struct BatchShape {
 // bitwise-neutral launch variants picked by the batch autotuner
 struct BatchTuning {
     int gemm_kind = 0;        // split-BF16 product kernel (QGEMM_*)
-    int tpass_wpb = 4;        // transport: planes (waves) per block, 1, 2 or 4
+    int tpass_wpb = 4;        // transport: waves per block, 1, 2 or 4 (4 where batch_tpass_tunes says no)
     int max_nz = 0;           // longest beam of the wave (set by the batch planner)
 };
 
@@ -149,6 +149,8 @@ struct BatchSide {
     char *pend;
 };
 
+// whether the transport sweep of a wave of this shape has a choice of waves per block
+bool batch_tpass_tunes(const BatchShape &Sh, int maxG);
 // One fused depth step s of a wave.  Without sd every sub-step runs on st in order.
 hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &Sh, int s, int maxG,
                              const BatchTuning &tu, hipStream_t st, const BatchSide *sd = nullptr);

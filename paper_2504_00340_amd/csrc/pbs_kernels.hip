@@ -4100,6 +4100,27 @@ __global__ __launch_bounds__(256) void dose_batched_kernel(const BeamDev *__rest
                          epass8_slots(Sh.NOCT), Sh.NLINE, NP, blockIdx.x);
 }
 
+// the sizes that the rules of the packed sweeps look at
+static TParams<float> batch_tsize(const BatchShape &Sh, long planes)
+{
+    TParams<float> P;
+    P.ny = Sh.ny;
+    P.NLINE = Sh.NLINE;
+    P.nplanes = planes;
+    return P;
+}
+
+// the sweeps that take BatchTuning::tpass_wpb waves per block: the aligned widths, and the shuffle sweep
+static bool batch_tpass_aligned(const BatchShape &Sh)
+{
+    return Sh.nx % TPASS_PF == 0 && (Sh.ny == 32 || Sh.ny == 64 || Sh.ny == 96 || Sh.ny == 128);
+}
+bool batch_tpass_tunes(const BatchShape &Sh, int maxG)
+{
+    const TParams<float> size = batch_tsize(Sh, (long)Sh.ngen * maxG * 2 * Sh.NA);
+    return batch_tpass_aligned(Sh) || (!tpass_packed_fits(size) && !tpass_far_fits(size));
+}
+
 hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &Sh, int s, int maxG,
                              const BatchTuning &tu, hipStream_t st, const BatchSide *sd)
 {
@@ -4140,10 +4161,7 @@ hipError_t launch_batch_step(const BeamDev *beams, int nbeam, const BatchShape &
                 PBS_TWW(128);
                 return;
             }
-            TParams<float> size;   // the sizes the packed sweep's rule looks at, of the largest beam
-            size.ny = Sh.ny;
-            size.NLINE = Sh.NLINE;
-            size.nplanes = planes;
+            const TParams<float> size = batch_tsize(Sh, planes);   // of the largest beam
             if (tpass_packed_fits(size)) {
                 const int np = tpass_packed_planes(Sh.ny);
                 const dim3 g((unsigned)(((planes + np - 1) / np + 3) / 4), nbeam);

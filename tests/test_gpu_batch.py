@@ -66,3 +66,18 @@ def test_batch_beam_matches_oracle():
     print("batch beam vs oracle", rel, flush=True)
     assert rel < 1e-4
     bt.close()
+
+
+@pytest.mark.parametrize("nx,ny,choices", [(10, 10, (4,)), (8, 64, (1, 2, 4)), (9, 64, (4,)), (5, 100, (4,))])
+def test_waves_per_block_are_tuned_where_the_sweep_takes_them(nx, ny, choices):
+    """Widths of the packed transport always take four waves: none is timed there, and none reported as chosen."""
+    from paper_2504_00340_amd.pbsplit import Batch
+
+    seen = set()
+    for _ in range(6):
+        bt = Batch(_beams(2, nx=nx, ny=ny), I.PHYS)
+        bt.prepare()
+        seen.add(bt.tuning()["tpass_waves_per_block"])
+        bt.close()
+    print("waves per block", nx, ny, seen, flush=True)
+    assert seen <= set(choices)
