@@ -44,14 +44,13 @@ def _check(got, ref, prec, what):
         assert e.max() <= TOL[prec] * np.abs(ref[k]).max()
 
 
-# group counts around the ring of groups in flight (shorter, equal, one more, a remainder), angular counts whose
-# last line group is full (nth 10: 81 = 8 * 10 + 1; nth 16: 225 = 8 * 28 + 1; nth 18 is not supported)
+# group counts around the groups a chunk of the pipeline of waves holds (grids this small take it), angular counts whose
+# last line group holds one line (nth 10: 81 = 8 * 10 + 1; nth 16: 225 = 8 * 28 + 1); the rings have a test of their own
 @pytest.mark.parametrize("ng", [2, 3, 4, 5, 7])
 @pytest.mark.parametrize("nth,prec", [(6, "fp32"), (10, "fp64"), (16, "fp64"), (16, "fp32"), (20, "fp32")])
 def test_energy_step_around_the_group_ring(O, nth, prec, ng):
     print("case energy ring", nth, prec, ng, flush=True)
-    # generation 1's one-product BF16 source has its own bound (checked elsewhere): three products here take the
-    # pass without the ring for it, so check generation 0 in the default mode and all in the exact one
+    # generation 1's one-product BF16 source has its own bound; the exact source modes are tested below
     s, o, c, st = _setup(O, prec, dict(nx=5, ny=7, nth=nth, ng=ng, ngen=2))
     ref = st.copy()
     o.energy_all(ref, np.ascontiguousarray(c["rho"][1].reshape(-1)), 0.02)
@@ -238,3 +237,91 @@ def test_transport_of_slabs_beyond_a_buffer_resource(ny, long_nx):
     e = np.abs(doses[0] - doses[1]).max() / np.abs(doses[1]).max()
     print("difference", e, flush=True)
     assert np.isfinite(doses[0]).all() and e <= TOL["fp32"]
+
+
+# the two-plane sweep that the passes take at 32 columns and whole groups of eight rows against the fused launch's
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx,nth,ng,ngen", [(8, 6, 50, 2), (32, 6, 48, 2), (16, 8, 60, 1), (8, 10, 50, 2), (8, 12, 48, 2)])
+def test_small_slabs_of_32_columns_in_one_launch(nx, nth, ng, ngen, prec):
+    from paper_2504_00340_amd import pbsplit as P
+
+    print("case one launch, 32 columns", nx, nth, ng, ngen, prec, flush=True)
+    c = I.small(nz=4, seed=3, nx=nx, ny=32, nth=nth, ng=ng, ngen=ngen)
+    out = []
+    for mode in (P.PBS_SCHED_ONE_STREAM, P.PBS_SCHED_TWO_STREAMS):
+        s = P.Solver(c["grid"], c["phys"], precision=prec)
+        s.set_schedule(mode)
+        s.set_phantom(c["rho"])
+        s.set_beam(c["beam"])
+        s.set_state(I.random_state(s.state_shape, 3))
+        s.step(3)
+        out.append((s.state(), s.dose()))
+        s.close()
+    assert np.isfinite(out[0][0]).all()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+# more than 800 blocks of 64 threads, so that the register rings run and not the pipeline of waves: one line per thread
+# (fewer than 128 angles, FP64), four lines (FP32 from 128 on), and the plain four-line pass above 8192 waves; group counts
+# with every remainder of the ring, with one law of nuclear data and with four bands
+@pytest.mark.parametrize("bands", [False, True])
+@pytest.mark.parametrize("nx,ny,nth,prec,ng", [
+    (65, 65, 6, "fp32", 2), (65, 65, 6, "fp32", 3), (65, 65, 6, "fp32", 5), (65, 65, 6, "fp64", 3), (65, 65, 6, "fp64", 4),
+    (20, 24, 16, "fp64", 5), (40, 32, 16, "fp32", 2), (40, 32, 16, "fp32", 3), (41, 33, 16, "fp32", 7), (20, 24, 24, "fp32", 5),
+    (96, 97, 16, "fp32", 3)])
+def test_energy_rings_above_the_pipeline(O, nx, ny, nth, prec, ng, bands):
+    print("case ring", nx, ny, nth, prec, ng, bands, flush=True)
+    phys = dict(I.PHYS, **I.NUC_BANDS) if bands else None
+    s, o, c, st = _setup(O, prec, dict(nx=nx, ny=ny, nth=nth, ng=ng, ngen=2), phys=phys)
+    ref, rho = st.copy(), np.ascontiguousarray(c["rho"][1].reshape(-1))
+    o.energy_all(ref, rho, 0.02)
+    s.apply(1, 1, 0.02)
+    got = s.state()
+    s.close()
+    _check_modes(got, ref, prec, nth, "ring", o, st, rho)
+
+
+def _check_modes(got, ref, prec, nth, what, o, st, rho):
+    """All generations at the sub-step bound; those that take the one-product BF16 source within what its roundings
+    (the matrix, the scans with their carried residue, the product: 2^-9 each) make of the source's part in them."""
+    n = 1 if prec == "fp32" and nth >= 16 else len(ref)
+    _check(got[:n], ref[:n], prec, what)
+    for k in range(n, len(ref)):
+        alone = np.zeros_like(st)   # no earlier generation, no source
+        alone[k] = st[k]
+        o.energy_all(alone, rho, 0.02)
+        top = np.abs(ref[k]).max()
+        tol = TOL[prec] + 2.0 ** -6 * np.abs(ref[k] - alone[k]).max() / top
+        e = np.abs(got[k] - ref[k]).max() / top
+        print(what, "generation", k, "BF16 source:", e, "of", tol, flush=True)
+        assert e <= tol
+
+
+# the exact source modes, every generation at the sub-step bound: FP32 scans (the one-line pipeline and ring) and three
+# BF16 products of scans in two halves (the plain four-line pass; each term within 2^-15 of the source)
+@pytest.mark.parametrize("ng", [2, 3, 4, 5, 7])
+@pytest.mark.parametrize("nx,ny,nth,src", [(5, 7, 16, 0), (20, 24, 16, 0), (5, 7, 16, 1), (5, 7, 20, 1), (40, 32, 16, 1)])
+def test_energy_step_with_an_exact_source(O, nx, ny, nth, src, ng):
+    print("case exact source", nx, ny, nth, src, ng, flush=True)
+    s, o, c, st = _setup(O, "fp32", dict(nx=nx, ny=ny, nth=nth, ng=ng, ngen=3), src=src)
+    ref = st.copy()
+    o.energy_all(ref, np.ascontiguousarray(c["rho"][1].reshape(-1)), 0.02)
+    s.apply(1, 1, 0.02)
+    got = s.state()
+    s.close()
+    _check(got, ref, "fp32", "exact source")
+
+
+# the later generations of the pipeline, whose source is read in BF16
+@pytest.mark.parametrize("bands", [False, True])
+@pytest.mark.parametrize("nx,ny,ng,ngen", [(4, 5, 2, 2), (4, 5, 9, 3), (5, 7, 7, 4), (16, 16, 5, 2)])
+def test_energy_pipeline_later_generations(O, nx, ny, ng, ngen, bands):
+    print("case pipeline generations", nx, ny, ng, ngen, bands, flush=True)
+    phys = dict(I.PHYS, **I.NUC_BANDS) if bands else None
+    s, o, c, st = _setup(O, "fp32", dict(nx=nx, ny=ny, nth=16, ng=ng, ngen=ngen), phys=phys)
+    ref, rho = st.copy(), np.ascontiguousarray(c["rho"][1].reshape(-1))
+    o.energy_all(ref, rho, 0.02)
+    s.apply(1, 1, 0.02)
+    got = s.state()
+    s.close()
+    _check_modes(got, ref, "fp32", 16, "pipeline", o, st, rho)
