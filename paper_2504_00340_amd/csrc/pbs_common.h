@@ -200,7 +200,7 @@ hipError_t launch_initial(T *psi0, const double *E1, const double *E2, const dou
 enum { QGEMM_GLOBAL_B = 0, QGEMM_LDS_256 = 1, QGEMM_LDS_128 = 2 };
 hipError_t launch_qgemm_bf16s(const QParams<float> &P, const unsigned short *Ahi, const unsigned short *Alo, int Kp,
                               int nprod, hipStream_t st, int kind = QGEMM_GLOBAL_B);
-// operand table of the MFMA angular pass for nth >= 8 (1024 entries, unused ones zero); fp64: the row order of the
+// operand table of the MFMA angular pass for nth >= 16 (1024 entries, unused ones zero); fp64: the row order of the
 // FP64 matrix instruction
 void apass_mfma_table(int nth, bool fp64, double *out1024);
 

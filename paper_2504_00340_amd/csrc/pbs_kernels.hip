@@ -1370,15 +1370,7 @@ __global__ __launch_bounds__(256) void tpass_kernel(TParams<T> P)
     tpass_body<T, NSEG>(P, (long)blockIdx.x * 4 + (threadIdx.x >> 6));
 }
 
-// FP32 variant for ny <= 64: cross-lane moves by DPP (wave_shr/shl:1 for the y neighbours, a
-// row_shr / row_bcast affine scan for the implicit row solve) and 8 rows in flight per wave.
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ float dpp_f(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWMASK, 0xF,
-                                                                 false));
-}
-
+// The sweeps below move neighbours by DPP (wave_shr/shl:1 in y) and solve a row by a row_shr / row_bcast affine scan.
 // All lanes written, lanes without a source read 0: the form the compiler folds into the DPP operand of the
 // consuming VALU op (a row-scan step becomes one v_fmac_f32_dpp).
 template <int CTRL>
