@@ -301,8 +301,12 @@ __global__ __launch_bounds__(64) void strag_factor_kernel(EParams<T> P, int firs
         const double F2 = B[10] * di[0] + B[11] * di[2], F3 = B[10] * di[1] + B[11] * di[3];
         const double m0 = (1.0 - B[4]) - (F0 * L[0] + F1 * L[2]), m1 = -B[5] - (F0 * L[1] + F1 * L[3]);
         const double m2 = -B[6] - (F2 * L[0] + F3 * L[2]), m3 = (1.0 - B[7]) - (F2 * L[1] + F3 * L[3]);
-        const double idet = 1.0 / (m0 * m3 - m1 * m2);
-        di[0] = m3 * idet, di[1] = -m1 * idet, di[2] = -m2 * idet, di[3] = m0 * idet;
+        const double det = m0 * m3 - m1 * m2, idet = 1.0 / det;
+        auto over_det = [&](double m) {   // FP64: corrected once, as accurate as a division
+            const double q = m * idet;
+            return sizeof(T) == 8 ? fma(fma(-q, det, m), idet, q) : q;
+        };
+        di[0] = over_det(m3), di[1] = -over_det(m1), di[2] = -over_det(m2), di[3] = over_det(m0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) L[i] = B[i];
         T *o = sfac + (size_t)g * 8 * NPpad + pq;
