@@ -259,8 +259,8 @@ pbs_status pbs_set_splitting(pbs_ctx *ctx, int order);
  * (section 3.3's Strang sequence is kept per generation; the next step's energy pass of k waits for
  * them).  mode PBS_SCHED_AUTO (the default) uses the second stream for several generations of fewer than
  * 1e8 phase-space cells each (below 1e6 and 128 angular unknowns where the groups make the step long enough,
- * and only where T A T of all generations is more than one launch), PBS_SCHED_ONE_STREAM never, PBS_SCHED_TWO_STREAMS always.  The stream is
- * created by pbs_bind and joined back into the bound stream at the end of every pbs_step_depth /
+ * and only where T A T of all generations is more than one launch), PBS_SCHED_ONE_STREAM never,
+ * PBS_SCHED_TWO_STREAMS always.  The stream is created by pbs_bind and joined back into the bound stream at the end of every pbs_step_depth /
  * pbs_run_beam call.  Returns PBS_EINVAL for another mode. */
 enum { PBS_SCHED_AUTO = 0, PBS_SCHED_ONE_STREAM = 1, PBS_SCHED_TWO_STREAMS = 2 };
 pbs_status pbs_set_schedule(pbs_ctx *ctx, int mode);
@@ -268,7 +268,8 @@ pbs_status pbs_set_schedule(pbs_ctx *ctx, int mode);
 /* Diagnostics: kernel timing.  pbs_profile(ctx, 1) starts recording a HIP event pair on the
  * bound stream around every launch of a pass, grouped by kind; pbs_profile(ctx, 0) stops and
  * clears.  The schedule and the results stay those of the march without timing; where that takes T A T of
- * all generations (and the dose reductions) as one launch, they are launched by themselves while timed.  pbs_profile_read synchronises the stream and returns, for kind = 0..n-1 (at most
+ * all generations (and the dose reductions) as one launch, they are launched by themselves while timed.
+ * pbs_profile_read synchronises the stream and returns, for kind = 0..n-1 (at most
  * PBS_NKIND), the summed duration in ms and the number of launches since recording began. */
 enum { PBS_K_EPASS = 0, PBS_K_TPASS = 1, PBS_K_APASS = 2, PBS_K_QGEMM = 3, PBS_K_DOSE = 4, PBS_NKIND = 5 };
 pbs_status pbs_profile(pbs_ctx *ctx, int enable);

@@ -92,7 +92,7 @@ struct QParams {
     const T *W;             // [2][G][NLINE]
     T *Q;                   // [2][G][NLINE]
     unsigned short *Qb = nullptr;   // non-null: write the source in BF16 there instead (EParams::Qb layout)
-    const T *P2p;           // [Kp][Mp] P2 (k = source node, row = destination); Kp >= 128: padded with zeros
+    const T *P2p;           // [Kp][Mp] P2 (k = source node, row = destination), padded with zeros from 128 angles on
     int Kp, Mp;
     const unsigned short *Bh, *Bl;   // split-BF16 W (see EParams), split-BF16 path
     int NOCT;

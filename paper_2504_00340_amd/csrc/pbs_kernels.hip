@@ -2600,10 +2600,11 @@ static bool tat_takes(int nth, int ny, long nline)
 // leave too many CUs idle (5 x 7, 11 x 11, 40, one generation: 80 slabs, 32 against 31 us; 60: 36.7 against 37.7).  A
 // second round still beats the passes on one stream by 5 to 15 % (16 x 16, 7 x 7, 120, two generations 93 against 108
 // us; 12 x 16, 7 x 7, 60, four, FP64 149 against 163), except for wide grids of large slabs (8 x 20, 11 x 11, 160, one
-// generation of 77 KB 93 against 87).  With two generations the passes on two streams, if they may take them (overlap), are
-// the better ones where the slabs take long: us a step here | there, 16 x 20, 7 x 7, 100 (63 KB) 104 | 98; 12 x 20, 7 x 7, 100 (50 KB) 95 | 98; 10 x
-// 16, 11 x 11, 128 (77 KB) 129 | 123; 8 x 16, 11 x 11, 100 (62 KB) 101 | 108; FP64 16 x 20, 5 x 5, 100 (64 KB) 108 | 104; 8 x
-// 20, 7 x 7, 100 (63 KB) 109 | 112; 4 x 4, 11 x 11, 100 (31 KB) 105 | 100.  24 x 32, 5 x 5, 128 (77 KB) 120 | 130.
+// generation of 77 KB 93 against 87).  With two generations the passes on two streams, if they may take them (overlap),
+// are the better ones where the slabs take long: us a step here | there, 16 x 20, 7 x 7, 100 (63 KB) 104 | 98; 12 x 20,
+// 7 x 7, 100 (50 KB) 95 | 98; 10 x 16, 11 x 11, 128 (77 KB) 129 | 123; 8 x 16, 11 x 11, 100 (62 KB) 101 | 108; 24 x 32, 5 x 5,
+// 128 (77 KB) 120 | 130; FP64 16 x 20, 5 x 5, 100 (64 KB) 108 | 104; 8 x 20, 7 x 7, 100 (63 KB) 109 | 112; 4 x 4, 11 x 11,
+// 100 (31 KB) 105 | 100.
 template <typename T>
 bool tat_fits(int nth, int ny, long nline, long nstack, int ngen, bool overlap)
 {
@@ -3790,8 +3791,9 @@ template hipError_t launch_combine<double>(double *, const double *, double, dou
 // lateral tile; lane (pt, h) of wave w sums the slots a = 2 w + h, + 8, ... of every generation in turn, then the
 // eight partials of a cell are added in the order of (w, h).  What bounds it is the latency of its loads (a
 // few hundred KB): four waves and eight loads in flight per lane took a launch at 4 x 4 cells, 11 x 11
-// angles, two generations from 17 to 9 us, one at 45 x 70, 19 x 19, three from 35 to 13.  Sixteen-wave blocks lose that again where the
-// reduction runs beside the transport and angular passes (they wait for a whole CU to drain).
+// angles, two generations from 17 to 9 us, one at 45 x 70, 19 x 19, three from 35 to 13.  Sixteen-wave blocks lose that
+// again where the reduction runs beside the transport and angular passes (they wait for a whole CU to drain); one wave
+// that takes all four shares is quicker there by itself (114 -> 45 us) but no batch is (48 to 128 beams: the same).
 __device__ __forceinline__ void dose_reduce_body(double *edep, const double *dep, int ngen, int NA, int nslot,
                                                  long NLINE, int NP, int pb)
 {
@@ -4062,12 +4064,12 @@ __device__ __forceinline__ AParams<float> batch_aparams(const BeamDev &B, const 
     return P;
 }
 
-// held to eight waves per SIMD: the registers then do without the accumulation file, and the pass, which shares the chip
-// with the energy passes, leaves them more of it (20 beams of 16 x 32 cells, 15 x 15 angles 66.5 -> 66.0 ms, 24 of 32 x 32 with
-// three generations 273.2 -> 271.9)
+// Held to eight waves per SIMD: the registers then do without the accumulation file, and the pass, which shares the chip
+// with the energy passes, leaves them more of it (20 beams of 16 x 32 cells, 15 x 15 angles 66.5 -> 66.0 ms, 24 of
+// 32 x 32 with three generations 273.2 -> 271.9).
 template <int N>
-__global__ __launch_bounds__((AngMfma<float, N>::NT)) __attribute__((amdgpu_waves_per_eu(8))) void apass_batched_kernel(const BeamDev *__restrict__ beams,
-                                                                                 BatchShape Sh, int s, int k)
+__global__ __launch_bounds__((AngMfma<float, N>::NT)) __attribute__((amdgpu_waves_per_eu(8)))
+void apass_batched_kernel(const BeamDev *__restrict__ beams, BatchShape Sh, int s, int k)
 {
     const BeamDev &B = beams[blockIdx.z];
     if (s >= B.nz || blockIdx.y >= (unsigned)((k < 0 ? Sh.ngen : 1) * B.G * 2)) return;
