@@ -307,6 +307,17 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const __bf16 *__restrict__ i
 // block brings 256 partials of 32 entries at a time to LDS, all loads in flight and the next 256 behind them, and 32
 // lanes add them up: 121 -> 8 us for the 512 partials of 32 slices of 64 x 64 pixels.
 constexpr int WR_NB = 256;
+__device__ __forceinline__ void wgrad_store(long e, float s, int CIN, int COP, int cin, int cout, float *__restrict__ gw,
+                                            float *__restrict__ gb)
+{
+    if (e >= 9L * COP * CIN) {
+        const int co = (int)(e - 9L * COP * CIN);
+        if (co < cout) gb[co] = s;
+    } else {
+        const int tap = (int)(e / ((long)COP * CIN)), co = (int)((e / CIN) % COP), ci = (int)(e % CIN);
+        if (co < cout && ci < cin) gw[((long)co * cin + ci) * 9 + tap] = s;
+    }
+}
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ part, long nblk, int CIN, int COP,
                                                            int cin, int cout, float *__restrict__ gw,
                                                            float *__restrict__ gb)
@@ -334,14 +345,29 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
             for (int b = 0; b < n; ++b) s += red[b][le];
         }
     }
-    if (sub != 0 || e >= PSZ) return;
-    if (e >= 9L * COP * CIN) {
-        const int co = (int)(e - 9L * COP * CIN);
-        if (co < cout) gb[co] = s;
-    } else {
-        const int tap = (int)(e / ((long)COP * CIN)), co = (int)((e / CIN) % COP), ci = (int)(e % CIN);
-        if (co < cout && ci < cin) gw[((long)co * cin + ci) * 9 + tap] = s;
+    if (sub == 0 && e < PSZ) wgrad_store(e, s, CIN, COP, cin, cout, gw, gb);
+}
+
+// The same sums for few partials, where the staging costs more than the loads it hides: one thread per entry, eight
+// loads in flight.  us a training step (four sums) here | staged: 3 partials 121 | 126, 8 217 | 222, 24 223.5 | 225, 32 226.5 |
+// 225, 128 266 | 242.
+constexpr long WR_FEW = 24;
+__global__ __launch_bounds__(256) void wgrad_reduce_few_kernel(const float *__restrict__ part, long nblk, int CIN, int COP,
+                                                               int cin, int cout, float *__restrict__ gw,
+                                                               float *__restrict__ gb)
+{
+    const long PSZ = 9L * COP * CIN + COP, e = (long)blockIdx.x * 256 + threadIdx.x;
+    if (e >= PSZ) return;
+    float s = 0.f;
+    for (long b0 = 0; b0 < nblk; b0 += 8) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = part[min(b0 + i, nblk - 1) * PSZ + e];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (b0 + i < nblk) s += v[i];
     }
+    wgrad_store(e, s, CIN, COP, cin, cout, gw, gb);
 }
 
 template <int CIN, int COP>
@@ -351,8 +377,12 @@ static hipError_t wgrad(const __bf16 *in, const __bf16 *g, float *part, int n, i
     const long nblk = (long)n * ((H + WG_TR - 1) / WG_TR);
     const long PSZ = 9L * COP * CIN + COP;
     hipLaunchKernelGGL((wgrad_kernel<CIN, COP>), dim3((unsigned)nblk), dim3(256), 0, st, in, g, part, H, Wd);
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((PSZ + 31) / 32)), dim3(256), 0, st, part, nblk, CIN,
-                       COP, cin, cout, gw, gb);
+    if (nblk <= WR_FEW)
+        hipLaunchKernelGGL(wgrad_reduce_few_kernel, dim3((unsigned)((PSZ + 255) / 256)), dim3(256), 0, st, part, nblk,
+                           CIN, COP, cin, cout, gw, gb);
+    else
+        hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((PSZ + 31) / 32)), dim3(256), 0, st, part, nblk, CIN,
+                           COP, cin, cout, gw, gb);
     return hipGetLastError();
 }
 

@@ -109,6 +109,31 @@ def test_gradient_exact_on_integers(S):
     assert np.array_equal(g.astype(np.float64), g_ref), np.abs(g - g_ref).max()
 
 
+# n ceil(H / 4) partials of a weight's sum: one, around eight (loads in flight), 24 (the rule between the two kernels) and 256
+# (a staged chunk).  The last layer's gradient is exact at any size: activations are integers, the residuals powers of
+# two, so every term is an integer times 2 / pixels as BF16 holds it
+@pytest.mark.parametrize("shape", [(1, 3, 9), (1, 25, 11), (2, 13, 20), (3, 9, 12), (4, 21, 17), (5, 17, 13), (32, 32, 6), (257, 4, 3)])
+def test_gradient_sum_at_its_partial_counts(S, shape):
+    from paper_2504_00340_amd.pbsplit import Net
+
+    torch = _torch()
+    n, H, W = shape
+    print("case partial counts", shape, n * ((H + 3) // 4), flush=True)
+    r = np.random.Generator(np.random.PCG64(17))
+    p = _integer_net(S, 14)
+    x = r.integers(-2, 3, size=(n, H, W, 8)).astype(np.float64)
+    y, _ = S.forward(p, x)
+    t = y - r.choice([-2.0, -1.0, 1.0, 2.0], size=y.shape)
+    _, g_ref = S.loss_grad(p, x, t)
+    net = Net(H, W, n)
+    net.set_params(p)
+    g, _ = net.gradient(_dev_bf16(x), _dev_f32(t))
+    unit = float(torch.tensor(2.0 / y.size, dtype=torch.float32).to(torch.bfloat16))
+    for sl in _layer_slices(S)[3]:
+        want = np.rint(g_ref[sl] * y.size / 2.0) * unit
+        assert np.array_equal(g[sl].astype(np.float64), want), np.abs(g[sl] - want).max()
+
+
 @pytest.mark.parametrize("shape", [(3, 13, 37), (2, 64, 64)])
 def test_gradient_bf16_random(S, shape):
     from paper_2504_00340_amd.pbsplit import Net
